@@ -2028,9 +2028,10 @@ struct htn_model {
     int device = -1;
     float *d_p = nullptr, *d_m = nullptr, *d_v = nullptr, *d_g = nullptr;
     int64_t step = 0;  // Adam steps taken
-    int64_t cap = 0;   // samples the work arrays hold
-    float *d_x = nullptr, *d_t = nullptr, *d_y = nullptr, *d_z1 = nullptr, *d_z2 = nullptr, *d_d1 = nullptr,
-          *d_d2 = nullptr, *d_dy = nullptr, *d_loss = nullptr;
+    int64_t cap = 0;   // samples d_x and d_y hold (model_predict)
+    float *d_x = nullptr, *d_y = nullptr, *d_loss = nullptr;
+    float *d_part = nullptr;  // the gradient kernel's partial sums
+    int64_t part_cap = 0;
     int32_t *d_idx = nullptr;
     int64_t idx_cap = 0, loss_cap = 0;
     std::mutex predict_mu;  // model_predict shares d_x / d_y between threads
@@ -2051,25 +2052,25 @@ struct DeviceScope {
     }
 };
 
-void model_free_work(htn_model *m) {
-    for (float *p : {m->d_x, m->d_t, m->d_y, m->d_z1, m->d_z2, m->d_d1, m->d_d2, m->d_dy}) dfree(p);
-    m->d_x = m->d_t = m->d_y = m->d_z1 = m->d_z2 = m->d_d1 = m->d_d2 = m->d_dy = nullptr;
-    m->cap = 0;
-}
-
 void model_reserve(htn_model *m, int64_t n) {
     if (n <= m->cap) return;
-    model_free_work(m);
-    const int64_t F = HTN_MODEL_FEATURES, H = HTN_MODEL_HIDDEN;
-    m->d_x = dalloc<float>(n * F);
-    m->d_t = dalloc<float>(n);
+    for (float *p : {m->d_x, m->d_y}) dfree(p);
+    m->d_x = m->d_y = nullptr;
+    m->cap = 0;
+    m->d_x = dalloc<float>(n * HTN_MODEL_FEATURES);
     m->d_y = dalloc<float>(n);
-    m->d_z1 = dalloc<float>(n * H);
-    m->d_z2 = dalloc<float>(n * H);
-    m->d_d1 = dalloc<float>(n * H);
-    m->d_d2 = dalloc<float>(n * H);
-    m->d_dy = dalloc<float>(n);
     m->cap = n;
+}
+
+// Scratch for the gradients of n samples (at most 6 MB).
+void model_reserve_part(htn_model *m, int64_t n) {
+    const int64_t need = kern::mlp_part_floats(n);
+    if (need <= m->part_cap) return;
+    dfree(m->d_part);
+    m->d_part = nullptr;
+    m->part_cap = 0;
+    m->d_part = dalloc<float>(need);
+    m->part_cap = need;
 }
 
 uint64_t splitmix64(uint64_t &s) {
@@ -2092,7 +2093,7 @@ std::vector<float> model_predict(htn_model *m, const std::vector<float> &x) {
     DeviceScope ds(m->device);
     model_reserve(m, n);
     HIP_TRY(hipMemcpy(m->d_x, x.data(), x.size() * 4, hipMemcpyHostToDevice));
-    HIP_TRY(kern::launch_mlp_forward(m->d_p, m->d_x, nullptr, (int)n, m->d_y, nullptr, nullptr, nullptr));
+    HIP_TRY(kern::launch_mlp_forward(m->d_p, m->d_x, nullptr, (int)n, m->d_y, nullptr));
     HIP_TRY(hipMemcpy(y.data(), m->d_y, n * 4, hipMemcpyDeviceToHost));
     return y;
 }
@@ -2163,7 +2164,7 @@ htn_status htn_model_forward(htn_model_t m, int32_t n, const float *x, float *y,
     API_GUARD_BEGIN
     if (!m || n < 0 || (n > 0 && (!x || !y))) return fail(HTN_E_ARG, "bad arguments");
     DeviceScope ds(m->device);
-    HIP_TRY(kern::launch_mlp_forward(m->d_p, x, nullptr, n, y, nullptr, nullptr, (hipStream_t)hip_stream));
+    HIP_TRY(kern::launch_mlp_forward(m->d_p, x, nullptr, n, y, (hipStream_t)hip_stream));
     return HTN_OK;
     API_GUARD_END
 }
@@ -2173,11 +2174,9 @@ htn_status htn_model_gradients(htn_model_t m, int32_t n, const float *x, const f
     API_GUARD_BEGIN
     if (!m || n <= 0 || !x || !t || !grad) return fail(HTN_E_ARG, "bad arguments");
     DeviceScope ds(m->device);
-    model_reserve(m, n);
-    const hipStream_t st = (hipStream_t)hip_stream;
-    HIP_TRY(kern::launch_mlp_forward(m->d_p, x, nullptr, n, m->d_y, m->d_z1, m->d_z2, st));
-    HIP_TRY(kern::launch_mlp_backward(m->d_p, x, t, nullptr, n, m->d_y, m->d_z1, m->d_z2, m->d_d1, m->d_d2, m->d_dy,
-                                      grad, loss, st));
+    model_reserve_part(m, n);
+    HIP_TRY(kern::launch_mlp_gradients(m->d_p, x, t, nullptr, n, m->d_part, grad, loss, nullptr,
+                                       (hipStream_t)hip_stream));
     return HTN_OK;
     API_GUARD_END
 }
@@ -2186,7 +2185,7 @@ htn_status htn_model_adam_step(htn_model_t m, const float *grad, float lr, void 
     API_GUARD_BEGIN
     if (!m || !grad) return fail(HTN_E_ARG, "NULL argument");
     DeviceScope ds(m->device);
-    HIP_TRY(kern::launch_adam(m->d_p, m->d_m, m->d_v, grad, lr, ++m->step, (hipStream_t)hip_stream));
+    HIP_TRY(kern::launch_adam(kern::MlpAdam{m->d_p, m->d_m, m->d_v, lr, ++m->step}, grad, (hipStream_t)hip_stream));
     return HTN_OK;
     API_GUARD_END
 }
@@ -2199,7 +2198,7 @@ htn_status htn_model_train(htn_model_t m, int32_t n, const float *x, const float
     const hipStream_t st = (hipStream_t)hip_stream;
     const int32_t nb_max = std::min(batch, n);
     const int64_t n_mb = (n + nb_max - 1) / nb_max;
-    model_reserve(m, nb_max);
+    model_reserve_part(m, nb_max);
     if (m->idx_cap < n) {
         dfree(m->d_idx);
         m->d_idx = nullptr;
@@ -2222,10 +2221,9 @@ htn_status htn_model_train(htn_model_t m, int32_t n, const float *x, const float
         HIP_TRY(hipMemcpyAsync(m->d_idx, perm.data(), (size_t)n * 4, hipMemcpyHostToDevice, st));
         for (int64_t k = 0; k < n_mb; ++k) {
             const int32_t b0 = (int32_t)(k * nb_max), nb = std::min<int32_t>(nb_max, n - b0);
-            HIP_TRY(kern::launch_mlp_forward(m->d_p, x, m->d_idx + b0, nb, m->d_y, m->d_z1, m->d_z2, st));
-            HIP_TRY(kern::launch_mlp_backward(m->d_p, x, t, m->d_idx + b0, nb, m->d_y, m->d_z1, m->d_z2, m->d_d1,
-                                              m->d_d2, m->d_dy, m->d_g, m->d_loss + k, st));
-            HIP_TRY(kern::launch_adam(m->d_p, m->d_m, m->d_v, m->d_g, lr, ++m->step, st));
+            const kern::MlpAdam adam{m->d_p, m->d_m, m->d_v, lr, ++m->step};
+            HIP_TRY(kern::launch_mlp_gradients(m->d_p, x, t, m->d_idx + b0, nb, m->d_part, m->d_g, m->d_loss + k, &adam,
+                                               st));
         }
         // the permutation buffer is reused next epoch: wait for this one
         HIP_TRY(hipStreamSynchronize(st));
@@ -2242,8 +2240,7 @@ htn_status htn_model_train(htn_model_t m, int32_t n, const float *x, const float
 
 void htn_model_destroy(htn_model_t m) {
     if (!m) return;
-    model_free_work(m);
-    for (float *p : {m->d_p, m->d_m, m->d_v, m->d_g, m->d_loss}) dfree(p);
+    for (float *p : {m->d_x, m->d_y, m->d_part, m->d_p, m->d_m, m->d_v, m->d_g, m->d_loss}) dfree(p);
     dfree(m->d_idx);
     delete m;
 }

@@ -296,18 +296,22 @@ hipError_t launch_truncate(const TruncItem *items, const TruncBlock *blocks, int
                            int elem_bytes, hipStream_t st);
 
 // Cost-model MLP (mlp.hip).  Samples are rows of x ([.][HTN_MODEL_FEATURES]);
-// idx (optional) maps batch position s to its row.  z1, z2, d1, d2 are
-// [n][HTN_MODEL_HIDDEN] work arrays; forward keeps pre-activations in
-// z1/z2 when they are non-null.  backward writes d(loss)/d(params) to grad
-// and, when loss is non-null, the batch's mean squared error.
+// idx (optional) maps batch position s to its row.  launch_mlp_gradients
+// writes d(loss)/d(params) to grad and, when loss is non-null, the batch's
+// mean squared error; with adam non-null the parameters take an Adam step
+// (b1 0.9, b2 0.999, eps 1e-8; step counts from 1) with that gradient.
+// part: mlp_part_floats(n) floats of scratch.
+struct MlpAdam {
+    float *p, *m, *v;
+    float lr;
+    int64_t step;
+};
 int64_t model_param_count();
-hipError_t launch_mlp_forward(const float *prm, const float *x, const int32_t *idx, int n, float *y, float *z1,
-                              float *z2, hipStream_t st);
-hipError_t launch_mlp_backward(const float *prm, const float *x, const float *t, const int32_t *idx, int n,
-                               const float *y, const float *z1, const float *z2, float *d1, float *d2, float *dy,
-                               float *grad, float *loss, hipStream_t st);
-// One Adam step (b1 0.9, b2 0.999, eps 1e-8); step counts from 1.
-hipError_t launch_adam(float *p, float *m, float *v, const float *g, float lr, int64_t step, hipStream_t st);
+int64_t mlp_part_floats(int64_t n);
+hipError_t launch_mlp_forward(const float *prm, const float *x, const int32_t *idx, int n, float *y, hipStream_t st);
+hipError_t launch_mlp_gradients(const float *prm, const float *x, const float *t, const int32_t *idx, int n,
+                                float *part, float *grad, float *loss, const MlpAdam *adam, hipStream_t st);
+hipError_t launch_adam(const MlpAdam &a, const float *g, hipStream_t st);
 
 }  // namespace kern
 }  // namespace htn

@@ -64,6 +64,29 @@ def test_gradients_match_oracle():
     assert float(loss.item()) == pytest.approx(mlp_ref.loss(p, X, t), rel=1e-5)
 
 
+@pytest.mark.parametrize("n", [1, 16, 17, 63, 64, 65, 16384, 16385])
+def test_gradient_tiles_match_oracle(n):
+    """Edges of a wave's 16 samples, of a 64-sample tile and of the launch
+    (256 tiles; one more sample makes a workgroup take a second tile)."""
+    import torch
+    m, p = _model(12)
+    X, t = _data(n, n)
+    x, tt = torch.from_numpy(X).cuda(), torch.from_numpy(t).cuda()
+    g = torch.full((htn.htn_model_param_count(),), np.nan, dtype=torch.float32, device="cuda")
+    y = torch.full((n + 8,), 7.0, dtype=torch.float32, device="cuda")
+    loss = torch.empty(1, dtype=torch.float32, device="cuda")
+    htn.htn_model_gradients(m, x, tt, g, loss)
+    htn.htn_model_forward(m, x, y[:n])
+    torch.cuda.synchronize()
+    ref = mlp_ref.gradients(p, X.astype(np.float64), t.astype(np.float64))
+    got = g.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 1e-4 * np.linalg.norm(ref)
+    assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+    assert float(loss.item()) == pytest.approx(mlp_ref.loss(p, X, t), rel=1e-5)
+    np.testing.assert_allclose(y[:n].cpu().numpy(), mlp_ref.forward(p, X.astype(np.float64))[0], rtol=1e-4, atol=1e-4)
+    assert bool((y[n:] == 7.0).all())
+
+
 def test_gradients_are_bit_reproducible():
     import torch
     m, _ = _model(4)
