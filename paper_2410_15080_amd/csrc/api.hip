@@ -17,6 +17,7 @@
 #include "htn_core.hpp"
 #include "kernels.hpp"
 #include "mfma_dev.hpp"
+#include "sv_plan.hpp"
 
 using namespace htn;
 
@@ -2704,22 +2705,152 @@ static void run_sliced(Net &n, void *out, hipStream_t st) {
 // ---------------------------------------------------------------------------
 
 struct htn_qteval {
-    int n_inst = 0;
     int64_t n_outputs = 0, n_entries = 0;
+    kern::SvLaunch launch;  // device arrays below and how they are launched
     kern::SvInst *d_insts = nullptr;
-    kern::SvOp *d_ops = nullptr;
-    double2 *d_state = nullptr;
+    kern::SvState *d_states = nullptr;
+    kern::SvPass *d_passes = nullptr;
+    SvRecord *d_recs = nullptr;
+    double2 *d_gstate = nullptr;
     double *d_outs = nullptr;
     int64_t *d_start = nullptr, *d_term = nullptr;
     double *d_coef = nullptr;
     ~htn_qteval() {
         dfree(d_insts);
-        dfree(d_ops);
-        dfree(d_state);
+        dfree(d_states);
+        dfree(d_passes);
+        dfree(d_recs);
+        dfree(d_gstate);
         dfree(d_outs);
         dfree(d_start);
         dfree(d_term);
         dfree(d_coef);
+    }
+};
+
+// The device form of a handle's instances, while it is built.
+struct SvBuild {
+    struct Ops {  // one distinct op list of an n-qubit instance
+        SvSchedule sched;
+        int64_t pass0 = 0;
+    };
+    std::vector<kern::SvInst> insts[3];
+    std::vector<kern::SvState> states[3];
+    std::vector<kern::SvPass> passes;
+    std::vector<SvRecord> recs;
+    std::unordered_map<std::string, Ops> ops_of;         // by qubits and op bytes
+    std::unordered_map<std::string, int32_t> large_of;   // class 2 states by op list and preparation
+    int64_t n_amps = 0;
+    int n_pass = 0;
+
+    static int class_of(int n) { return n <= kern::kSvTinyQubits ? 0 : (n <= kern::kSvLdsQubits ? 1 : 2); }
+
+    // x: a validated instance; k: its measurement, all but the state set.
+    void add(const htn_sv_instance &x, kern::SvInst k) {
+        const int n = x.n_qubits, c = class_of(n);
+        const int32_t above = ((1 << n) - 1) & ~63;  // amplitude bits that no lane spells
+        k.waves = kern::sv_meas_waves(int64_t(1) << __builtin_popcount(above & ~k.kept_mask),
+                                      c == 0   ? kern::kSvThreads0 / 64
+                                      : c == 1 ? kern::kSvThreads1 / 64
+                                               : kern::kSvMeasWaves);
+        std::string key((const char *)&x.n_qubits, sizeof(x.n_qubits));
+        for (int j = 0; j < x.n_ops; ++j) {
+            const htn_sv_op &o = x.ops[j];
+            key.append((const char *)&o.kind, 3 * sizeof(int32_t));
+            if (o.kind == HTN_SV_U1 || o.kind == HTN_SV_RZZ) key.append((const char *)o.m, sizeof(o.m));
+        }
+        auto it = ops_of.find(key);
+        if (it == ops_of.end()) {
+            Ops ops;
+            const int K = c == 0 ? kern::kSvRegBits0 : (c == 1 ? kern::kSvRegBits1 : kern::kSvRegBits2);
+            ops.sched = sv_schedule(n, x.ops, x.n_ops, c == 2 ? kern::kSvTileBits : std::max(K, n), K);
+            ops.pass0 = (int64_t)passes.size();
+            for (const SvSchedule::Pass &p : ops.sched.passes) {
+                kern::SvPass d;
+                std::memset(&d, 0, sizeof(d));
+                d.rec0 = (int64_t)recs.size();
+                d.n_rec = (int32_t)p.recs.size();
+                for (size_t j = 0; j < p.lpos.size(); ++j) d.lpos[j] = (uint8_t)p.lpos[j];
+                for (size_t j = 0; j < p.hpos.size(); ++j) d.hpos[j] = (uint8_t)p.hpos[j];
+                recs.insert(recs.end(), p.recs.begin(), p.recs.end());
+                passes.push_back(d);
+            }
+            it = ops_of.emplace(std::move(key), std::move(ops)).first;
+        }
+        const Ops &ops = it->second;
+        // a large state is evolved once for all instances that differ in
+        // their measurement only
+        if (c == 2) {
+            std::string sk((const char *)&ops.pass0, sizeof(ops.pass0));
+            sk.append((const char *)x.init, 4 * sizeof(double) * (size_t)n);
+            const auto f = large_of.emplace(std::move(sk), (int32_t)states[2].size());
+            k.state = f.first->second;
+            if (!f.second) {
+                insts[2].push_back(k);
+                return;
+            }
+        } else {
+            k.state = (int32_t)states[c].size();
+        }
+        kern::SvState e;
+        std::memset(&e, 0, sizeof(e));
+        e.n = n;
+        e.n_pass = (int32_t)ops.sched.passes.size();
+        e.pass0 = ops.pass0;
+        for (int q = 0; q < n; ++q) {
+            const double *u = &ops.sched.lead[8 * (size_t)q], *v = x.init + 4 * q;
+            double *d = e.init[n - 1 - q];
+            for (int r = 0; r < 2; ++r) {
+                d[2 * r] = (u[4 * r] * v[0] - u[4 * r + 1] * v[1]) + (u[4 * r + 2] * v[2] - u[4 * r + 3] * v[3]);
+                d[2 * r + 1] = (u[4 * r] * v[1] + u[4 * r + 1] * v[0]) + (u[4 * r + 2] * v[3] + u[4 * r + 3] * v[2]);
+            }
+        }
+        if (c == 2) {
+            e.off = n_amps;
+            n_amps += int64_t(1) << n;
+            n_pass = std::max(n_pass, (int)e.n_pass);
+        }
+        states[c].push_back(e);
+        insts[c].push_back(k);
+    }
+
+    void upload(htn_qteval &q) {
+        kern::SvLaunch &L = q.launch;
+        std::vector<kern::SvInst> hi;
+        std::vector<kern::SvState> hs;
+        for (int c = 0; c < 3; ++c) {
+            kern::SvClass &k = L.cls[c];
+            k.inst0 = (int64_t)hi.size();
+            k.n_insts = (int64_t)insts[c].size();
+            for (kern::SvInst i : insts[c]) {
+                k.max_n = std::max(k.max_n, (int)i.n);
+                const int64_t tasks = int64_t(1) << __builtin_popcount(i.kept_mask & ~63);
+                k.parts = std::max(k.parts, (int)std::min<int64_t>(1024, tasks * i.waves / kern::kSvMeasWaves));
+                i.state += (int32_t)hs.size();
+                hi.push_back(i);
+            }
+            if (c == 2) {
+                L.large0 = (int64_t)hs.size();
+                L.n_large = (int64_t)states[c].size();
+            }
+            hs.insert(hs.end(), states[c].begin(), states[c].end());
+        }
+        L.n_pass = n_pass;
+        auto up = [](auto *&d, const auto &h) {
+            typedef typename std::decay<decltype(h[0])>::type E;
+            d = dalloc<E>(std::max<size_t>(1, h.size()));
+            if (!h.empty()) HIP_TRY(hipMemcpy(d, h.data(), h.size() * sizeof(E), hipMemcpyHostToDevice));
+        };
+        up(q.d_insts, hi);
+        up(q.d_states, hs);
+        up(q.d_passes, passes);
+        up(q.d_recs, recs);
+        if (n_amps > 0) q.d_gstate = dalloc<double2>((size_t)n_amps);
+        L.insts = q.d_insts;
+        L.states = q.d_states;
+        L.passes = q.d_passes;
+        L.recs = q.d_recs;
+        L.gstate = q.d_gstate;
     }
 };
 
@@ -2733,26 +2864,22 @@ htn_status htn_qt_eval_create(htn_qteval_t *out, int32_t n_instances, const htn_
     *out = nullptr;
     if (n_instances < 1 || !instances) return fail(HTN_E_ARG, "bad instance list");
     if (n_entries < 0 || (n_entries > 0 && !entry_start)) return fail(HTN_E_ARG, "bad entry list");
-    std::vector<kern::SvInst> hi((size_t)n_instances);
-    std::vector<kern::SvOp> hops;
-    int64_t n_out = 0, n_state = 0;
+    SvBuild build;
+    int64_t n_out = 0;
     for (int i = 0; i < n_instances; ++i) {
         const htn_sv_instance &x = instances[i];
         const std::string it = "instance " + std::to_string(i) + ": ";
         if (x.n_qubits < 1 || x.n_qubits > HTN_SV_MAX_QUBITS) return fail(HTN_E_ARG, it + "bad qubit count");
         if (!x.init || !x.observable || (x.n_ops > 0 && !x.ops) || x.n_ops < 0) return fail(HTN_E_ARG, it + "NULL data");
         if (x.n_kept < 0 || x.n_kept > x.n_qubits || (x.n_kept > 0 && !x.kept)) return fail(HTN_E_ARG, it + "bad kept list");
-        kern::SvInst &k = hi[(size_t)i];
+        kern::SvInst k;
         std::memset(&k, 0, sizeof(k));
         const int n = x.n_qubits;
         k.n = n;
-        k.n_ops = x.n_ops;
         k.n_kept = x.n_kept;
-        k.op_off = (int64_t)hops.size();
         k.out_off = n_out;
         for (int q = 0; q < n; ++q) {
-            for (int c = 0; c < 4; ++c) k.init[q][c] = x.init[4 * q + c];
-            const int64_t bit = int64_t(1) << (n - 1 - q);
+            const int32_t bit = 1 << (n - 1 - q);
             switch (x.observable[q]) {
                 case 'I': break;
                 case 'X': k.xmask |= bit; break;
@@ -2766,7 +2893,8 @@ htn_status htn_qt_eval_create(htn_qteval_t *out, int32_t n_instances, const htn_
             if (q < 0 || q >= n || x.observable[q] != 'I') return fail(HTN_E_ARG, it + "kept qubit out of range or not I");
             for (int j2 = 0; j2 < j; ++j2)
                 if (x.kept[j2] == q) return fail(HTN_E_ARG, it + "kept qubit repeated");
-            k.kept[j] = q;
+            k.kept_pos[j] = n - 1 - q;
+            k.kept_mask |= 1 << (n - 1 - q);
         }
         for (int j = 0; j < x.n_ops; ++j) {
             const htn_sv_op &o = x.ops[j];
@@ -2775,21 +2903,9 @@ htn_status htn_qt_eval_create(htn_qteval_t *out, int32_t n_instances, const htn_
             if (o.q0 < 0 || o.q0 >= n) return fail(HTN_E_ARG, it + "op qubit out of range");
             if (two && (o.q1 < 0 || o.q1 >= n || o.q1 == o.q0)) return fail(HTN_E_ARG, it + "bad second qubit");
             if (o.kind == HTN_SV_PROJ && o.q1 != 0 && o.q1 != 1) return fail(HTN_E_ARG, it + "projection bit not 0/1");
-            kern::SvOp d;
-            d.kind = o.kind;
-            d.q0 = o.q0;
-            d.q1 = o.q1;
-            d.pad = 0;
-            for (int c = 0; c < 8; ++c) d.m[c] = o.m[c];
-            hops.push_back(d);
         }
         n_out += int64_t(1) << x.n_kept;
-        if (n > kern::kSvLdsQubits) {
-            k.state_off = n_state;
-            n_state += int64_t(1) << n;
-        } else {
-            k.state_off = -1;
-        }
+        build.add(x, k);
     }
     if (n_entries > 0) {
         if (entry_start[0] != 0) return fail(HTN_E_ARG, "entry_start[0] must be 0");
@@ -2802,15 +2918,9 @@ htn_status htn_qt_eval_create(htn_qteval_t *out, int32_t n_instances, const htn_
     }
     auto *q = new htn_qteval();
     try {
-        q->n_inst = n_instances;
         q->n_outputs = n_out;
         q->n_entries = n_entries;
-        q->d_insts = dalloc<kern::SvInst>(hi.size());
-        HIP_TRY(hipMemcpy(q->d_insts, hi.data(), hi.size() * sizeof(kern::SvInst), hipMemcpyHostToDevice));
-        q->d_ops = dalloc<kern::SvOp>(std::max<size_t>(1, hops.size()));
-        if (!hops.empty())
-            HIP_TRY(hipMemcpy(q->d_ops, hops.data(), hops.size() * sizeof(kern::SvOp), hipMemcpyHostToDevice));
-        if (n_state > 0) q->d_state = dalloc<double2>((size_t)n_state);
+        build.upload(*q);
         q->d_outs = dalloc<double>((size_t)n_out);
         if (n_entries > 0) {
             const int64_t n_terms = entry_start[n_entries];
@@ -2838,7 +2948,7 @@ htn_status htn_qt_eval_run(htn_qteval_t q, double *entries, double *outputs, voi
     if (q->n_entries > 0 && !entries) return fail(HTN_E_ARG, "entries is NULL");
     const hipStream_t st = (hipStream_t)hip_stream;
     double *outs = outputs ? outputs : q->d_outs;
-    HIP_TRY(kern::launch_sv_eval(q->d_insts, q->n_inst, q->d_ops, q->d_state, outs, st));
+    HIP_TRY(kern::launch_sv_eval(q->launch, outs, st));
     HIP_TRY(kern::launch_qt_assemble(q->d_start, q->d_term, q->d_coef, q->n_entries, outs, entries, st));
     return HTN_OK;
     API_GUARD_END

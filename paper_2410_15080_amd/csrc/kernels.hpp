@@ -115,25 +115,72 @@ inline int fprep_form(int rank, int n_scales) {
     return 2;
 }
 
-// QT evaluator (qteval.hip): statevector instances, one workgroup each.
+// QT evaluator (qteval.hip).
+}  // namespace kern
+struct SvRecord;  // sv_plan.hpp
+namespace kern {
 constexpr int kSvMaxQubits = 24;
 constexpr int kSvLdsQubits = 12;  // states of at most this many qubits live in LDS
-enum SvKind { SV_U1 = 0, SV_CZ = 1, SV_CX = 2, SV_RZZ = 3, SV_PROJ = 4 };
-struct SvOp {
-    int32_t kind, q0, q1, pad;  // PROJ: q1 = the bit kept
-    double m[8];                // U1: u00, u01, u10, u11 as (re, im); RZZ: m[0] = theta
+// Instance classes: 0: up to kSvTinyQubits qubits, one wave each; 1: up to
+// kSvLdsQubits; 2: states in device memory, in tiles of kSvTileBits bits.
+// Register bits and threads of each.  Measured (whole calls): class 1 at
+// three register bits and 512 threads 50.3 us for 80 instances of 12 qubits
+// (four and 256: 66.8; tiles in device memory from 11 qubits on: 51.9); class
+// 2 in tiles of 10 bits 100.6 us for 37 states of 15 qubits and 42.3 for 13
+// and 14 qubits (12 bits and 512 threads: 110.3 and 47.6, too few workgroups
+// for the chip); a wave per tiny instance keeps its barriers free.
+constexpr int kSvTinyQubits = 8;
+constexpr int kSvRegBits0 = 2, kSvThreads0 = 64;
+constexpr int kSvRegBits1 = 3, kSvThreads1 = 512;
+constexpr int kSvTileBits = 10, kSvRegBits2 = 2, kSvThreads2 = 256;
+static_assert((1 << (kSvTinyQubits - kSvRegBits0)) <= kSvThreads0 && (1 << (kSvLdsQubits - kSvRegBits1)) <= kSvThreads1 &&
+                  (1 << (kSvTileBits - kSvRegBits2)) <= kSvThreads2,
+              "every group of a state has a thread");
+// A state to be prepared and evolved (init[p]: vector of the qubit at
+// amplitude bit p).
+struct SvState {
+    int32_t n, n_pass;
+    int64_t pass0;  // its passes (SvLaunch::passes)
+    int64_t off;    // amplitudes into gstate (class 2)
+    double init[kSvMaxQubits][4];  // (re0, im0, re1, im1)
+};
+struct SvPass {
+    int64_t rec0;  // its records (SvLaunch::recs)
+    int32_t n_rec;
+    uint8_t lpos[kSvLdsQubits];                // amplitude bits of the tile
+    uint8_t hpos[kSvMaxQubits - kSvTileBits];  // amplitude bits of the tile number
 };
 struct SvInst {
-    int32_t n, n_ops, n_kept, n_y;  // n_y: qubits measured in Y
-    int64_t op_off;                 // first op
-    int64_t out_off;                // first output (2^n_kept of them)
-    int64_t state_off;              // offset (amplitudes) in the global state buffer; -1: LDS
-    int64_t xmask, zymask;          // amplitude-index bits of X|Y qubits and of Z|Y qubits
-    int32_t kept[kSvMaxQubits];
-    double init[kSvMaxQubits][4];   // (re0, im0, re1, im1) per qubit
+    int32_t n, n_kept, n_y, state;   // n_y: qubits measured in Y
+    int64_t out_off;                 // first output (2^n_kept of them)
+    int32_t xmask, zymask;           // amplitude bits of X|Y qubits and of Z|Y qubits
+    int32_t kept_mask, waves;        // waves: that share an output's sum (sv_meas_waves)
+    int32_t kept_pos[kSvMaxQubits];  // amplitude bits of the kept qubits, in output order
 };
-hipError_t launch_sv_eval(const SvInst *insts, int n_insts, const SvOp *ops, double2 *gstate, double *outs,
-                          hipStream_t st);
+struct SvClass {
+    int64_t inst0 = 0, n_insts = 0;  // its instances
+    int max_n = 0;
+    int parts = 1;  // class 2: most workgroups an instance's measurement fills
+};
+struct SvLaunch {
+    const SvInst *insts = nullptr;
+    const SvState *states = nullptr;
+    const SvPass *passes = nullptr;
+    const SvRecord *recs = nullptr;
+    double2 *gstate = nullptr;
+    SvClass cls[3];
+    int64_t large0 = 0, n_large = 0;  // the class 2 states
+    int n_pass = 0;                   // most passes of a class 2 state
+};
+constexpr int kSvMeasWaves = 16;  // per workgroup of the class 2 measurement
+// Waves (of at most `most`) that share a sum of n_iter steps of 64 terms: four
+// steps' loads are in flight together, so each takes at least four.
+inline int sv_meas_waves(int64_t n_iter, int most) {
+    int w = 1;
+    while (w < most && n_iter >= 8 * w) w <<= 1;
+    return w;
+}
+hipError_t launch_sv_eval(const SvLaunch &L, double *outs, hipStream_t st);
 hipError_t launch_qt_assemble(const int64_t *start, const int64_t *term_out, const double *coef, int64_t n_entries,
                               const double *outs, double *entries, hipStream_t st);
 

@@ -1,0 +1,294 @@
+// Scheduling of statevector ops into register groups and tile passes (see
+// sv_plan.hpp).
+#include "sv_plan.hpp"
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+namespace htn {
+
+namespace {
+
+// Ops looked ahead (in program order) when a group or a tile is chosen: the
+// search stays linear in the number of ops.
+constexpr int kWindow = 256;
+
+enum { U1, CZ, CX, RZZ, PROJ };
+
+struct Op {
+    int kind;
+    int need = -1;  // amplitude bit that must be a register bit (-1: none)
+    int p0 = 0, p1 = 0;
+    double m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int bit = 0;               // PROJ: the value kept
+    std::vector<int> preds;    // ops that must come before
+    bool done = false;
+};
+
+// c = a * b, 2x2 complex row-major (re, im)
+void mul2(const double *a, const double *b, double *c) {
+    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j) {
+            double re = 0.0, im = 0.0;
+            for (int k = 0; k < 2; ++k) {
+                const double *x = a + 4 * i + 2 * k, *y = b + 4 * k + 2 * j;
+                re += x[0] * y[0] - x[1] * y[1];
+                im += x[0] * y[1] + x[1] * y[0];
+            }
+            c[4 * i + 2 * j] = re;
+            c[4 * i + 2 * j + 1] = im;
+        }
+}
+
+struct Scheduler {
+    std::vector<Op> ops;
+    std::vector<int> left;   // ops not yet run, program order
+    std::vector<int> mark;   // trial runs: mark[i] == stamp
+    int stamp = 0;
+
+    bool ready(int i) const {
+        for (int p : ops[i].preds)
+            if (!ops[p].done && mark[p] != stamp) return false;
+        return true;
+    }
+    // Worth of the ops that can run with register (or tile) bits `set`, in
+    // program order within the window; `order`, if given, receives them.
+    // A CZ waits for one of its bits.
+    int trial(uint32_t set, std::vector<int> *order) {
+        ++stamp;
+        int n = 0, seen = 0;
+        for (int i : left) {
+            if (++seen > kWindow) break;
+            const Op &o = ops[i];
+            if (o.need >= 0 && !((set >> o.need) & 1)) continue;
+            if (o.kind == CZ && !((set >> o.p0) & 1) && !((set >> o.p1) & 1)) continue;
+            if (!ready(i)) continue;
+            mark[i] = stamp;
+            n += o.need >= 0 ? 4 : 1;
+            if (order) order->push_back(i);
+        }
+        return n;
+    }
+    // `count` bits out of `from`, starting from `set`: each time the bit
+    // that lets the most ops run (the lowest among equals).
+    uint32_t choose(uint32_t from, uint32_t set, int count) {
+        while (__builtin_popcount(set) < count) {
+            int best = -1, best_n = -1;
+            for (int p = 0; p < 32; ++p) {
+                if (!((from >> p) & 1) || ((set >> p) & 1)) continue;
+                const int n = trial(set | (1u << p), nullptr);
+                if (n > best_n) {
+                    best_n = n;
+                    best = p;
+                }
+            }
+            set |= 1u << best;
+        }
+        return set;
+    }
+    void finish(const std::vector<int> &run) {
+        for (int i : run) ops[i].done = true;
+        left.erase(std::remove_if(left.begin(), left.end(), [&](int i) { return ops[i].done; }), left.end());
+    }
+};
+
+// The records of one group's ops (program order; reg[p]: register bit of
+// amplitude bit p, or -1).
+void emit_group(const Scheduler &S, const std::vector<int> &run, const std::vector<int> &reg, int K,
+                std::vector<SvRecord> &recs) {
+    std::vector<SvRecord> layers;
+    int u_next[kSvMaxRegBits], z_next[kSvMaxRegBits];  // first layer a unitary / a CZ on the bit may join
+    auto fresh = [] {
+        SvRecord x;
+        std::memset(&x, 0, sizeof(x));
+        x.kind = SVR_LAYER;
+        return x;
+    };
+    auto layer = [&](int l) -> SvRecord & {
+        while ((int)layers.size() <= l) layers.push_back(fresh());
+        return layers[l];
+    };
+    auto close = [&] {
+        recs.insert(recs.end(), layers.begin(), layers.end());
+        layers.clear();
+        for (int k = 0; k < kSvMaxRegBits; ++k) u_next[k] = z_next[k] = 0;
+    };
+    close();
+    for (int i : run) {
+        const Op &o = S.ops[i];
+        if (o.kind == U1) {
+            const int k = reg[o.p0], l = u_next[k];
+            SvRecord &x = layer(l);
+            x.a |= 1 << k;
+            std::memcpy(x.m[k], o.m, sizeof(o.m));
+            u_next[k] = z_next[k] = l + 1;
+        } else if (o.kind == CZ) {
+            const int k0 = reg[o.p0], k1 = reg[o.p1];
+            const int l = std::max(k0 >= 0 ? z_next[k0] : 0, k1 >= 0 ? z_next[k1] : 0);
+            SvRecord &x = layer(l);
+            x.a |= kSvLayerSigns;
+            if (k0 >= 0 && k1 >= 0) {
+                for (int r = 0; r < (1 << K); ++r)
+                    if (((r >> k0) & 1) && ((r >> k1) & 1)) x.b ^= 1 << r;
+            } else {
+                x.adj[k0 >= 0 ? k0 : k1] ^= 1 << (k0 >= 0 ? o.p1 : o.p0);
+            }
+            // the signs come before the layer's unitaries
+            for (int k : {k0, k1})
+                if (k >= 0) u_next[k] = std::max(u_next[k], l);
+        } else {
+            close();
+            SvRecord x = fresh();
+            std::memcpy(x.m[0], o.m, sizeof(o.m));
+            if (o.kind == CX) {
+                x.kind = SVR_CX;
+                x.a = reg[o.p1];
+                x.b = 1 << o.p0;
+            } else if (o.kind == RZZ) {
+                x.kind = SVR_RZZ;
+                x.a = o.p0;
+                x.b = o.p1;
+            } else {
+                x.kind = SVR_PROJ;
+                x.b = 1 << o.p0;
+                x.c = o.bit;
+            }
+            recs.push_back(x);
+        }
+    }
+    close();
+}
+
+}  // namespace
+
+SvSchedule sv_schedule(int n, const htn_sv_op *in, int n_ops, int tile, int K) {
+    SvSchedule out;
+    const int nb = std::max(n, K);  // amplitude bits (bits n.. of a padded small state stay 0)
+    static const double one[8] = {1, 0, 0, 0, 0, 0, 1, 0};
+    out.lead.resize(8 * (size_t)n);
+    for (int q = 0; q < n; ++q) std::memcpy(&out.lead[8 * (size_t)q], one, sizeof(one));
+    Scheduler S;
+    // consecutive single-qubit unitaries of a qubit become one matrix
+    std::vector<double> pend(8 * (size_t)n);
+    std::vector<char> has(n, 0), touched(n, 0);
+    auto push = [&](Op o) { S.ops.push_back(std::move(o)); };
+    auto flush = [&](int q) {
+        if (has[q]) {
+            if (!touched[q]) {
+                std::memcpy(&out.lead[8 * (size_t)q], &pend[8 * (size_t)q], sizeof(one));
+            } else {
+                Op o;
+                o.kind = U1;
+                o.need = o.p0 = n - 1 - q;
+                std::memcpy(o.m, &pend[8 * (size_t)q], sizeof(o.m));
+                push(o);
+            }
+            has[q] = 0;
+        }
+        touched[q] = 1;
+    };
+    for (int k = 0; k < n_ops; ++k) {
+        const htn_sv_op &x = in[k];
+        if (x.kind == HTN_SV_U1) {
+            double *p = &pend[8 * (size_t)x.q0];
+            if (has[x.q0]) {
+                double t[8];
+                mul2(x.m, p, t);
+                std::memcpy(p, t, sizeof(t));
+            } else {
+                std::memcpy(p, x.m, sizeof(one));
+            }
+            has[x.q0] = 1;
+            continue;
+        }
+        flush(x.q0);
+        Op o;
+        o.p0 = n - 1 - x.q0;
+        if (x.kind == HTN_SV_PROJ) {
+            o.kind = PROJ;
+            o.bit = x.q1;
+        } else {
+            flush(x.q1);
+            o.p1 = n - 1 - x.q1;
+            o.kind = x.kind == HTN_SV_CZ ? CZ : (x.kind == HTN_SV_CX ? CX : RZZ);
+            if (x.kind == HTN_SV_CX) o.need = o.p1;  // the control may be any bit
+            if (x.kind == HTN_SV_RZZ) {
+                o.m[0] = std::cos(0.5 * x.m[0]);
+                o.m[1] = std::sin(0.5 * x.m[0]);
+            }
+        }
+        push(o);
+    }
+    for (int q = 0; q < n; ++q) flush(q);
+    // order kept: an op that changes a bit against every other op on it;
+    // diagonal ops (and controls) on a bit commute with each other
+    {
+        std::vector<int> last(nb, -1);
+        std::vector<std::vector<int>> diag(nb);
+        for (int i = 0; i < (int)S.ops.size(); ++i) {
+            Op &o = S.ops[i];
+            auto diagonal = [&](int p) {
+                if (last[p] >= 0) o.preds.push_back(last[p]);
+                diag[p].push_back(i);
+            };
+            auto changing = [&](int p) {
+                if (last[p] >= 0) o.preds.push_back(last[p]);
+                o.preds.insert(o.preds.end(), diag[p].begin(), diag[p].end());
+                diag[p].clear();
+                last[p] = i;
+            };
+            if (o.kind == U1) {
+                changing(o.p0);
+            } else {
+                diagonal(o.p0);
+                if (o.kind == CX)
+                    changing(o.p1);
+                else if (o.kind != PROJ)
+                    diagonal(o.p1);
+            }
+            S.left.push_back(i);
+        }
+        S.mark.assign(S.ops.size(), 0);
+    }
+    const uint32_t all = nb >= 32 ? ~0u : (1u << nb) - 1;
+    // a tile holds the three lowest bits: 128-byte runs of the state
+    const uint32_t low = std::min<uint32_t>(all, 7u);
+    do {
+        const uint32_t tset = tile >= nb ? all : S.choose(all, low, tile);
+        SvSchedule::Pass P;
+        std::vector<int> local(32, -1);
+        for (int p = 0; p < nb; ++p) {
+            if ((tset >> p) & 1) {
+                local[p] = (int)P.lpos.size();
+                P.lpos.push_back(p);
+            } else {
+                P.hpos.push_back(p);
+            }
+        }
+        while (!S.left.empty()) {
+            const uint32_t rset = S.choose(tset, 0, K);
+            std::vector<int> run;
+            S.trial(rset, &run);
+            if (run.empty()) break;  // the rest needs another tile
+            SvRecord g;
+            std::memset(&g, 0, sizeof(g));
+            g.kind = SVR_GROUP;
+            std::vector<int> reg(32, -1);
+            int r = 0;
+            for (int p = 0; p < nb; ++p)
+                if ((rset >> p) & 1) {
+                    g.a |= local[p] << (8 * r);
+                    g.b |= p << (8 * r);
+                    reg[p] = r++;
+                }
+            P.recs.push_back(g);
+            emit_group(S, run, reg, K, P.recs);
+            S.finish(run);
+        }
+        out.passes.push_back(std::move(P));
+    } while (!S.left.empty());
+    return out;
+}
+
+}  // namespace htn

@@ -70,6 +70,25 @@ def test_instance_outputs_match_oracle(sizes):
     assert np.array_equal(outs.cpu().numpy(), got.cpu().numpy())
 
 
+@pytest.mark.parametrize("sizes,n_ops", [((2, 7, 8, 9), 0), ((6, 8, 9, 10), 200), ((12, 13, 17), 120)])
+def test_schedules_match_oracle(sizes, n_ops):
+    """Sizes at the borders of the evaluator's kernels (one wave, one
+    workgroup, tiles in device memory) with no ops and with more records
+    than a workgroup stages at once; several observables on one evolution
+    (large states are shared) and one evolution on two preparations."""
+    import torch
+    rng = np.random.default_rng(n_ops + len(sizes))
+    insts = []
+    for n in sizes:
+        a = _random_instance(rng, n, min(2, n - 1), n_ops)
+        b = _random_instance(rng, n, n // 2, 1)
+        insts += [a, c.Instance(n, a.init, a.ops, b.observable, b.kept), c.Instance(n, b.init, a.ops, b.observable, b.kept)]
+    (got,) = qteval.Evaluator([_spec_of(insts)]).run()
+    torch.cuda.synchronize()
+    ref = np.concatenate([sv.instance_outputs(i) for i in insts])
+    assert np.abs(got.cpu().numpy() - ref).max() <= 1e-12
+
+
 def _workloads():
     ws = [c.cut_wires(s) for s in range(2)]
     ws += [c.cut_gates(s, k, gate=g) for s in (1, 2) for k in (1, 2) for g in ("cz", "rzz", "cx")]
