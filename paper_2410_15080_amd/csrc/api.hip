@@ -57,7 +57,6 @@ struct DeviceState {
     int device = -1;
     std::vector<void *> in;  // per tensor, compute input dtype
     std::vector<char> own;
-    void **d_inptrs = nullptr;
     int32_t *d_prog = nullptr;
     int2 *d_tab = nullptr;
     void *d_ws = nullptr;
@@ -88,15 +87,16 @@ static void run_sliced(htn::Net &n, void *out, hipStream_t st);
 
 // A network contracted on its own (htn_contract, fused) whose inputs total
 // at most this many elements materialises them inside its workgroup, which
-// saves a launch.  Batches materialise every network's inputs in one wide
-// launch instead: spread over thousands of waves it finishes sooner than
-// per-workgroup prologues.
-static constexpr int64_t kInKernelPrepMax = 65536;
+// saves a launch: 24 elements (the 10-qubit circuit with two wire cuts) take
+// 21.5 us with the evaluation against 24.0, but 3 652 elements (a 4x4 grid)
+// 40.3 against 28.7, where a launch of its own spreads them over the chip
+// (batches always use one).
+static constexpr int64_t kInKernelPrepMax = 256;
 
-static kern::FusedDesc fused_desc(const DeviceState &D, bool in_kernel_prep, bool lds_only) {
+static kern::FusedDesc fused_desc(const DeviceState &D, const Plan &P, bool in_kernel_prep, int32_t net) {
     const bool k = in_kernel_prep && D.fprep_in_kernel;
-    return kern::FusedDesc{D.d_prog, D.d_tab, (const void *const *)D.d_inptrs, D.d_ws, k ? D.d_fprep : nullptr,
-                           k ? (int32_t)D.fprep.size() : 0, lds_only ? 1 : 0};
+    return kern::FusedDesc{D.d_prog, D.d_ws, k ? D.d_fprep : nullptr, k ? (int32_t)D.fprep.size() : 0, P.program[0],
+                           net, 0};
 }
 
 struct htn_net : public Net {};
@@ -105,7 +105,7 @@ struct htn_batch {
     struct Group {
         int compute = 0, fm = 0, lds = 0, threads = 256;
         std::vector<int> idx;  // net indices, heaviest first
-        int32_t *d_order = nullptr;
+        size_t desc0 = 0;      // its networks' descriptors, in that order (d_desc)
         kern::FPrepEntry *d_fprep = nullptr;  // input materialisation of every net
         int n_fprep = 0, fprep_form = 0, fprep_max = 0;
     };
@@ -288,7 +288,6 @@ static void release_device(Net &n) {
     free_slices(*n.dev);
     release_inputs(n);
     DeviceState &D = *n.dev;
-    dfree(D.d_inptrs);
     dfree(D.d_prog);
     dfree(D.d_tab);
     dfree(D.d_ws);
@@ -342,9 +341,6 @@ static void upload_inputs(Net &n) {
         }
     }
     HIP_TRY(hipDeviceSynchronize());
-    dfree(D.d_inptrs);
-    D.d_inptrs = dalloc<void *>(n.n_t);
-    HIP_TRY(hipMemcpy(D.d_inptrs, D.in.data(), sizeof(void *) * n.n_t, hipMemcpyHostToDevice));
     n.data_dirty = false;
     D.plan_uploaded = -1;  // prep descriptors hold input pointers
     ++D.uploads;
@@ -524,7 +520,8 @@ static void upload_plan(Net &n) {
     int64_t in_elems = 0;
     for (const LoadPlan &lp : P.loads) in_elems += lp.size;
     D.fprep_in_kernel = !D.fprep.empty() && in_elems <= kInKernelPrepMax;
-    kern::FusedDesc fd = fused_desc(D, true, P.fused_lds_only);
+    for (const kern::FPrepEntry &e : D.fprep) D.fprep_in_kernel = D.fprep_in_kernel && e.n_words <= 64;
+    kern::FusedDesc fd = fused_desc(D, P, true, 0);
     dfree(D.d_fdesc);
     D.d_fdesc = dalloc<kern::FusedDesc>(1);
     HIP_TRY(hipMemcpy(D.d_fdesc, &fd, sizeof(fd), hipMemcpyHostToDevice));
@@ -572,7 +569,7 @@ static void run_fused_single(Net &n, void *out, hipStream_t st) {
     if (!n.dev->fprep_in_kernel)
         HIP_TRY(kern::launch_fprep(n.dev->d_fprep, (int)n.dev->fprep.size(), n.dev->fprep_form, n.dev->fprep_max,
                                    (int)n.compute, nullptr, st));
-    HIP_TRY(kern::launch_fused(n.dev->d_fdesc, nullptr, nullptr, nullptr, out, nullptr, 0, 1,
+    HIP_TRY(kern::launch_fused(n.dev->d_fdesc, nullptr, nullptr, out, nullptr, 0, 1,
                                (int)n.plan.fused_lds_bytes, (int)n.compute, final_mode(n), n.fused_threads, st));
 }
 
@@ -1058,7 +1055,6 @@ static void batch_free(htn_batch *b) {
     b->gexec = nullptr;
     b->graph = nullptr;
     for (auto &g : b->groups) {
-        dfree(g.d_order);
         dfree(g.d_fprep);
     }
     dfree(b->q.d_items);
@@ -1469,7 +1465,7 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
     htn_batch *b = new htn_batch;
     try {
         b->nets.assign(nets, nets + n);
-        std::vector<kern::FusedDesc> desc(n);
+        std::vector<kern::FusedDesc> desc;  // of the fused nets, group by group
         for (int i = 0; i < n; ++i)
             if (!nets[i]) throw Error{HTN_E_ARG, "nets[" + std::to_string(i) + "] is NULL"};
         // straggler threshold from the work of the fused-eligible nets and
@@ -1510,7 +1506,6 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
             ensure_device(net);
             b->versions.push_back(net.plan_version);
             b->uploads.push_back(net.dev->uploads);
-            desc[i] = fused_desc(*net.dev, false, net.plan.fused_lds_only);
             if (net.queue_mode == 1 || !use_fused_in_batch(net) || net.plan.mults > straggler) {
                 b->step_nets.push_back(i);
                 continue;
@@ -1534,11 +1529,11 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
         for (auto &g : b->groups) {
             std::stable_sort(g.idx.begin(), g.idx.end(),
                              [&](int x, int y) { return nets[x]->plan.mults > nets[y]->plan.mults; });
-            g.d_order = dalloc<int32_t>(g.idx.size());
-            HIP_TRY(hipMemcpy(g.d_order, g.idx.data(), g.idx.size() * 4, hipMemcpyHostToDevice));
+            g.desc0 = desc.size();
             std::vector<kern::FPrepEntry> fp;
             for (int i : g.idx) {
                 const DeviceState &D = *nets[i]->dev;
+                desc.push_back(fused_desc(D, nets[i]->plan, false, i));
                 fp.insert(fp.end(), D.fprep.begin(), D.fprep.end());
                 g.fprep_max = std::max(g.fprep_max, D.fprep_max);
                 g.fprep_form = std::max(g.fprep_form, D.fprep_form);
@@ -1549,8 +1544,10 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
                 HIP_TRY(hipMemcpy(g.d_fprep, fp.data(), fp.size() * sizeof(kern::FPrepEntry), hipMemcpyHostToDevice));
             }
         }
-        b->d_desc = dalloc<kern::FusedDesc>(n);
-        HIP_TRY(hipMemcpy(b->d_desc, desc.data(), n * sizeof(kern::FusedDesc), hipMemcpyHostToDevice));
+        if (!desc.empty()) {
+            b->d_desc = dalloc<kern::FusedDesc>(desc.size());
+            HIP_TRY(hipMemcpy(b->d_desc, desc.data(), desc.size() * sizeof(kern::FusedDesc), hipMemcpyHostToDevice));
+        }
         b->d_outs = dalloc<void *>(n);
         b->d_stamps = dalloc<int64_t>(2 * (size_t)n + 1);  // [2n]: start of the run
         if (!b->step_nets.empty()) {
@@ -1666,7 +1663,7 @@ static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool 
         HIP_TRY(hipStreamWaitEvent(b->q.stream, b->q.ev_fork, 0));
     }
     for (auto &g : b->groups)
-        HIP_TRY(kern::launch_fused(b->d_desc, g.d_order, b->d_outs, b->d_stamps, nullptr, b->d_phase, b->max_phases,
+        HIP_TRY(kern::launch_fused(b->d_desc + g.desc0, b->d_outs, b->d_stamps, nullptr, b->d_phase, b->max_phases,
                                    (int)g.idx.size(), g.lds, g.compute, g.fm, g.threads, st));
     if (events) HIP_TRY(hipEventRecord(next_event(b), st));
     // the queue goes after the fused launch: launched first, its resident

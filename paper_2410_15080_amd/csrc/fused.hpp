@@ -6,6 +6,11 @@
 // the last step writes the result.  One launch serves a batch of networks
 // (one workgroup each).  Each workgroup size is instantiated in its own
 // translation unit (fused_b*.hip).
+//
+// What bounds it: latency.  A network is 6-10 dependent phases of a few
+// hundred multiplications per thread, so what a phase costs besides its
+// arithmetic decides: finding and decoding the wave's step, the copies for
+// the next phase, the offsets of the results, the barrier.
 #pragma once
 
 #include <type_traits>
@@ -17,46 +22,98 @@ namespace kern {
 
 // ----------------------------------------------------------------- k_fused
 
-// One step inside the fused kernel.  A, B point into LDS; C into LDS or, for
-// the final step, global memory.
+// Program words of a step, word i in lane i (words 64.. in a second
+// register): one LDS read brings them all, and a wave-uniform read is then
+// one lane read.  Reading each word where it lies in LDS instead made
+// every field a round trip of 130 cycles, and the fields' use a chain of
+// them: 900-3200 cycles to find a wave's step, 4000-6000 for the offsets of
+// a 24 x 16 result.
+struct StepWords {
+    int32_t r, d;  // the step's fields; the digit descriptors of a tiled step
+    __device__ __forceinline__ StepWords(const int32_t *img, int n_words, int off, int lane) {
+        r = off + lane < n_words ? img[off + lane] : 0;
+        d = off + 15 + lane < n_words ? img[off + 15 + lane] : 0;
+    }
+    __device__ __forceinline__ int32_t operator()(int i) const { return __builtin_amdgcn_readlane(r, i); }
+    __device__ __forceinline__ int32_t digit(int i) const { return __builtin_amdgcn_readlane(d, i); }
+};
+
+// Pointers of known address spaces, so that operands and results in LDS are
+// read and written by LDS instructions (a pointer that may be either is
+// accessed through the slower flat path).
+template <typename T>
+using LdsPtr = __attribute__((address_space(3))) T *;
+template <typename T>
+using GlobalPtr = __attribute__((address_space(1))) T *;
+
+// Where a step's results go.
+template <typename T>
+struct Dest {
+    bool in_lds;
+    LdsPtr<T> l;
+    GlobalPtr<T> g;
+    __device__ __forceinline__ void put(int o, T v) const {
+        if (in_lds)  // wave-uniform
+            l[o] = v;
+        else
+            g[o] = v;
+    }
+};
+
+// The next NB terms of one output's sum from (sh, sl) on, products in pv[]
+// (0 past the end); (sh, sl) advances by NB strides.
+template <int NB, typename ACC, bool UNARY, typename P>
+__device__ __forceinline__ void next_terms(P a0, P b0, const int2 *tsh, const int2 *tsl, int &sh, int &sl, int dq,
+                                           int dr, int n_shi, int n_slo, ACC (&pv)[NB]) {
+    int hv[NB], lv[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        hv[u] = sh;
+        lv[u] = sl;
+        sh += dq;
+        sl += dr;
+        if (sl >= n_slo) {
+            sl -= n_slo;
+            ++sh;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const bool ok = hv[u] < n_shi;
+        const int2 h = tsh[ok ? hv[u] : 0], l = tsl[lv[u]];
+        ACC q = (ACC)a0[h.x + l.x];
+        if constexpr (!UNARY) q *= (ACC)b0[h.y + l.y];
+        pv[u] = ok ? q : ACC(0);
+    }
+}
+
 // Sum over the summed index space (n_shi x n_slo, two-level tables) of one
 // output, visiting s = start, start + stride, ... in (sh, sl) form with
-// stride = dq * n_slo + dr (dr < n_slo).  Plain sums keep four independent
-// partial sums, so four table reads and four operand reads are in flight
-// together; compensated sums stay sequential.
-template <typename T, typename ACC, bool COMP, bool UNARY>
-__device__ __forceinline__ void strided_sum(const T *a0, const T *b0, const int2 *tsh, const int2 *tsl, int sh, int sl,
-                                            int dq, int dr, int n_shi, int n_slo, ACC &s, ACC &c) {
+// stride = dq * n_slo + dr (dr < n_slo), `terms` of them at most per lane.
+// Long sums read 16 terms ahead of their additions (operands outside LDS
+// take 1000 cycles and more: a sum of 3456 terms by 16 lanes took 164 000
+// cycles with 4 in flight).  Plain sums keep four independent partial sums
+// (term t in t mod 4) whatever the number in flight; compensated ones are
+// added in order.
+template <typename ACC, bool COMP, bool UNARY, typename P>
+__device__ __forceinline__ void strided_sum(P a0, P b0, const int2 *tsh, const int2 *tsl, int sh, int sl, int dq,
+                                            int dr, int n_shi, int n_slo, int terms, ACC &s, ACC &c) {
     if constexpr (!COMP) {
         ACC s1 = 0, s2 = 0, s3 = 0;
-        while (sh < n_shi) {
-            int hv[4], lv[4];
-            hv[0] = sh;
-            lv[0] = sl;
+        for (; terms > 8; terms -= 16) {  // terms: the same for every lane
+            ACC pv[16];
+            next_terms<16, ACC, UNARY>(a0, b0, tsh, tsl, sh, sl, dq, dr, n_shi, n_slo, pv);
 #pragma unroll
-            for (int u = 1; u < 4; ++u) {
-                hv[u] = hv[u - 1] + dq;
-                lv[u] = lv[u - 1] + dr;
-                if (lv[u] >= n_slo) {
-                    lv[u] -= n_slo;
-                    ++hv[u];
-                }
+            for (int u = 0; u < 16; u += 4) {
+                s += pv[u];
+                s1 += pv[u + 1];
+                s2 += pv[u + 2];
+                s3 += pv[u + 3];
             }
-            sh = hv[3] + dq;
-            sl = lv[3] + dr;
-            if (sl >= n_slo) {
-                sl -= n_slo;
-                ++sh;
-            }
+        }
+        for (; terms > 0; terms -= 4) {
             ACC pv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool ok = hv[u] < n_shi;
-                const int2 h = tsh[ok ? hv[u] : 0], l = tsl[lv[u]];
-                ACC q = (ACC)a0[h.x + l.x];
-                if constexpr (!UNARY) q *= (ACC)b0[h.y + l.y];
-                pv[u] = ok ? q : ACC(0);
-            }
+            next_terms<4, ACC, UNARY>(a0, b0, tsh, tsl, sh, sl, dq, dr, n_shi, n_slo, pv);
             s += pv[0];
             s1 += pv[1];
             s2 += pv[2];
@@ -65,32 +122,40 @@ __device__ __forceinline__ void strided_sum(const T *a0, const T *b0, const int2
         s += (s1 + s2) + s3;
     } else {
         while (sh < n_shi) {
-            const int2 h = tsh[sh], l = tsl[sl];
-            ACC q = (ACC)a0[h.x + l.x];
-            if constexpr (!UNARY) q *= (ACC)b0[h.y + l.y];
-            accum<COMP>(s, c, q);
-            sh += dq;
-            sl += dr;
-            if (sl >= n_slo) {
-                sl -= n_slo;
-                ++sh;
+            ACC pv[8];
+            const int h0 = sh, l0 = sl;
+            next_terms<8, ACC, UNARY>(a0, b0, tsh, tsl, sh, sl, dq, dr, n_shi, n_slo, pv);
+            int h = h0, l = l0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (h < n_shi) accum<COMP>(s, c, pv[u]);
+                h += dq;
+                l += dr;
+                if (l >= n_slo) {
+                    l -= n_slo;
+                    ++h;
+                }
             }
         }
     }
 }
 
-template <int BLK, typename T, typename ACC, bool COMP, bool UNARY, typename TOUT>
+template <int BLK, typename ACC, bool COMP, bool UNARY, typename TOUT, typename P>
 // Threads tid = 0..nthr-1 of the step's waves run it; R == nthr (the whole
 // workgroup per output) is planned only when the step owns the workgroup
 // (nthr == BLK), since it synchronises every wave.
-__device__ __forceinline__ void fstep(const T *A, const T *B, TOUT *C, const int2 *__restrict__ tab,
-                                      const int32_t *g, int R, ACC *scratch, const int tid, const int nthr) {
-    const int n_ohi = g[0], n_olo = g[1], n_shi = g[2], n_slo = g[3];
-    const int2 *toh = tab + g[4];
-    const int2 *tol = tab + g[5];
-    const int2 *tsh = tab + g[6];
-    const int2 *tsl = tab + g[7];
+__device__ __forceinline__ void fstep(P A, P B, const Dest<TOUT> &C, const int2 *__restrict__ tab,
+                                      const StepWords &p, ACC *scratch, const int tid, const int nthr) {
+    const int n_ohi = p(4), n_olo = p(5), n_shi = p(6), n_slo = p(7);
+    const int2 *toh = tab + p(8);
+    const int2 *tol = tab + p(9);
+    const int2 *tsh = tab + p(10);
+    const int2 *tsl = tab + p(11);
+    const int R = p(12);
     const int n_out = n_ohi * n_olo;
+    int log2R = 0;
+    while ((1 << log2R) < R) ++log2R;
+    const int terms = (n_shi * n_slo + R - 1) >> log2R;  // of one lane, at most
     if (R == BLK && nthr == BLK) {
         // whole workgroup per output (tiny outputs, long sums)
         const int dq = BLK / n_slo, dr = BLK - dq * n_slo;
@@ -98,11 +163,11 @@ __device__ __forceinline__ void fstep(const T *A, const T *B, TOUT *C, const int
         for (int o = 0; o < n_out; ++o) {
             const int oh = o / n_olo, ol = o - oh * n_olo;  // wave-uniform
             const int2 x = toh[oh], y = tol[ol];
-            const T *a0 = A + (x.x + y.x);
-            const T *b0 = B;
+            const P a0 = A + (x.x + y.x);
+            P b0 = B;
             if constexpr (!UNARY) b0 = B + (x.y + y.y);
             ACC s = 0, c = 0;
-            strided_sum<T, ACC, COMP, UNARY>(a0, b0, tsh, tsl, sh0, sl0, dq, dr, n_shi, n_slo, s, c);
+            strided_sum<ACC, COMP, UNARY>(a0, b0, tsh, tsl, sh0, sl0, dq, dr, n_shi, n_slo, terms, s, c);
             lane_reduce<COMP>(s, c, 64);
             if ((tid & 63) == 0) {
                 scratch[2 * (tid >> 6)] = s;
@@ -112,14 +177,12 @@ __device__ __forceinline__ void fstep(const T *A, const T *B, TOUT *C, const int
             if (tid == 0) {
                 ACC ts = scratch[0], tc = scratch[1];
                 for (int w = 1; w < BLK / 64; ++w) combine<COMP>(ts, tc, scratch[2 * w], scratch[2 * w + 1]);
-                C[o] = st_cvt<TOUT>(COMP ? ts + tc : ts);
+                C.put(o, st_cvt<TOUT>(COMP ? ts + tc : ts));
             }
             __syncthreads();
         }
         return;
     }
-    int log2R = 0;
-    while ((1 << log2R) < R) ++log2R;
     const int groups = nthr >> log2R;
     const int gi = tid >> log2R, sub = tid & (R - 1);
     const int dq = R / n_slo, dr = R - dq * n_slo;
@@ -134,32 +197,48 @@ __device__ __forceinline__ void fstep(const T *A, const T *B, TOUT *C, const int
         ACC s = 0, c = 0;
         if (active) {
             const int2 x = toh[oh], y = tol[ol];
-            const T *a0 = A + (x.x + y.x);
-            const T *b0 = B;
+            const P a0 = A + (x.x + y.x);
+            P b0 = B;
             if constexpr (!UNARY) b0 = B + (x.y + y.y);
             if (R == 1) {
                 ACC s1 = 0, s2 = 0, s3 = 0;
                 for (int sh = 0; sh < n_shi; ++sh) {
                     const int2 h = tsh[sh];
-                    const T *a1 = a0 + h.x;
-                    const T *b1 = b0;
+                    const P a1 = a0 + h.x;
+                    P b1 = b0;
                     if constexpr (!UNARY) b1 = b0 + h.y;
                     int sl = 0;
                     if constexpr (!COMP) {
-                        // four independent partial sums (ILP)
-                        for (; sl + 4 <= n_slo; sl += 4) {
-                            const int2 l0 = tsl[sl], l1 = tsl[sl + 1], l2 = tsl[sl + 2], l3 = tsl[sl + 3];
-                            ACC p0 = (ACC)a1[l0.x], p1 = (ACC)a1[l1.x], p2 = (ACC)a1[l2.x], p3 = (ACC)a1[l3.x];
-                            if constexpr (!UNARY) {
-                                p0 *= (ACC)b1[l0.y];
-                                p1 *= (ACC)b1[l1.y];
-                                p2 *= (ACC)b1[l2.y];
-                                p3 *= (ACC)b1[l3.y];
+                        // four independent partial sums (ILP), up to 16
+                        // terms in flight
+                        for (; sl + 16 <= n_slo; sl += 16) {
+                            ACC q[16];
+#pragma unroll
+                            for (int u = 0; u < 16; ++u) {
+                                const int2 l = tsl[sl + u];
+                                q[u] = (ACC)a1[l.x];
+                                if constexpr (!UNARY) q[u] *= (ACC)b1[l.y];
                             }
-                            s += p0;
-                            s1 += p1;
-                            s2 += p2;
-                            s3 += p3;
+#pragma unroll
+                            for (int u = 0; u < 16; u += 4) {
+                                s += q[u];
+                                s1 += q[u + 1];
+                                s2 += q[u + 2];
+                                s3 += q[u + 3];
+                            }
+                        }
+                        for (; sl + 4 <= n_slo; sl += 4) {
+                            ACC q[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const int2 l = tsl[sl + u];
+                                q[u] = (ACC)a1[l.x];
+                                if constexpr (!UNARY) q[u] *= (ACC)b1[l.y];
+                            }
+                            s += q[0];
+                            s1 += q[1];
+                            s2 += q[2];
+                            s3 += q[3];
                         }
                     }
                     for (; sl < n_slo; ++sl) {
@@ -171,11 +250,11 @@ __device__ __forceinline__ void fstep(const T *A, const T *B, TOUT *C, const int
                 }
                 s += (s1 + s2) + s3;
             } else {
-                strided_sum<T, ACC, COMP, UNARY>(a0, b0, tsh, tsl, sh0, sl0, dq, dr, n_shi, n_slo, s, c);
+                strided_sum<ACC, COMP, UNARY>(a0, b0, tsh, tsl, sh0, sl0, dq, dr, n_shi, n_slo, terms, s, c);
             }
         }
         lane_reduce<COMP>(s, c, R);
-        if (active && sub == 0) C[o] = st_cvt<TOUT>(COMP ? s + c : s);
+        if (active && sub == 0) C.put(o, st_cvt<TOUT>(COMP ? s + c : s));
         oh += oq;
         ol += orr;
         if (ol >= n_olo) {
@@ -185,32 +264,63 @@ __device__ __forceinline__ void fstep(const T *A, const T *B, TOUT *C, const int
     }
 }
 
+// C offsets of indices x[] of a label group from its digit descriptors (per
+// label, last fastest: extent, magic (2 words), stride; from word w0 on).
+// The descriptors are wave-uniform, so a digit costs a lane read per word
+// and a few vector operations per index, all indices side by side.
+// narrow: x, extents <= 4096 and C below 2^24 elements: 24-bit products (full
+// rate; 32-bit ones run at a quarter of it).  The magic rounded to 24 bits
+// exceeds 2^24 / d by less than 1.0001, exact while x d < 2^24 / 1.0001.
+template <int NV>
+__device__ __forceinline__ void digit_offsets(const StepWords &p, int w0, int nl, bool narrow, uint32_t (&x)[NV],
+                                              int (&off)[NV]) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) off[v] = 0;
+    if (nl == 0) return;
+    if (narrow) {
+        for (int w = w0 + 4 * (nl - 1); w > w0; w -= 4) {
+            const uint32_t ext = (uint32_t)p.digit(w);
+            const uint32_t m24 = (((uint32_t)p.digit(w + 2) << 16) | ((uint32_t)p.digit(w + 1) >> 16)) + 1u;
+            const uint32_t stride = (uint32_t)p.digit(w + 3);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const uint32_t xs = (x[v] << 8) & 0xffffffu;
+                const uint32_t quo = (uint32_t)(((uint64_t)xs * (m24 & 0xffffffu)) >> 32);
+                off[v] += (int)__umul24(x[v] - __umul24(quo, ext), stride);
+                x[v] = quo;
+            }
+        }
+        const uint32_t stride = (uint32_t)p.digit(w0 + 3);  // the slowest digit is what is left
+#pragma unroll
+        for (int v = 0; v < NV; ++v) off[v] += (int)__umul24(x[v], stride);
+    } else {
+        for (int w = w0 + 4 * (nl - 1); w > w0; w -= 4) {
+            const uint32_t ext = (uint32_t)p.digit(w);
+            const uint64_t magic = ((uint64_t)(uint32_t)p.digit(w + 2) << 32) | (uint32_t)p.digit(w + 1);
+            const int stride = p.digit(w + 3);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const uint32_t quo = (uint32_t)(((uint64_t)x[v] * magic) >> 40);
+                off[v] += (int)(x[v] - quo * ext) * stride;
+                x[v] = quo;
+            }
+        }
+        const int stride = p.digit(w0 + 3);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) off[v] += (int)x[v] * stride;
+    }
+}
+__device__ __forceinline__ bool narrow_digits(int M, int N) { return M <= 4080 && N <= 4080 && M * N < (1 << 24); }
+
 // Register-tiled step: C[tcm[m] + tcn[n]] = sum_k A[k*M + m] * B[k*N + n].
 // Thread (tx, ty) of a GX x (kBlk/GX) grid owns outputs m = m0 + tx + GX*i,
 // n = n0 + ty + GY*j (i < TM, j < TN).  Across a wave, A reads are
 // consecutive or broadcast, B reads broadcast or consecutive.
-// Offset of index x of a label group from its digit descriptors (per label,
-// last fastest: extent, magic (2 words), stride).
-__device__ __forceinline__ int digit_offset(uint32_t x, const int32_t *dg, int nl) {
-    int off = 0;
-#pragma unroll
-    for (int k = 7; k >= 0; --k) {
-        if (k < nl) {
-            const int32_t *q = dg + 4 * k;
-            const uint64_t magic = ((uint64_t)(uint32_t)q[2] << 32) | (uint32_t)q[1];
-            const uint32_t quo = (uint32_t)(((uint64_t)x * magic) >> 40);
-            off += (int)(x - quo * (uint32_t)q[0]) * q[3];
-            x = quo;
-        }
-    }
-    return off;
-}
-
-template <int BLK, typename T, typename ACC, int TM, int TN, typename TOUT>
-__device__ __forceinline__ void tstep(const T *A, const T *B, TOUT *C, const int32_t *dgm, int nm, const int32_t *dgn,
-                                      int nn_l, int M, int N, int K, int GX, const int tid, const int nthr) {
-    int lgx = 0;
-    while ((1 << lgx) < GX) ++lgx;
+template <typename T, typename ACC, int TM, int TN, typename TOUT, typename P>
+__device__ __forceinline__ void tstep(P A, P B, const Dest<TOUT> &C, const StepWords &p, const int tid,
+                                      const int nthr) {
+    const int M = p(4), N = p(5), K = p(6), GX = p(9), nm = p(11), nn_l = p(12);
+    const int lgx = 31 - __clz(GX);
     const int GY = nthr >> lgx;
     const int tx = tid & (GX - 1), ty = tid >> lgx;
     const int SM = GX * TM, SN = GY * TN;
@@ -238,8 +348,7 @@ __device__ __forceinline__ void tstep(const T *A, const T *B, TOUT *C, const int
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[u][i][j] = 0;
-            const T *a = A;
-            const T *b = B;
+            P a = A, b = B;
             int k = 0;
             for (; k + U <= K; k += U) {
                 T av[U][TM], bv[U][TN];
@@ -273,21 +382,21 @@ __device__ __forceinline__ void tstep(const T *A, const T *B, TOUT *C, const int
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) acc[0][i][j] += acc[u][i][j];
-            int cn[TN];
+            uint32_t xn[TN], xm[TM];
+            int cn[TN], cm[TM];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) cn[j] = digit_offset((uint32_t)nj[j], dgn, nn_l);
+            for (int j = 0; j < TN; ++j) xn[j] = (uint32_t)nj[j];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int m = m0 + tx + GX * i;
-                if (m < M) {
-                    const int cm = digit_offset((uint32_t)m, dgm, nm);
+            for (int i = 0; i < TM; ++i) xm[i] = (uint32_t)mi[i];
+            digit_offsets<TN>(p, 4 * nm, nn_l, narrow_digits(M, N), xn, cn);
+            digit_offsets<TM>(p, 0, nm, narrow_digits(M, N), xm, cm);
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int nn = n0 + ty + GY * j;
-                        if (nn < N) C[cm + cn[j]] = st_cvt<TOUT>(acc[0][i][j]);
-                    }
+            for (int i = 0; i < TM; ++i)
+                if (m0 + tx + GX * i < M) {
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        if (n0 + ty + GY * j < N) C.put(cm[i] + cn[j], st_cvt<TOUT>(acc[0][i][j]));
                 }
-            }
         }
     }
 }
@@ -317,336 +426,328 @@ struct FMfma<float> {
     __device__ __forceinline__ static int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
-template <int BLK, typename T, typename TOUT>
-__device__ __forceinline__ void mstep(const T *A, const T *B, TOUT *C, const int32_t *dgm, int nm, const int32_t *dgn,
-                                      int nn_l, int M, int N, int K, const int tid, const int nthr) {
+//
+// BM x BN blocks of a wave share their operands' reads, and 16 values of K
+// are read while the previous 16 are multiplied: operands outside LDS
+// arrive at the rate of the L1 cache (64 bytes a clock, which single blocks
+// use up) instead of one round trip per 16.  A 144 x 144 x 216 step with both
+// operands outside took 262 000 cycles with single blocks and no read ahead.
+template <int BM, int BN, typename T, typename TOUT, typename P>
+__device__ __forceinline__ void mstep(P A, P B, const Dest<TOUT> &C, const StepWords &p, const int tid, const int nthr) {
     typedef FMfma<T> Op;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int M = p(4), N = p(5), K = p(6), nm = p(11), nn_l = p(12);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lk = lane >> 4;
-    const int nbm = (M + 15) >> 4, nbn = (N + 15) >> 4;
-    for (int blk = wave; blk < nbm * nbn; blk += nthr >> 6) {
-        const int bm = blk / nbn, bn = blk - bm * nbn;
-        const int m = bm * 16 + li, n = bn * 16 + li;
-        const bool mok = m < M, nok = n < N;
-        const T *a = A + (mok ? m : 0);
-        const T *b = B + (nok ? n : 0);
-        typename Op::acc acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
-        int k0 = 0;
-        for (; k0 + 8 <= K; k0 += 8) {
-            const int k = k0 + lk;
-            T a0 = a[k * M], b0 = b[k * N], a1 = a[(k + 4) * M], b1 = b[(k + 4) * N];
-            a0 = mok ? a0 : T(0);
-            a1 = mok ? a1 : T(0);
-            b0 = nok ? b0 : T(0);
-            b1 = nok ? b1 : T(0);
-            acc0 = Op::mma(a0, b0, acc0);
-            acc1 = Op::mma(a1, b1, acc1);
-        }
-        for (; k0 < K; k0 += 4) {
-            const int k = k0 + lk;
-            const bool kok = k < K;
-            T a0 = a[(kok ? k : 0) * M], b0 = b[(kok ? k : 0) * N];
-            a0 = (mok && kok) ? a0 : T(0);
-            b0 = (nok && kok) ? b0 : T(0);
-            acc0 = Op::mma(a0, b0, acc0);
-        }
-        if (nok) {
-            const int cn = digit_offset((uint32_t)n, dgn, nn_l);
+    const int nbm = (M + 16 * BM - 1) / (16 * BM), nbn = (N + 16 * BN - 1) / (16 * BN);
+    const int nw = nthr >> 6;
+    const bool narrow = narrow_digits(M, N);
+    int bm = 0, bn = wave;  // block bm * nbn + bn, advanced without divisions
+    while (bn >= nbn) {
+        bn -= nbn;
+        ++bm;
+    }
+    while (bm < nbm) {
+        int am[BM], bx[BN];  // operand columns (0 outside the matrix, whose products are dropped below)
+        bool mok[BM], nok[BN];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int mm = bm * 16 + Op::row(lane, r);
-                if (mm < M) C[digit_offset((uint32_t)mm, dgm, nm) + cn] = st_cvt<TOUT>(acc0[r] + acc1[r]);
+        for (int i = 0; i < BM; ++i) {
+            const int m = (bm * BM + i) * 16 + li;
+            mok[i] = m < M;
+            am[i] = mok[i] ? m : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < BN; ++j) {
+            const int n = (bn * BN + j) * 16 + li;
+            nok[j] = n < N;
+            bx[j] = nok[j] ? n : 0;
+        }
+        typename Op::acc acc0[BM][BN], acc1[BM][BN];
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j) acc0[i][j] = acc1[i][j] = typename Op::acc{0, 0, 0, 0};
+        auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok, typename Op::acc (&acc)[BM][BN]) {
+            T a[BM], b[BN];
+#pragma unroll
+            for (int i = 0; i < BM; ++i) a[i] = mok[i] && ok ? av[i] : T(0);
+#pragma unroll
+            for (int j = 0; j < BN; ++j) b[j] = nok[j] && ok ? bv[j] : T(0);
+#pragma unroll
+            for (int i = 0; i < BM; ++i)
+#pragma unroll
+                for (int j = 0; j < BN; ++j) acc[i][j] = Op::mma(a[i], b[j], acc[i][j]);
+        };
+        T av[4][BM], bv[4][BN];
+        int ao = lk * M, bo = lk * N;
+        auto load = [&](int u, int so, int to) {
+#pragma unroll
+            for (int i = 0; i < BM; ++i) av[u][i] = A[so + am[i]];
+#pragma unroll
+            for (int j = 0; j < BN; ++j) bv[u][j] = B[to + bx[j]];
+        };
+        int k = K;
+        if (k >= 16) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
+            for (;;) {
+                T ac[4][BM], bc[4][BN];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                    for (int i = 0; i < BM; ++i) ac[u][i] = av[u][i];
+#pragma unroll
+                    for (int j = 0; j < BN; ++j) bc[u][j] = bv[u][j];
+                }
+                k -= 16;
+                ao += 16 * M;
+                bo += 16 * N;
+                if (k >= 16) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 4; u += 2) {
+                    mma_all(ac[u], bc[u], true, acc0);
+                    mma_all(ac[u + 1], bc[u + 1], true, acc1);
+                }
+                if (k < 16) break;
             }
+        }
+        // the last k < 16: a pair of slices, then up to two into acc0
+        const bool pair = k >= 8;
+        const int rest = k & 7;
+        if (pair) {
+            load(0, ao, bo);
+            load(1, ao + 4 * M, bo + 4 * N);
+            ao += 8 * M;
+            bo += 8 * N;
+        }
+        const bool ok0 = lk < rest, ok1 = lk + 4 < rest;
+        if (rest > 0) load(2, ok0 ? ao : 0, ok0 ? bo : 0);
+        if (rest > 4) load(3, ok1 ? ao + 4 * M : 0, ok1 ? bo + 4 * N : 0);
+        if (pair) {
+            mma_all(av[0], bv[0], true, acc0);
+            mma_all(av[1], bv[1], true, acc1);
+        }
+        if (rest > 0) mma_all(av[2], bv[2], ok0, acc0);
+        if (rest > 4) mma_all(av[3], bv[3], ok1, acc0);
+        uint32_t xn[BN];
+        int cn[BN];
+#pragma unroll
+        for (int j = 0; j < BN; ++j) xn[j] = (uint32_t)((bn * BN + j) * 16 + li);
+        digit_offsets<BN>(p, 4 * nm, nn_l, narrow, xn, cn);
+#pragma unroll
+        for (int i = 0; i < BM; ++i) {
+            const int m0 = (bm * BM + i) * 16;
+            uint32_t xm[4];
+            int cm[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) xm[r] = (uint32_t)(m0 + Op::row(lane, r));
+            digit_offsets<4>(p, 0, nm, narrow, xm, cm);
+            if (C.in_lds) {
+#pragma unroll
+                for (int j = 0; j < BN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (nok[j] && m0 + Op::row(lane, r) < M)
+                            C.l[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < BN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (nok[j] && m0 + Op::row(lane, r) < M)
+                            C.g[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
+            }
+        }
+        bn += nw;
+        while (bn >= nbn) {
+            bn -= nbn;
+            ++bm;
         }
     }
 }
 
-template <int BLK, typename T, typename ACC, typename TOUT>
-__device__ __forceinline__ void tstep_sel(const T *A, const T *B, TOUT *C, const int32_t *tcm, int nm,
-                                          const int32_t *tcn, int nn_l, int M, int N, int K, int TM, int TN, int GX,
+template <typename T, typename ACC, typename TOUT, typename P>
+__device__ __forceinline__ void tstep_sel(P A, P B, const Dest<TOUT> &C, const StepWords &p,
                                           const int tid, const int nthr) {
+    const int TM = p(7), TN = p(8);
     if constexpr (std::is_same<T, ACC>::value) {
         if (TM == 0) {  // matrix-core mode
-            mstep<BLK, T, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, tid, nthr);
+            // four blocks a wave where every wave has that many
+            if (((p(4) + 31) >> 5) * ((p(5) + 31) >> 5) >= (nthr >> 6))
+                mstep<2, 2, T>(A, B, C, p, tid, nthr);
+            else
+                mstep<1, 1, T>(A, B, C, p, tid, nthr);
             return;
         }
     }
     switch (TM * 8 + TN) {
-        case 9: tstep<BLK, T, ACC, 1, 1, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 10: tstep<BLK, T, ACC, 1, 2, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 12: tstep<BLK, T, ACC, 1, 4, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 17: tstep<BLK, T, ACC, 2, 1, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 18: tstep<BLK, T, ACC, 2, 2, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 20: tstep<BLK, T, ACC, 2, 4, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 33: tstep<BLK, T, ACC, 4, 1, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        case 34: tstep<BLK, T, ACC, 4, 2, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
-        default: tstep<BLK, T, ACC, 4, 4, TOUT>(A, B, C, tcm, nm, tcn, nn_l, M, N, K, GX, tid, nthr); break;
+        case 9: tstep<T, ACC, 1, 1>(A, B, C, p, tid, nthr); break;
+        case 10: tstep<T, ACC, 1, 2>(A, B, C, p, tid, nthr); break;
+        case 12: tstep<T, ACC, 1, 4>(A, B, C, p, tid, nthr); break;
+        case 17: tstep<T, ACC, 2, 1>(A, B, C, p, tid, nthr); break;
+        case 18: tstep<T, ACC, 2, 2>(A, B, C, p, tid, nthr); break;
+        case 20: tstep<T, ACC, 2, 4>(A, B, C, p, tid, nthr); break;
+        case 33: tstep<T, ACC, 4, 1>(A, B, C, p, tid, nthr); break;
+        case 34: tstep<T, ACC, 4, 2>(A, B, C, p, tid, nthr); break;
+        default: tstep<T, ACC, 4, 4>(A, B, C, p, tid, nthr); break;
     }
 }
 
-// OP_TSTEP: [a, b, c, M, N, K, TM, TN, GX, final, nm, nn, w0, nw, digits of M, digits of N]
-// (TM = 0: matrix-core mode, planned only where the accumulator is the
-// compute type)
-template <int BLK, typename T, int FM, bool PURE>
-__device__ __forceinline__ void tstep_dispatch(const int32_t *p, T *sm, T *scr, void *out, const int tid,
-                                               const int nthr) {
-    const int la = p[1], lb = p[2], lc = p[3];
-    const int M = p[4], N = p[5], K = p[6];
-    const int TM = p[7], TN = p[8], GX = p[9];
-    const bool fin = p[10] != 0;
-    const int nm = p[11], nn_l = p[12];
-    const int32_t *tcm = p + 15;
-    const int32_t *tcn = p + 15 + 4 * nm;
+// One step on its waves (threads tid of nthr).
+//   OP_TSTEP: [a, b, c, M, N, K, TM, TN, GX, final, nm, nn, w0, nw, digits of M, digits of N]
+//             (TM = 0: matrix-core mode, planned only where the accumulator is
+//             the compute type)
+//   OP_STEP:  [a, b, c, n_ohi, n_olo, n_shi, n_slo, t_ohi, t_olo, t_shi, t_slo, R, final, slot, w0, nw]
+// Operands in LDS take a body of their own (LDS reads, not flat ones).
+template <int BLK, typename T, int FM>
+__device__ __forceinline__ void run_step(const StepWords &p, T *sm, T *scr, void *out, const int32_t *slots,
+                                         int slot_words, unsigned char *red) {
     typedef typename std::conditional<FM == FM_INTER, T, double>::type TO;
-    if (PURE || (la >= 0 && lb >= 0 && (fin || lc >= 0))) {
-        if (!fin)
-            tstep_sel<BLK, T, T, T>(sm + la, sm + lb, sm + lc, tcm, nm, tcn, nn_l, M, N, K, TM, TN, GX, tid, nthr);
-        else
-            tstep_sel<BLK, T, TO, TO>(sm + la, sm + lb, (TO *)out, tcm, nm, tcn, nn_l, M, N, K, TM, TN, GX, tid,
-                                      nthr);
-    } else if constexpr (!PURE) {
-        const T *A = la >= 0 ? sm + la : scr + (-la - 2);
-        const T *B = lb >= 0 ? sm + lb : scr + (-lb - 2);
-        if (!fin)
-            tstep_sel<BLK, T, T, T>(A, B, lc >= 0 ? sm + lc : scr + (-lc - 2), tcm, nm, tcn, nn_l, M, N, K, TM, TN,
-                                    GX, tid, nthr);
-        else
-            tstep_sel<BLK, T, TO, TO>(A, B, (TO *)out, tcm, nm, tcn, nn_l, M, N, K, TM, TN, GX, tid, nthr);
-    }
-}
-
-// Contiguous 16-byte-chunk copies of one phase.  The copies that follow a
-// step are issued into registers before the step's arithmetic and written
-// to LDS after it, so their global latency overlaps the computation.
-constexpr int kPrefetch = 4;  // staged chunks per thread
-// Global-memory view of a copy source: the image and the workspace both
-// live in device memory, so the loads are plain global loads (no flat
-// address-space dispatch) and stay independent of LDS traffic.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) const u32x4 g_uint4;
-
-struct CopyOp {
-    const g_uint4 *src;
-    int dst;  // 16-byte chunk index in LDS
-    int n;
-};
-
-__device__ __forceinline__ CopyOp decode_copy(const int32_t *p, const int32_t *image, const unsigned char *ws) {
-    // [kind, src chunk, chunks, dst chunk]; kind 0: image words, 1: workspace
-    CopyOp c;
-    const u32x4 *s = p[1] == 0 ? (const u32x4 *)(image) + p[2] : (const u32x4 *)ws + p[2];
-    c.src = (const g_uint4 *)s;
-    c.dst = p[4];
-    c.n = p[3];
-    return c;
-}
-
-// Copy n 16-byte chunks from global memory to LDS, four independent loads
-// in flight per thread.
-template <int BLK>
-__device__ __forceinline__ void copy_chunks(const g_uint4 *src, u32x4 *dst, int n) {
-    for (int c0 = threadIdx.x; c0 < n; c0 += 4 * BLK) {
-        u32x4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (c0 + u * BLK < n) v[u] = src[c0 + u * BLK];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (c0 + u * BLK < n) dst[c0 + u * BLK] = v[u];
-    }
-}
-
-// Copies the chunks [from, ...) of a phase's copy ops [ops, ops_end) (their
-// chunks numbered consecutively in op order) with kFlatLoads independent
-// loads in flight per thread: the phase then waits about one memory
-// latency for all of them, not one per op.
-constexpr int kFlatLoads = 8;
-template <int BLK>
-__device__ __forceinline__ void copy_ops_flat(const int32_t *ops, const int32_t *ops_end, int from,
-                                              const int32_t *image, const unsigned char *ws, u32x4 *lds4) {
-    if (ops == ops_end) return;
-    const int32_t *r = ops;
-    CopyOp cur = decode_copy(r, image, ws);
-    int cur_start = 0;
-    for (int base = from;; base += kFlatLoads * BLK) {
-        u32x4 v[kFlatLoads];
-        int dst[kFlatLoads];
-#pragma unroll
-        for (int u = 0; u < kFlatLoads; ++u) {
-            const int c = base + (int)threadIdx.x + u * BLK;
-            while (r != ops_end && c >= cur_start + cur.n) {  // this thread's chunks only grow
-                cur_start += cur.n;
-                r += 5;
-                if (r != ops_end) cur = decode_copy(r, image, ws);
-            }
-            dst[u] = -1;
-            if (r != ops_end) {
-                v[u] = cur.src[c - cur_start];
-                dst[u] = cur.dst + (c - cur_start);
-            }
+    constexpr bool CMP = (FM == FM_COMP);
+    const bool tiled = p(0) == OP_TSTEP;
+    const int la = p(1), lb = p(2), lc = p(3);
+    const int w0 = tiled ? p(13) : p(15), nw = tiled ? p(14) : p(16);
+    const bool fin = (tiled ? p(10) : p(13)) != 0;
+    const int tid = threadIdx.x - 64 * w0, nthr = 64 * nw;
+    const bool unary = !tiled && lb == -1;
+    const bool in_lds = la >= 0 && (unary || lb >= 0);
+    const int2 *tab = reinterpret_cast<const int2 *>(slots + (tiled ? 0 : p(14) * slot_words));
+    Dest<T> C;
+    C.in_lds = !fin && lc >= 0;
+    C.l = (LdsPtr<T>)(sm + (C.in_lds ? lc : 0));
+    C.g = (GlobalPtr<T>)(fin ? (T *)out : scr + (lc < 0 ? -lc - 2 : 0));
+    auto go = [&](auto A, auto B) {
+        if (FM == FM_INTER || !fin) {
+            if (tiled)
+                tstep_sel<T, T>(A, B, C, p, tid, nthr);
+            else if (unary)
+                fstep<BLK, T, false, true>(A, B, C, tab, p, (T *)red, tid, nthr);
+            else
+                fstep<BLK, T, false, false>(A, B, C, tab, p, (T *)red, tid, nthr);
+        } else {
+            const Dest<TO> O = {false, nullptr, (GlobalPtr<TO>)out};
+            if (tiled)
+                tstep_sel<T, TO>(A, B, O, p, tid, nthr);
+            else if (unary)
+                fstep<BLK, TO, CMP, true>(A, B, O, tab, p, (TO *)red, tid, nthr);
+            else
+                fstep<BLK, TO, CMP, false>(A, B, O, tab, p, (TO *)red, tid, nthr);
         }
-#pragma unroll
-        for (int u = 0; u < kFlatLoads; ++u)
-            if (dst[u] >= 0) lds4[dst[u]] = v[u];
-        if (r == ops_end) break;
+    };
+    if (in_lds) {
+        go((LdsPtr<const T>)(sm + la), (LdsPtr<const T>)(sm + (unary ? 0 : lb)));
+    } else {
+        const T *A = la >= 0 ? sm + la : scr + (-la - 2);
+        const T *B = unary ? A : (lb >= 0 ? sm + lb : scr + (-lb - 2));
+        go(A, B);
     }
 }
 
-// The fused kernel.  A workgroup copies its network's program into LDS and
-// interprets it: COPY moves tables or materialised inputs into LDS,
-// STEP / TSTEP contract two values, SYNC ends a phase.
-// The interpreter for one network.  PURE: every operand and result lives
-// in LDS (no workspace-operand paths, so a smaller body with less register
-// pressure).
-template <int BLK, typename T, typename TIN, int FM, bool PURE>
-__device__ __forceinline__ void fused_body(const FusedDesc &d, const int net, void *const *__restrict__ outs,
-                                                     int64_t *__restrict__ stamps, void *out1,
-                                                     int64_t *__restrict__ phase_ticks, int max_phases, int64_t t0) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    int phase = 0;
-    int32_t *img = reinterpret_cast<int32_t *>(smem);
-    // program words (a multiple of four) as 16-byte chunks
-    copy_chunks<BLK>((const g_uint4 *)d.prog, (u32x4 *)smem, d.prog[0] / 4);
-    if (d.n_fprep > 0) {
-        // materialise the network's inputs into its workspace, one wave per
-        // entry, then make the writes visible to the workgroup's reads
-        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        for (int j = wave; j < d.n_fprep; j += BLK / 64) fprep_entry<T, TIN>(d.fprep[j], lane);
-        __threadfence();
+// The copies of one phase: n ops [kind (0: image tables, 1: workspace), src
+// chunk, chunks, dst chunk] of five words (the first is the opcode), word i in
+// lane i of r.  16-byte chunks go from global memory straight to LDS (no
+// registers, nothing to wait for until the phase ends), 64 consecutive
+// chunks an instruction.  Ops of up to 64 chunks go to the waves in turn,
+// larger ones are shared by all.
+constexpr int kCopyBatch = 12;  // ops in 64 words
+template <int BLK>
+__device__ __forceinline__ void issue_copies(int32_t r, int first, int n, const int32_t *tabs, const void *scratch,
+                                             unsigned char *lds, int lane, int wave) {
+    typedef __attribute__((address_space(1))) const uint32_t g_word;
+    typedef __attribute__((address_space(3))) uint32_t l_word;
+    constexpr int W = BLK / 64;
+    for (int i = 0; i < n; ++i) {
+        const int w = first + 5 * i, chunks = __builtin_amdgcn_readlane(r, w + 3);
+        const int seg = (wave - i) & (W - 1);
+        if (64 * seg >= chunks) continue;
+        const int kind = __builtin_amdgcn_readlane(r, w + 1), src = __builtin_amdgcn_readlane(r, w + 2);
+        const int dst = __builtin_amdgcn_readlane(r, w + 4);
+        const unsigned char *from =
+            (kind == 0 ? (const unsigned char *)tabs : (const unsigned char *)scratch) + 16 * (int64_t)src;
+        for (int c0 = 64 * seg; c0 < chunks; c0 += BLK)
+            if (c0 + lane < chunks)
+                __builtin_amdgcn_global_load_lds((g_word *)(from + 16 * (c0 + lane)), (l_word *)(lds + 16 * (dst + c0)),
+                                                 16, 0, 0);
     }
-    __syncthreads();
-    int32_t *slots = img + img[3];
-    const int slot_words = img[4];
-    unsigned char *red = smem + img[5];  // reduction scratch (256 bytes)
-    const int32_t *gimg = d.prog + img[6];
+}
+
+// Waits for the wave's global loads (also those on their way to LDS).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
+// The fused kernel: one network per workgroup.  The program's index (words
+// from header word 2 on: the number of phases, then per phase the word
+// offset and number of its copies and, per wave, the word offset of its
+// step or 0) leads every wave straight to its own work.  A phase issues the
+// copies for the next one (regions no step of the phase touches), runs
+// its steps (each on its own waves), waits for the copies and ends with a
+// barrier.
+template <int BLK, typename T, typename TIN, int FM>
+__device__ __forceinline__ void fused_body(const FusedDesc &d, void *const *__restrict__ outs,
+                                           int64_t *__restrict__ stamps, void *out1,
+                                           int64_t *__restrict__ phase_ticks, int max_phases, int64_t t0) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int W = BLK / 64, S = 2 + W;  // waves; index words per phase
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int net = d.net, n_words = d.n_words;
+    const int32_t *img = reinterpret_cast<const int32_t *>(smem);
+    // header and the first ops: phase 0 (copies only) starts from them while
+    // the program is on its way to LDS
+    int32_t head = lane < n_words ? d.prog[lane] : 0;
+    {
+        // the program itself is one copy (words a multiple of four)
+        typedef __attribute__((address_space(1))) const uint32_t g_word;
+        typedef __attribute__((address_space(3))) uint32_t l_word;
+        for (int c0 = 64 * wave; c0 < n_words / 4; c0 += BLK)
+            if (c0 + lane < n_words / 4)
+                __builtin_amdgcn_global_load_lds((g_word *)(d.prog + 4 * (c0 + lane)), (l_word *)(smem + 16 * c0), 16,
+                                                 0, 0);
+    }
+    if (d.n_fprep > 0) {
+        // materialise the network's (few) inputs into its workspace, one wave
+        // per entry, then make the writes visible to the workgroup's reads
+        for (int j = wave; j < d.n_fprep; j += W) fprep_tiny<T, TIN>(d.fprep[j], lane);
+        __threadfence();
+        __syncthreads();
+    }
+    const int slot0 = __builtin_amdgcn_readlane(head, 3), slot_words = __builtin_amdgcn_readlane(head, 4);
+    const int index = __builtin_amdgcn_readlane(head, 2);
+    unsigned char *red = smem + __builtin_amdgcn_readlane(head, 5);  // reduction scratch (256 bytes)
+    const int32_t *slots = img + slot0;
+    const int32_t *tabs = d.prog + __builtin_amdgcn_readlane(head, 6);
     T *sm = reinterpret_cast<T *>(smem);
     T *scr = (T *)d.scratch;
     void *out = out1 ? out1 : outs[net];
-    const int32_t *p = img + 8;
-    for (;;) {
-        const int op = p[0];
-        if (op == OP_END) break;
-        if (op == OP_SYNC) {
-            __syncthreads();
-            if (phase_ticks && threadIdx.x == 0 && phase < max_phases)
-                phase_ticks[(int64_t)net * max_phases + phase] = (int64_t)wall_clock64();
-            ++phase;
-            p += 1;
-            continue;
-        }
-        // A phase: the copies for the next phase (tables and operands; they
-        // land after this phase's steps, in regions no step of the phase
-        // touches), then the step ops (independent steps, each run by its
-        // own waves [w0, w0 + nw); none in the first phase, which only loads
-        // operands).  The copies come first so that their loads are issued
-        // before the steps are decoded: each thread stages up to kPrefetch
-        // chunks in registers while the steps run.
-        auto step_length = [](const int32_t *r) { return r[0] == OP_TSTEP ? 15 + 4 * (r[11] + r[12]) : 17; };
-        const int32_t *const copies0 = p;
-        const int32_t *q = p;
-        CopyOp cps[4];
-        int starts[5] = {0, 0, 0, 0, 0};
-        int nc = 0, tot = 0;
-        while (nc < 4 && q[0] == OP_COPY) {
-            cps[nc] = decode_copy(q, gimg, (const unsigned char *)d.scratch);
-            starts[nc] = tot;
-            tot += cps[nc].n;
-            ++nc;
-            q += 5;
-        }
-        starts[nc] = tot;
-        u32x4 stg0, stg1, stg2, stg3;
-        int dst0 = -1, dst1 = -1, dst2 = -1, dst3 = -1;
-        {
-            const g_uint4 *src[kPrefetch];
-            int dst[kPrefetch];
-#pragma unroll
-            for (int j = 0; j < kPrefetch; ++j) {
-                const int c = threadIdx.x + j * BLK;
-                src[j] = cps[0].src;
-                dst[j] = -1;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (k < nc && c >= starts[k] && c < starts[k + 1]) {
-                        src[j] = cps[k].src + (c - starts[k]);
-                        dst[j] = cps[k].dst + (c - starts[k]);
-                    }
-            }
-            if (dst[0] >= 0) stg0 = *src[0];
-            if (dst[1] >= 0) stg1 = *src[1];
-            if (dst[2] >= 0) stg2 = *src[2];
-            if (dst[3] >= 0) stg3 = *src[3];
-            dst0 = dst[0];
-            dst1 = dst[1];
-            dst2 = dst[2];
-            dst3 = dst[3];
-        }
-        const int32_t *const staged_end = q;  // copy ops [copies0, staged_end) are staged
-        while (q[0] == OP_COPY) q += 5;        // more than four copy ops: copied after the steps
-        const int32_t *const copies_end = q;
-        const int32_t *const steps0 = q;
-        while (q[0] == OP_STEP || q[0] == OP_TSTEP) q += step_length(q);
-        const int32_t *const steps_end = q;
-        const int wave = threadIdx.x >> 6;
-        for (const int32_t *op_w = steps0; op_w != steps_end; op_w += step_length(op_w)) {
-            const int w0 = op_w[0] == OP_TSTEP ? op_w[13] : op_w[15];
-            const int nw = op_w[0] == OP_TSTEP ? op_w[14] : op_w[16];
-            if (wave < w0 || wave >= w0 + nw) continue;  // wave-uniform
-            const int tid = threadIdx.x - 64 * w0, nthr = 64 * nw;
-            if (op_w[0] == OP_TSTEP) {
-                tstep_dispatch<BLK, T, FM, PURE>(op_w, sm, scr, out, tid, nthr);
-                continue;
-            }
-            // OP_STEP: [a, b, c, n_ohi, n_olo, n_shi, n_slo, t_ohi, t_olo, t_shi, t_slo, R, final, slot, w0, nw]
-            const int2 *itab2 = reinterpret_cast<const int2 *>(slots + op_w[14] * slot_words);
-            const int la = op_w[1], lb = op_w[2], lc = op_w[3];
-            const bool unary = lb == -1;
-            const bool fin = op_w[13] != 0;
-            const int R = op_w[12];
-            typedef typename std::conditional<FM == FM_INTER, T, double>::type TO;
-            constexpr bool CMP = (FM == FM_COMP);
-            if (PURE || (la >= 0 && (unary || lb >= 0) && (fin || lc >= 0))) {
-                const T *A = sm + la;
-                const T *B = unary ? nullptr : sm + lb;
-                if (!fin) {
-                    if (unary)
-                        fstep<BLK, T, T, false, true, T>(A, B, sm + lc, itab2, op_w + 4, R, (T *)red, tid, nthr);
-                    else
-                        fstep<BLK, T, T, false, false, T>(A, B, sm + lc, itab2, op_w + 4, R, (T *)red, tid, nthr);
-                } else {
-                    if (unary)
-                        fstep<BLK, T, TO, CMP, true, TO>(A, B, (TO *)out, itab2, op_w + 4, R, (TO *)red, tid, nthr);
-                    else
-                        fstep<BLK, T, TO, CMP, false, TO>(A, B, (TO *)out, itab2, op_w + 4, R, (TO *)red, tid, nthr);
-                }
-            } else if constexpr (!PURE) {
-                const T *A = la >= 0 ? sm + la : scr + (-la - 2);
-                const T *B = unary ? nullptr : (lb >= 0 ? sm + lb : scr + (-lb - 2));
-                if (!fin) {
-                    T *C = lc >= 0 ? sm + lc : scr + (-lc - 2);
-                    if (unary)
-                        fstep<BLK, T, T, false, true, T>(A, B, C, itab2, op_w + 4, R, (T *)red, tid, nthr);
-                    else
-                        fstep<BLK, T, T, false, false, T>(A, B, C, itab2, op_w + 4, R, (T *)red, tid, nthr);
-                } else {
-                    if (unary)
-                        fstep<BLK, T, TO, CMP, true, TO>(A, B, (TO *)out, itab2, op_w + 4, R, (TO *)red, tid, nthr);
-                    else
-                        fstep<BLK, T, TO, CMP, false, TO>(A, B, (TO *)out, itab2, op_w + 4, R, (TO *)red, tid, nthr);
-                }
+    int n_copies = 0;  // of phase 0, among the first 64 words
+    while (8 + 5 * n_copies + 4 < 64 && __builtin_amdgcn_readlane(head, 8 + 5 * n_copies) == OP_COPY) ++n_copies;
+    issue_copies<BLK>(head, 8, n_copies, tabs, d.scratch, smem, lane, wave);
+    wait_loads();
+    __syncthreads();
+    const int32_t *const entries = index < n_words ? img : d.prog;  // the index, in LDS where it fits
+    const int n_phases = __builtin_amdgcn_readfirstlane(entries[index]);
+    int at = index + 1;
+    int32_t ix = lane < S ? entries[at + lane] : 0;
+    for (int phase = 0; phase < n_phases; ++phase) {
+        const int c_off = __builtin_amdgcn_readlane(ix, 0), c_n = __builtin_amdgcn_readlane(ix, 1);
+        const int step = __builtin_amdgcn_readlane(ix, 2 + wave);
+        if (phase > 0 || c_n > n_copies) {
+            const int done = phase > 0 ? 0 : n_copies;
+            for (int i = done; i < c_n; i += kCopyBatch) {
+                const int o = c_off + 5 * i;
+                const int32_t r = o + lane < n_words ? img[o + lane] : 0;
+                issue_copies<BLK>(r, 0, min(kCopyBatch, c_n - i), tabs, d.scratch, smem, lane, wave);
             }
         }
-        // land the staged chunks, copy any remainder directly
-        u32x4 *lds4 = (u32x4 *)smem;
-        if (dst0 >= 0) lds4[dst0] = stg0;
-        if (dst1 >= 0) lds4[dst1] = stg1;
-        if (dst2 >= 0) lds4[dst2] = stg2;
-        if (dst3 >= 0) lds4[dst3] = stg3;
-        // then every chunk beyond the staged ones, all loads in flight
-        if (tot > kPrefetch * BLK || copies_end != staged_end)
-            copy_ops_flat<BLK>(copies0, copies_end, min(tot, kPrefetch * BLK), gimg, (const unsigned char *)d.scratch,
-                               lds4);
-        p = steps_end;
+        const StepWords p(img, n_words, step, lane);
+        at += S;
+        ix = lane < S && phase + 1 < n_phases ? entries[at + lane] : 0;  // the next phase's
+        if (step) run_step<BLK, T, FM>(p, sm, scr, out, slots, slot_words, red);
+        wait_loads();
+        if (phase > 0 || c_n > n_copies) __syncthreads();
+        if (phase_ticks && threadIdx.x == 0 && phase < max_phases)
+            phase_ticks[(int64_t)net * max_phases + phase] = (int64_t)wall_clock64();
     }
     if (stamps && threadIdx.x == 0) {
         stamps[2 * net] = t0;
@@ -655,20 +756,16 @@ __device__ __forceinline__ void fused_body(const FusedDesc &d, const int net, vo
 }
 
 template <int BLK, typename T, typename TIN, int FM>
-__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2))) void k_fused(const FusedDesc *__restrict__ nets, const int32_t *__restrict__ order,
-                                               void *const *__restrict__ outs, int64_t *__restrict__ stamps,
-                                               void *out1, int64_t *__restrict__ phase_ticks, int max_phases) {
-    const int net = order ? order[blockIdx.x] : (int)blockIdx.x;
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2))) void k_fused(
+    const FusedDesc *__restrict__ nets, void *const *__restrict__ outs, int64_t *__restrict__ stamps, void *out1,
+    int64_t *__restrict__ phase_ticks, int max_phases) {
     const int64_t t0 = stamps ? (int64_t)wall_clock64() : 0;
-    const FusedDesc d = nets[net];
-    if (d.lds_only)
-        fused_body<BLK, T, TIN, FM, true>(d, net, outs, stamps, out1, phase_ticks, max_phases, t0);
-    else
-        fused_body<BLK, T, TIN, FM, false>(d, net, outs, stamps, out1, phase_ticks, max_phases, t0);
+    const FusedDesc d = nets[blockIdx.x];
+    fused_body<BLK, T, TIN, FM>(d, outs, stamps, out1, phase_ticks, max_phases, t0);
 }
 
 template <int BLK, typename T, typename TIN, int FM>
-static hipError_t go_fused(const FusedDesc *nets, const int32_t *order, void *const *outs, int64_t *stamps,
+static hipError_t go_fused(const FusedDesc *nets, void *const *outs, int64_t *stamps,
                            void *out1, int64_t *phase_ticks, int max_phases, int n_blocks, int lds_bytes,
                            hipStream_t st) {
     static int configured = -1;
@@ -681,16 +778,16 @@ static hipError_t go_fused(const FusedDesc *nets, const int32_t *order, void *co
         }
         configured = lds_bytes;
     }
-    hipLaunchKernelGGL((k_fused<BLK, T, TIN, FM>), dim3(n_blocks), dim3(BLK), lds_bytes, st, nets, order, outs,
+    hipLaunchKernelGGL((k_fused<BLK, T, TIN, FM>), dim3(n_blocks), dim3(BLK), lds_bytes, st, nets, outs,
                        stamps, out1, phase_ticks, max_phases);
     return hipGetLastError();
 }
 
 template <int BLK>
-hipError_t launch_fused_blk(const FusedDesc *nets, const int32_t *order, void *const *outs, int64_t *stamps,
+hipError_t launch_fused_blk(const FusedDesc *nets, void *const *outs, int64_t *stamps,
                             void *out1, int64_t *phase_ticks, int max_phases, int n_blocks, int lds_bytes, int compute,
                             int fm, hipStream_t st) {
-#define HTN_GO(T, TIN, F) go_fused<BLK, T, TIN, F>(nets, order, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes, st)
+#define HTN_GO(T, TIN, F) go_fused<BLK, T, TIN, F>(nets, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes, st)
     if (compute == 0) return fm == FM_COMP ? HTN_GO(double, double, FM_COMP) : HTN_GO(double, double, FM_INTER);
     if (compute == 1) {
         if (fm == FM_COMP) return HTN_GO(float, float, FM_COMP);

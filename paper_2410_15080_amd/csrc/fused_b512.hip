@@ -3,7 +3,7 @@
 
 namespace htn {
 namespace kern {
-template hipError_t launch_fused_blk<512>(const FusedDesc *, const int32_t *, void *const *, int64_t *, void *,
+template hipError_t launch_fused_blk<512>(const FusedDesc *, void *const *, int64_t *, void *,
                                           int64_t *, int, int, int, int, int, hipStream_t);
 }  // namespace kern
 }  // namespace htn

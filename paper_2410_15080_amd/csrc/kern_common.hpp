@@ -203,5 +203,39 @@ __device__ __forceinline__ void fprep_entry(const FPrepEntry &en, int lane) {
     fprep_words<T, TIN>(ConstWords{(const c_int32 *)en.desc}, en.ws, en.e0, lane);
 }
 
+// An entry of a descriptor of at most 64 words, element by element: small
+// code for the fused kernel, where it runs for networks of a few hundred
+// input elements only.
+template <typename T, typename TIN>
+__device__ __forceinline__ void fprep_tiny(const FPrepEntry &en, int lane) {
+    typedef const TIN __attribute__((address_space(1))) g_tin;
+    const LaneWords p(en.desc, en.n_words, lane);
+    const int size = p(4), rk = p(5), ns = p(6);
+    const int per = 7 + 2 * ns, Wd = 4 + ns;
+    const int64_t dst_off = (int64_t)(((uint64_t)(uint32_t)p(3) << 32) | (uint32_t)p(2));
+    T *o = (T *)en.ws + dst_off;
+    const int e_end = min(size, en.e0 + kFPrepChunk);
+    for (int e = en.e0 + lane; e < e_end; e += 64) {
+        T v = T(0);
+        // the input (q = -1), then each scale in order
+        for (int q = -1; q < ns; ++q) {
+            const int w = q < 0 ? 0 : 7 + 2 * q;
+            const g_tin *src = (const g_tin *)(uintptr_t)(((uint64_t)(uint32_t)p(w + 1) << 32) | (uint32_t)p(w));
+            uint32_t rem = (uint32_t)e;
+            int off = 0;
+            for (int k = rk - 1; k >= 0; --k) {
+                const int pk = per + k * Wd;
+                const uint64_t magic = ((uint64_t)(uint32_t)p(pk + 2) << 32) | (uint32_t)p(pk + 1);
+                const uint32_t quo = (uint32_t)(((uint64_t)rem * magic) >> 40);
+                off += (int)(rem - quo * (uint32_t)p(pk)) * p(q < 0 ? pk + 3 : pk + 4 + q);
+                rem = quo;
+            }
+            const T f = to_compute<T>(src[off]);
+            v = q < 0 ? f : v * f;
+        }
+        o[e] = v;
+    }
+}
+
 }  // namespace kern
 }  // namespace htn

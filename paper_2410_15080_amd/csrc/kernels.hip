@@ -447,18 +447,18 @@ hipError_t launch_fprep(const FPrepEntry *entries, int n_entries, int form, int 
     return hipGetLastError();
 }
 
-hipError_t launch_fused(const FusedDesc *nets, const int32_t *order, void *const *outs, int64_t *stamps, void *out1,
+hipError_t launch_fused(const FusedDesc *nets, void *const *outs, int64_t *stamps, void *out1,
                         int64_t *phase_ticks, int max_phases, int n_blocks, int lds_bytes, int compute, int fm,
                         int threads, hipStream_t st) {
     if (n_blocks <= 0) return hipSuccess;
     if (threads == 64)
-        return launch_fused_blk<64>(nets, order, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes,
+        return launch_fused_blk<64>(nets, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes,
                                     compute, fm, st);
     if (threads == 256)
-        return launch_fused_blk<256>(nets, order, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes,
+        return launch_fused_blk<256>(nets, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes,
                                      compute, fm, st);
     if (threads == 512)
-        return launch_fused_blk<512>(nets, order, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes,
+        return launch_fused_blk<512>(nets, outs, stamps, out1, phase_ticks, max_phases, n_blocks, lds_bytes,
                                      compute, fm, st);
     return hipErrorInvalidValue;
 }

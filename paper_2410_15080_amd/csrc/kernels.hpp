@@ -53,27 +53,27 @@ hipError_t launch_prep(const PrepDesc *d_desc, int n_desc, int max_size, int tin
 struct FPrepEntry;
 struct FusedDesc {
     const int32_t *prog;
-    const int2 *tab;
-    const void *const *in;  // device array of input pointers
     void *scratch;          // workspace: materialised inputs, then spill space
     // inputs the workgroup materialises itself before its program
     // (n_fprep = 0: already done by a separate launch)
     const FPrepEntry *fprep;
     int32_t n_fprep;
-    int32_t lds_only;  // every operand and result of every step in LDS
+    int32_t n_words;  // program words (a multiple of four)
+    int32_t net;      // index of its result and clocks
+    int32_t pad;
 };
-// nets[order[b]] is run by workgroup b; outs[net] receives its result.
+// nets[b] is run by workgroup b; outs[nets[b].net] receives its result.
 // stamps (optional): [2*net] start, [2*net+1] end, 100 MHz ticks.
 // out1 (optional): output of a single-network launch, used instead of outs.
 // phase_ticks (optional): [net * max_phases + k] receives the clock at the
 // end of the network's k-th phase (after its barrier).
 // threads: 64, 256 or 512.
-hipError_t launch_fused(const FusedDesc *nets, const int32_t *order, void *const *outs, int64_t *stamps, void *out1,
+hipError_t launch_fused(const FusedDesc *nets, void *const *outs, int64_t *stamps, void *out1,
                         int64_t *phase_ticks, int max_phases, int n_blocks, int lds_bytes, int compute, int fm,
                         int threads, hipStream_t st);
 // One workgroup size (instantiated in fused_b<BLK>.hip).
 template <int BLK>
-hipError_t launch_fused_blk(const FusedDesc *nets, const int32_t *order, void *const *outs, int64_t *stamps,
+hipError_t launch_fused_blk(const FusedDesc *nets, void *const *outs, int64_t *stamps,
                             void *out1, int64_t *phase_ticks, int max_phases, int n_blocks, int lds_bytes, int compute,
                             int fm, hipStream_t st);
 

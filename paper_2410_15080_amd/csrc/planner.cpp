@@ -1022,13 +1022,23 @@ void build_plan(Net &n) {
             flat_table(n, s.t_gn, cn, P.tables, s.t_cn);
             auto digits = [&](const std::vector<int> &g, const std::vector<int64_t> &st, std::vector<int32_t> &out) {
                 out.clear();
+                // labels that follow one another in C as in the group are one
+                // digit (of at most 2^16 values); a label of extent 1 has none
+                std::vector<std::pair<uint64_t, int64_t>> dg;  // extent, stride
                 for (size_t k = 0; k < g.size(); ++k) {
                     const uint64_t d = (uint64_t)n.dims[g[k]];
-                    const uint64_t magic = ((uint64_t(1) << 40) + d - 1) / d;
-                    out.push_back((int32_t)d);
+                    if (d == 1) continue;
+                    if (!dg.empty() && dg.back().second == (int64_t)d * st[k] && dg.back().first * d < 65536)
+                        dg.back() = {dg.back().first * d, st[k]};
+                    else
+                        dg.push_back({d, st[k]});
+                }
+                for (auto &e : dg) {
+                    const uint64_t magic = ((uint64_t(1) << 40) + e.first - 1) / e.first;
+                    out.push_back((int32_t)e.first);
                     out.push_back((int32_t)(uint32_t)(magic & 0xffffffffu));
                     out.push_back((int32_t)(uint32_t)(magic >> 32));
-                    out.push_back((int32_t)st[k]);
+                    out.push_back((int32_t)e.second);
                 }
             };
             digits(s.t_gm, cm, s.c_digits_m);
@@ -1311,7 +1321,7 @@ void build_plan(Net &n) {
     // planned layout, coefficient tensors applied) by one prep launch into
     // the front of the network's workspace; the fused kernel then only moves
     // contiguous 16-byte chunks (OP_COPY) and computes.  Device image
-    // (int32 words): [0] program words, [1] LDS bytes, [2] op count,
+    // (int32 words): [0] program words, [1] LDS bytes, [2] word of the index,
     // [3] LDS word offset of table slot 0, [4] words per slot, [5] LDS byte
     // offset of the 256-byte reduction scratch, [6] image word offset of the
     // step tables, [7] image word offset of the load descriptors; ops from
@@ -1319,7 +1329,9 @@ void build_plan(Net &n) {
     // the prep kernel).  Phase 0 copies the tables and LDS-resident operands
     // of step 0; phase k runs step k and copies those of step k+1 (the
     // kernel issues these copies before the step's arithmetic); a barrier
-    // ends each phase.  Value locations: >= 0 LDS element offset; <= -2
+    // ends each phase.  The index, after the ops, holds the number of phases
+    // and per phase the word offset and number of its copies and, for
+    // each wave, the word offset of the step it runs (0: none).  Value locations: >= 0 LDS element offset; <= -2
     // workspace element offset -loc-2; -1 the network's output / none.
     {
         const int64_t es = dtype_size(inter_dtype(n.compute));
@@ -1460,7 +1472,18 @@ void build_plan(Net &n) {
             seq.push_back(OpRec{OP_SYNC, -1, -1, -1, {OP_SYNC}});
         }
         int64_t prog_words = 8 + 1;
-        for (auto &r : seq) prog_words += (int64_t)r.w.size();
+        int64_t n_syncs = 0;
+        for (auto &r : seq) {
+            prog_words += (int64_t)r.w.size();
+            n_syncs += r.kind == OP_SYNC;
+        }
+        const int W = std::max(1, n.fused_threads / 64), index_stride = 2 + W;
+        // (a budget too small for the index leaves it in the image, behind
+        // the program)
+        const int64_t index_words = 1 + n_syncs * index_stride;
+        auto lds_front = [&](int64_t words) { return ((words + 3) / 4 * 4 + 2 * slot_words) * 4 + 256; };
+        const bool index_in_lds = lds_front(prog_words + index_words) <= n.fused_lds_budget;
+        if (index_in_lds) prog_words += index_words;
         prog_words = (prog_words + 3) / 4 * 4;
         const int64_t slot0 = prog_words;
         const int64_t scratch_byte = (slot0 + 2 * slot_words) * 4;
@@ -1493,7 +1516,6 @@ void build_plan(Net &n) {
         };
         // keep spill scratch above the inputs area
         glb_ff.used[0] = inputs_end;
-        int n_ops = 0;
         std::vector<int> pending;
         int phase = 0, last_step = -1;
         bool lds_only = true;
@@ -1537,30 +1559,46 @@ void build_plan(Net &n) {
                 ++phase;
                 last_step = -1;
             }
-            ++n_ops;
         }
-        std::vector<int32_t> prog = {0, 0, n_ops, (int32_t)slot0, (int32_t)slot_words, (int32_t)scratch_byte, 0, 0};
+        std::vector<int32_t> prog = {0, 0, 0, (int32_t)slot0, (int32_t)slot_words, (int32_t)scratch_byte, 0, 0};
         // within a phase the copies (which land after its steps, into
         // regions no step of the phase touches) come first, so the kernel
         // issues their loads before decoding the steps
+        std::vector<int32_t> index = {(int32_t)n_syncs};
         {
-            std::vector<int32_t> steps_of_phase;
+            std::vector<const OpRec *> steps_of_phase;
+            std::vector<int32_t> entry(index_stride, 0);
             for (auto &r : seq) {
                 if (r.kind == OP_COPY && r.w[3] == 0) continue;
                 if (r.kind == OP_STEP || r.kind == OP_TSTEP) {
-                    steps_of_phase.insert(steps_of_phase.end(), r.w.begin(), r.w.end());
+                    steps_of_phase.push_back(&r);
                     continue;
                 }
+                if (r.kind == OP_COPY && entry[1]++ == 0) entry[0] = (int32_t)prog.size();
                 if (r.kind == OP_SYNC) {
-                    prog.insert(prog.end(), steps_of_phase.begin(), steps_of_phase.end());
+                    for (const OpRec *t : steps_of_phase) {
+                        const StepPlan &s = P.steps[t->step];
+                        // (a matrix-core step has no work for waves beyond its
+                        // 16x16 blocks)
+                        const int64_t blocks = s.tile && s.TM == 0 ? ((s.tM + 15) / 16) * ((s.tN + 15) / 16) : s.f_nw;
+                        for (int w = 0; w < s.f_nw && w < blocks; ++w) entry[2 + s.f_w0 + w] = (int32_t)prog.size();
+                        prog.insert(prog.end(), t->w.begin(), t->w.end());
+                    }
                     steps_of_phase.clear();
+                    index.insert(index.end(), entry.begin(), entry.end());
+                    entry.assign(index_stride, 0);
                 }
                 prog.insert(prog.end(), r.w.begin(), r.w.end());
             }
-            prog.insert(prog.end(), steps_of_phase.begin(), steps_of_phase.end());
         }
         prog.push_back(OP_END);
-        prog.resize(prog_words, 0);
+        if (!index_in_lds) prog.resize(prog_words, 0);
+        prog[2] = (int32_t)prog.size();
+        prog.insert(prog.end(), index.begin(), index.end());
+        if (index_in_lds)
+            prog.resize(prog_words, 0);
+        else
+            prog.resize((prog.size() + 3) / 4 * 4, 0);  // the tables that follow are read in 16-byte chunks
         prog[0] = (int32_t)prog_words;
         prog[6] = (int32_t)prog.size();
         prog.insert(prog.end(), gtab.begin(), gtab.end());
