@@ -181,7 +181,11 @@ typedef enum {
                                       HTN_OPT_MAX_INTERMEDIATE is HTN_E_OOM.  1: slicing (see below) */
     HTN_OPT_QUEUE = 8              /* batches: 0 (default) a net run step by step goes to the batch's
                                       work queue if its kernel steps are small (mean below 2^19
-                                      multiplications), else one launch per step; 1 the net always
+                                      multiplications), else to launches that it
+                                      shares with the batch's other such nets, one
+                                      per dependency level (nets up to 2^30
+                                      multiplications without fold chains, two or
+                                      more; the rest one launch per step); 1 the net always
                                       goes to the queue (even one the fused kernel could take);
                                       2 never (one launch per step, on side streams) */
 } htn_option;

@@ -126,6 +126,20 @@ struct htn_batch {
         hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     } q;
     std::vector<char> in_queue;
+    // Level launches of the step-by-step nets that are not in the queue
+    // (in_levels[k]: step_nets[k] is in them), on the first side stream.
+    struct Levels {
+        struct Level {
+            int item0 = 0, n_items = 0, n_blocks = 0;
+            int done0 = 0, n_done = 0;  // networks that the level before completed
+        };
+        std::vector<Level> level;  // (then one without items: the last ones' ends)
+        kern::QItem *d_items = nullptr;
+        int32_t *d_first = nullptr, *d_done = nullptr;
+        void *d_ws = nullptr;
+        int gk = 0;
+    } lv;
+    std::vector<char> in_levels;
     kern::FusedDesc *d_desc = nullptr;
     void **d_outs = nullptr;
     int64_t *d_stamps = nullptr;
@@ -399,10 +413,12 @@ static void upload_plan(Net &n) {
             q.thi[k] = (int32_t)lp.scales[k].t_hi;
             q.tlo[k] = (int32_t)lp.scales[k].t_lo;
             q.nlo[k] = (int32_t)lp.scales[k].n_lo;
+            kern::prep_divisor(q.nlo[k], q.mul[k], q.sh[k]);
         }
         q.sthi = (int32_t)lp.src_thi;
         q.stlo = (int32_t)lp.src_tlo;
         q.snlo = (int32_t)lp.src_nlo;
+        if (q.snlo > 0) kern::prep_divisor(q.snlo, q.smul, q.ssh);
         pmax = std::max<int>(pmax, q.size);
         prep.push_back(q);
     }
@@ -1049,6 +1065,14 @@ htn_status htn_plan_tables(htn_net_t net, int32_t *buf, int64_t capacity, int64_
 
 // ---------------------------------------------------------------- batch
 
+static void levels_free(htn_batch *b) {
+    dfree(b->lv.d_items);
+    dfree(b->lv.d_first);
+    dfree(b->lv.d_done);
+    dfree(b->lv.d_ws);
+    b->lv = htn_batch::Levels{};
+}
+
 static void batch_free(htn_batch *b) {
     if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
@@ -1068,6 +1092,7 @@ static void batch_free(htn_batch *b) {
     if (b->q.ev_fork) (void)hipEventDestroy(b->q.ev_fork);
     if (b->q.stream) (void)hipStreamDestroy(b->q.stream);
     b->q = htn_batch::Queue{};
+    levels_free(b);
     dfree(b->d_desc);
     dfree(b->d_outs);
     dfree(b->d_stamps);
@@ -1094,12 +1119,24 @@ static hipEvent_t next_event(htn_batch *b) {
 
 // ------------------------------------------------------------ work queue
 
+// Task sizes of the work queue: each task carries about kQTaskWork operand
+// reads (or element writes), and one item is cut into at most
+// kQMaxItemTasks tasks: a task's fixed cost (taking it, waiting, one
+// device-scope acquire and release) is then small against its work.  A task
+// of a level launch is a block of its grid, with no more to pay than its
+// start: smaller ones spread a level over the chip.
+static constexpr int64_t kQTaskWork = int64_t(1) << 14;
+static constexpr int64_t kQMaxItemTasks = 1024;
+static constexpr int64_t kLevelTaskWork = int64_t(1) << 12;
+static constexpr int64_t kLevelMaxItemTasks = 4096;
+
 namespace {
 // Items of the work queue under construction.  Buffers in the queue's
 // workspace are recorded as byte offsets (off: A, B, C, s.part; -1 where
 // the field holds a device address already) and patched once the
 // workspace is allocated.
 struct QBuild {
+    int64_t task_work = kQTaskWork, max_tasks = kQMaxItemTasks;
     std::vector<kern::QItem> items;
     std::vector<std::array<int64_t, 4>> off;
     std::vector<int> level, sub;  // dependency level and sub-queue (XCD) of each item
@@ -1121,6 +1158,21 @@ struct QBuild {
         sub.push_back(cur_sub);
         return (int)items.size() - 1;
     }
+    // a net's items taken back
+    struct Mark {
+        size_t n;
+        int64_t ws;
+        int gk;
+    };
+    Mark mark() const { return {items.size(), ws, gk}; }
+    void reset(const Mark &m) {
+        items.resize(m.n);
+        off.resize(m.n);
+        level.resize(m.n);
+        sub.resize(m.n);
+        ws = m.ws;
+        gk = m.gk;
+    }
 };
 }  // namespace
 
@@ -1135,25 +1187,18 @@ static kern::QItem q_item(int kind, int net, const Net &n) {
     return it;
 }
 
-// Task sizes of the work queue: each task carries about kQTaskWork operand
-// reads (or element writes), and one item is cut into at most
-// kQMaxItemTasks tasks: a task's fixed cost (taking it, waiting, one
-// device-scope acquire and release) is then small against its work.
-static constexpr int64_t kQTaskWork = int64_t(1) << 14;
-static constexpr int64_t kQMaxItemTasks = 1024;
-
-static int64_t q_units_per_task(int64_t units, int64_t work_per_unit) {
+static int64_t q_units_per_task(const QBuild &Q, int64_t units, int64_t work_per_unit) {
     const int64_t work = units * std::max<int64_t>(1, work_per_unit);
-    const int64_t tasks = std::min<int64_t>(kQMaxItemTasks, std::max<int64_t>(1, work / kQTaskWork));
+    const int64_t tasks = std::min<int64_t>(Q.max_tasks, std::max<int64_t>(1, work / Q.task_work));
     return std::max<int64_t>(1, (units + tasks - 1) / tasks);
 }
 
 // Blocks of a table-driven step per task (operand reads per block: 256
 // threads, each summing its share of the summed range).
-static int64_t q_step_blocks_per_task(const kern::StepArgs &a, int64_t n_sum, int64_t blocks) {
+static int64_t q_step_blocks_per_task(const QBuild &Q, const kern::StepArgs &a, int64_t n_sum, int64_t blocks) {
     const int64_t chunk = a.split > 1 ? a.chunk : n_sum;
     const int64_t per_thread = std::max<int64_t>(1, (chunk + a.R - 1) / a.R);
-    return q_units_per_task(blocks, kBlock * per_thread);
+    return q_units_per_task(Q, blocks, kBlock * per_thread);
 }
 
 // Appends the items of net `bi` of the batch; false (nothing appended) if
@@ -1191,7 +1236,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
         it.tc = tint;
         it.prep = D.d_prep + D.prep_index[j++];
         it.n_units = (lp.size + 255) / 256;
-        it.units_per_task = (int32_t)q_units_per_task(it.n_units, 256 * (1 + (int64_t)lp.scales.size()));
+        it.units_per_task = (int32_t)q_units_per_task(Q, it.n_units, 256 * (1 + (int64_t)lp.scales.size()));
         voff[lp.value] = Q.take(lp.size * es);
         prod[lp.value] = Q.add(it, {-1, -1, voff[lp.value], -1});
     }
@@ -1246,7 +1291,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
                 it.unary = 1;
                 it.s = pack_args(pk);
                 it.n_units = (pk.n + kBlock - 1) / kBlock;
-                it.units_per_task = (int32_t)q_step_blocks_per_task(it.s, 1, it.n_units);
+                it.units_per_task = (int32_t)q_step_blocks_per_task(Q, it.s, 1, it.n_units);
                 Opd r;
                 r.off = o[2] = Q.take(pk.n * pes);
                 r.t = tp;
@@ -1285,7 +1330,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
                 ksum.dep0 = g;
                 ksum.flags = out_flags;
                 ksum.n_units = (total + 255) / 256;
-                ksum.units_per_task = (int32_t)q_units_per_task(ksum.n_units, 256 * (int64_t)ks);
+                ksum.units_per_task = (int32_t)q_units_per_task(Q, ksum.n_units, 256 * (int64_t)ks);
                 last = Q.add(ksum, {part_off, -1, coff, -1});
             } else {
                 it.flags = out_flags;
@@ -1323,7 +1368,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
                 o[3] = Q.take(s.n_out * s.split_global * 16);
             }
             it.n_units = (s.n_out * a.R * a.split + kBlock - 1) / kBlock;
-            it.units_per_task = (int32_t)q_step_blocks_per_task(a, s.n_sum, it.n_units);
+            it.units_per_task = (int32_t)q_step_blocks_per_task(Q, a, s.n_sum, it.n_units);
             if (a.split > 1) {
                 const int g = Q.add(it, o);
                 kern::QItem fin = q_item(kern::QI_FINISH, bi, n);
@@ -1333,7 +1378,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
                 fin.dep0 = g;
                 fin.flags = out_flags;
                 fin.n_units = (s.n_out + 3) / 4;
-                fin.units_per_task = (int32_t)q_units_per_task(fin.n_units, 4 * (int64_t)a.split);
+                fin.units_per_task = (int32_t)q_units_per_task(Q, fin.n_units, 4 * (int64_t)a.split);
                 last = Q.add(fin, {-1, -1, coff, o[3]});
             } else {
                 it.flags = out_flags;
@@ -1456,6 +1501,106 @@ static void queue_upload(htn_batch *b, QBuild &Q, const std::vector<int> &sub_xc
     // every XCD must get workgroups: the whole resident capacity (workgroups
     // are spread over the XCDs; those without a task leave at once)
     q.n_blocks = std::max(kern::queue_blocks_per_cu(q.gk, q.lds) * cus, 2 * kern::QC_MAX_SUB);
+}
+
+// Level launches take a step-by-step net whose steps leave a launch of their
+// own mostly overhead: up to 2^30 multiplications (8 us of FP32 products at
+// the matrix cores' rate, about what a launch costs), without fold chains
+// (those have a kernel of their own).  Their intermediates are kept apart for
+// the batch's lifetime, up to kLevelMaxBytes in all; the nets beyond that, or
+// all of them where the device has no such memory left, keep one launch per
+// step in their own workspaces.
+static constexpr double kLevelMaxMults = 1073741824.0;
+static constexpr int64_t kLevelMaxBytes = int64_t(8) << 30;
+
+static bool level_net(const Net &n) {
+    return n.queue_mode == 0 && n.plan.chains.empty() && n.plan.mults <= kLevelMaxMults;
+}
+
+// Orders the items by dependency level, heaviest item first, and uploads;
+// false (nothing kept) if the device has no memory for the intermediates.
+static bool levels_upload(htn_batch *b, QBuild &Q) {
+    htn_batch::Levels &lv = b->lv;
+    const int ni = (int)Q.items.size();
+    if (Q.ws > 0) {
+        hipError_t e = hipMalloc(&lv.d_ws, (size_t)Q.ws);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            lv.d_ws = nullptr;
+            return false;
+        }
+    }
+    unsigned char *ws = (unsigned char *)lv.d_ws;
+    std::vector<int> order(ni);
+    std::vector<int64_t> tasks(ni);
+    for (int i = 0; i < ni; ++i) {
+        order[i] = i;
+        const kern::QItem &it = Q.items[i];
+        tasks[i] = (it.n_units + it.units_per_task - 1) / it.units_per_task;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        return Q.level[x] != Q.level[y] ? Q.level[x] < Q.level[y] : tasks[x] > tasks[y];
+    });
+    std::vector<kern::QItem> items(ni);
+    std::vector<int32_t> first(ni), done;
+    std::vector<char> seen(b->nets.size(), 0);
+    lv.level.clear();
+    int cur = -1;
+    std::vector<int32_t> ended;  // by the level under construction
+    auto open_level = [&](int i) {
+        htn_batch::Levels::Level L;
+        L.item0 = i;
+        L.done0 = (int)done.size();
+        L.n_done = (int)ended.size();
+        done.insert(done.end(), ended.begin(), ended.end());
+        ended.clear();
+        lv.level.push_back(L);
+    };
+    for (int i = 0; i < ni; ++i) {
+        const int k = order[i];
+        if (i == 0 || Q.level[k] != cur) {
+            open_level(i);
+            cur = Q.level[k];
+        }
+        auto &L = lv.level.back();
+        kern::QItem it = Q.items[k];
+        const auto &o = Q.off[k];
+        if (o[0] >= 0) it.A = ws + o[0];
+        if (o[1] >= 0) it.B = ws + o[1];
+        if (o[2] >= 0) it.C = ws + o[2];
+        if (o[3] >= 0) it.s.part = (double *)(ws + o[3]);
+        if (!seen[it.net]) {
+            it.flags |= kern::QF_FIRST;
+            seen[it.net] = 1;
+        }
+        if (it.flags & kern::QF_LAST) ended.push_back(it.net);
+        if (L.n_blocks + tasks[k] > (int64_t(1) << 30)) throw Error{HTN_E_UNSUPPORTED, "level: too many blocks"};
+        it.n_tasks = (int32_t)tasks[k];
+        first[i] = L.n_blocks;
+        L.n_blocks += (int)tasks[k];
+        ++L.n_items;
+        items[i] = it;
+    }
+    open_level(ni);
+    lv.gk = Q.gk;
+    lv.d_items = dalloc<kern::QItem>(ni);
+    HIP_TRY(hipMemcpy(lv.d_items, items.data(), ni * sizeof(kern::QItem), hipMemcpyHostToDevice));
+    lv.d_first = dalloc<int32_t>(ni);
+    HIP_TRY(hipMemcpy(lv.d_first, first.data(), ni * 4, hipMemcpyHostToDevice));
+    lv.d_done = dalloc<int32_t>(done.size());
+    HIP_TRY(hipMemcpy(lv.d_done, done.data(), done.size() * 4, hipMemcpyHostToDevice));
+    return true;
+}
+
+static void run_levels(htn_batch *b, hipStream_t st) {
+    const htn_batch::Levels &lv = b->lv;
+    for (const auto &L : lv.level) {
+        if (L.n_items)
+            HIP_TRY(kern::launch_level(lv.d_items + L.item0, lv.d_first + L.item0, L.n_items, L.n_blocks, b->d_outs,
+                                       b->d_stamps, lv.d_done + L.done0, L.n_done, lv.gk, st));
+        else if (L.n_done)
+            HIP_TRY(kern::launch_level_end(b->d_stamps, lv.d_done + L.done0, L.n_done, st));
+    }
 }
 
 htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) {
@@ -1585,6 +1730,25 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
                     HIP_TRY(hipEventCreateWithFlags(&b->q.ev_join, hipEventDisableTiming));
                 }
             }
+            // the others in level launches, if they can and are several
+            QBuild L;
+            L.task_work = kLevelTaskWork;
+            L.max_tasks = kLevelMaxItemTasks;
+            b->in_levels.assign(b->step_nets.size(), 0);
+            int n_level = 0;
+            for (size_t k = 0; k < b->step_nets.size(); ++k) {
+                Net &net = *nets[b->step_nets[k]];
+                if (b->in_queue[k] || !level_net(net)) continue;
+                const QBuild::Mark m = L.mark();
+                if (!queue_net(L, net, b->step_nets[k])) continue;
+                if (L.ws > kLevelMaxBytes) {
+                    L.reset(m);
+                    continue;
+                }
+                b->in_levels[k] = 1;
+                ++n_level;
+            }
+            if (n_level < 2 || !levels_upload(b, L)) b->in_levels.assign(b->step_nets.size(), 0);
             HIP_TRY(hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
             for (int q = 0; q < ns; ++q) {
                 hipStream_t sq = nullptr;
@@ -1678,8 +1842,10 @@ static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool 
         HIP_TRY(hipEventRecord(b->q.ev_join, b->q.stream));
         HIP_TRY(hipStreamWaitEvent(st, b->q.ev_join, 0));
     }
+    const bool use_levels = !b->lv.level.empty() && !b->d_phase;
+    if (use_levels) run_levels(b, b->sides[0]);
     for (size_t k = 0; k < b->step_nets.size(); ++k) {
-        if (use_queue && b->in_queue[k]) continue;
+        if ((use_queue && b->in_queue[k]) || (use_levels && b->in_levels[k])) continue;
         const int i = b->step_nets[k];
         hipStream_t ss = b->sides[b->side_of[k]];
         HIP_TRY(kern::launch_stamp(b->d_stamps + 2 * (size_t)i, ss));

@@ -95,8 +95,7 @@ __global__ __launch_bounds__(kBlk) void k_prep(const PrepDesc *__restrict__ desc
                                                 unsigned char *__restrict__ ws) {
     const PrepDesc &q = descs[blockIdx.y];
     TI *dst = (TI *)(ws + q.dst_off);
-    for (int e = blockIdx.x * kBlk + threadIdx.x; e < q.size; e += gridDim.x * kBlk)
-        dst[e] = prep_value<TIN, TI>(q, tab, e);
+    prep_range<TIN, TI>(q, tab, dst, blockIdx.x * kBlk + threadIdx.x, q.size, gridDim.x * kBlk);
 }
 
 hipError_t launch_prep(const PrepDesc *d_desc, int n_desc, int max_size, int tin, int tinter, const int2 *tab,

@@ -44,7 +44,19 @@ struct PrepDesc {
     const void *sp[kMaxScalesDev];
     int32_t thi[kMaxScalesDev], tlo[kMaxScalesDev], nlo[kMaxScalesDev];
     int32_t sthi, stlo, snlo;  // source gather table (snlo = 0: same layout)
+    // multipliers and shifts of the divisions by nlo[k] and snlo (prep_div)
+    uint32_t mul[kMaxScalesDev], smul;
+    int32_t sh[kMaxScalesDev], ssh;
 };
+// Multiplier and shift that divide by d (1 <= d < 2^31): for 0 <= e < 2^31,
+// e / d = (e * mul) >> (31 + sh) with mul = ceil(2^(31 + sh) / d) and 2^sh the
+// power of two at or above d (the rounding of mul adds less than
+// e * 2^sh / 2^(31 + sh) < 1 part of d, so the quotient is exact).
+inline void prep_divisor(int32_t d, uint32_t &mul, int32_t &sh) {
+    sh = 0;
+    while ((int64_t(1) << sh) < d) ++sh;
+    mul = (uint32_t)(((uint64_t(1) << (31 + sh)) + (uint64_t)d - 1) / (uint64_t)d);
+}
 // ws: the workspace the copies are written to (base of dst_off).
 hipError_t launch_prep(const PrepDesc *d_desc, int n_desc, int max_size, int tin, int tinter, const int2 *tab,
                        void *ws, hipStream_t st);
@@ -245,6 +257,15 @@ int queue_blocks_per_cu(int gk, int lds_bytes);
 hipError_t launch_queue(const QItem *items, const QTask *tasks, const int32_t *qinfo, int n_sub, const int32_t *init,
                         int32_t *counters, int n_items, int32_t *ctrl, void *const *outs, int64_t *stamps,
                         int64_t *run_start, int gk, int lds_bytes, int n_blocks, hipStream_t st);
+
+// Level launches (queue.hip): the queue's items, one launch per dependency
+// level over the whole device instead of one persistent launch per network
+// and XCD.  first[i]: the level's first block of item i (blocks in all:
+// n_blocks, one per task).  done: networks that the previous level completed
+// (their end clocks are stamped); launch_level_end stamps those of the last.
+hipError_t launch_level(const QItem *items, const int32_t *first, int n_items, int n_blocks, void *const *outs,
+                        int64_t *stamps, const int32_t *done, int n_done, int gk, hipStream_t st);
+hipError_t launch_level_end(int64_t *stamps, const int32_t *done, int n_done, hipStream_t st);
 
 // Fold chain: a value X contracted with small matrices one mode at a time.
 // X's labels split into in-tile axes (every folded axis, plus carried axes

@@ -176,23 +176,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-// Sum of the K-range partial products, in range order; eight ranges are read
-// before they are added (18 ranges of 124 416 outputs took 54 us one by one).
+// Sum of the K-range partial products, in range order.
 template <typename TOUT>
 __global__ __launch_bounds__(256) void k_ksum(const TOUT *__restrict__ part, TOUT *__restrict__ C, int64_t total,
                                              int ksplit) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        TOUT a = part[i];
-        int kz = 1;
-        for (; kz + 8 <= ksplit; kz += 8) {
-            TOUT v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(kz + u) * total + i];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a += v[u];
-        }
-        for (; kz < ksplit; ++kz) a += part[(int64_t)kz * total + i];
-        C[i] = a;
+        C[i] = ksum_one(part + i, total, ksplit);
     }
 }
 

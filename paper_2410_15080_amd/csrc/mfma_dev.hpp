@@ -234,6 +234,24 @@ __device__ void gemm_tile(const T *__restrict__ A0, const T *__restrict__ B0, TO
             }
 }
 
+// Partial products of one output, `total` apart, added in range order; eight
+// ranges are read before they are added (18 ranges of 124 416 outputs: 54 us
+// one by one, 5.8 us so).
+template <typename TOUT>
+__device__ __forceinline__ TOUT ksum_one(const TOUT *__restrict__ part, int64_t total, int ksplit) {
+    TOUT a = part[0];
+    int kz = 1;
+    for (; kz + 8 <= ksplit; kz += 8) {
+        TOUT v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(kz + u) * total];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a += v[u];
+    }
+    for (; kz < ksplit; ++kz) a += part[(int64_t)kz * total];
+    return a;
+}
+
 // K range of each split part (a multiple of 64) and the number of parts.
 __host__ __device__ inline void gemm_ksplit(int K, int &ksplit, int &kper) {
     kper = ksplit > 1 ? ((K + ksplit - 1) / ksplit + 63) / 64 * 64 : K;

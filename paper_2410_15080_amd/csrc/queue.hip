@@ -129,10 +129,8 @@ __device__ void q_finish(const QItem &it, void *C, int64_t u0, int64_t u1) {
 template <typename TIN, typename TI>
 __device__ void q_load_t(const QItem &it, void *C, int64_t u0, int64_t u1) {
     const PrepDesc &q = *it.prep;
-    TI *dst = (TI *)C;
-    const int64_t e1 = min(u1 * kQThreads, (int64_t)q.size);
-    for (int64_t e = u0 * kQThreads + threadIdx.x; e < e1; e += kQThreads)
-        dst[e] = prep_value<TIN, TI>(q, it.tab, (int)e);
+    prep_range<TIN, TI>(q, it.tab, (TI *)C, u0 * kQThreads + threadIdx.x, min(u1 * kQThreads, (int64_t)q.size),
+                        kQThreads);
 }
 
 __device__ void q_load(const QItem &it, void *C, int64_t u0, int64_t u1) {
@@ -151,9 +149,7 @@ __device__ void q_ksum_t(const QItem &it, void *C, int64_t u0, int64_t u1) {
     const TOUT *part = (const TOUT *)it.A;
     const int64_t e1 = min(u1 * kQThreads, it.total);
     for (int64_t i = u0 * kQThreads + threadIdx.x; i < e1; i += kQThreads) {
-        TOUT a = part[i];
-        for (int kz = 1; kz < it.ksplit; ++kz) a += part[(int64_t)kz * it.total + i];
-        ((TOUT *)C)[i] = a;
+        ((TOUT *)C)[i] = ksum_one(part + i, it.total, it.ksplit);
     }
 }
 
@@ -177,6 +173,31 @@ __device__ void q_gemm(const QItem &it, void *C, int64_t u0, int64_t u1, unsigne
         if constexpr (GK == 5) HTN_TILE(bf16_t, float, false);
 #undef HTN_TILE
         __syncthreads();  // the tile's LDS is free before the next one is staged
+    }
+}
+
+// Units [u0, u1) of an item.
+template <int GK>
+__device__ __forceinline__ void q_run(const QItem &it, void *C, int64_t u0, int64_t u1, unsigned char *lds) {
+    switch (it.kind) {
+        case QI_LOAD:
+            q_load(it, C, u0, u1);
+            break;
+        case QI_STEP:
+            q_step(it, C, u0, u1);
+            break;
+        case QI_FINISH:
+            q_finish(it, C, u0, u1);
+            break;
+        case QI_GEMM:
+            if constexpr (GK != 0) q_gemm<GK>(it, C, u0, u1, lds);
+            break;
+        default:
+            if (it.tc == 0)
+                q_ksum_t<double>(it, C, u0, u1);
+            else
+                q_ksum_t<float>(it, C, u0, u1);
+            break;
     }
 }
 
@@ -236,26 +257,7 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK ? 
             void *C = (it.flags & QF_OUT) ? outs[it.net] : it.C;
             const int64_t u0 = (int64_t)tk.task * it.units_per_task;
             const int64_t u1 = min(it.n_units, u0 + it.units_per_task);
-            switch (it.kind) {
-                case QI_LOAD:
-                    q_load(it, C, u0, u1);
-                    break;
-                case QI_STEP:
-                    q_step(it, C, u0, u1);
-                    break;
-                case QI_FINISH:
-                    q_finish(it, C, u0, u1);
-                    break;
-                case QI_GEMM:
-                    if constexpr (GK != 0) q_gemm<GK>(it, C, u0, u1, q_lds);
-                    break;
-                default:
-                    if (it.tc == 0)
-                        q_ksum_t<double>(it, C, u0, u1);
-                    else
-                        q_ksum_t<float>(it, C, u0, u1);
-                    break;
-            }
+            q_run<GK>(it, C, u0, u1, q_lds);
             // every wave waits until its stores have reached the L2 (a
             // workgroup-scope fence does not wait: the waves share one CU);
             // thread 0 then counts the task done at the top of the loop
@@ -286,6 +288,40 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK ? 
     }
 }
 
+// One dependency level of the level launches: items [0, n_items) of the
+// level, of every network in them, all in one grid; item i has the blocks
+// from first[i] on.  What the items read was written by earlier launches on
+// the stream.  Launched one by one, a network's steps are a chain of small
+// grids (8 to 25 us each, most of it filling and draining the chip); all the
+// networks' steps of one level together fill it.  done: the networks that
+// the previous level completed, whose end clocks are read here.
+template <int GK>
+__global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK ? 2 : 1))) void k_level(
+    const QItem *__restrict__ items, const int32_t *__restrict__ first, int n_items, void *const *__restrict__ outs,
+    int64_t *__restrict__ stamps, const int32_t *__restrict__ done, int n_done) {
+    extern __shared__ __align__(16) unsigned char q_lds[];
+    const int blk = blockIdx.x, lane = threadIdx.x & 63;
+    if (blk == 0)
+        for (int i = threadIdx.x; i < n_done; i += kQThreads) stamps[2 * done[i] + 1] = (int64_t)wall_clock64();
+    // the item this block belongs to: the last whose first block is <= blk
+    int i = -1;
+    for (int b = 0; b < n_items; b += 64) {
+        const bool le = b + lane < n_items && first[b + lane] <= blk;
+        i += __popcll(__ballot(le));
+    }
+    i = __builtin_amdgcn_readfirstlane(i);
+    const QItem &it = items[i];
+    const int task = blk - first[i];
+    if (threadIdx.x == 0 && task == 0 && (it.flags & QF_FIRST)) stamps[2 * it.net] = (int64_t)wall_clock64();
+    void *C = (it.flags & QF_OUT) ? outs[it.net] : it.C;
+    const int64_t u0 = (int64_t)task * it.units_per_task;
+    q_run<GK>(it, C, u0, min(it.n_units, u0 + it.units_per_task), q_lds);
+}
+
+__global__ void k_level_end(int64_t *__restrict__ stamps, const int32_t *__restrict__ done, int n_done) {
+    for (int i = threadIdx.x; i < n_done; i += blockDim.x) stamps[2 * done[i] + 1] = (int64_t)wall_clock64();
+}
+
 // One wave per workgroup records the XCD it runs on.
 __global__ void k_xcc_probe(uint32_t *mask) {
     if (threadIdx.x == 0) atomicOr(mask, 1u << q_xcc_id());
@@ -307,6 +343,15 @@ hipError_t go_queue(const QItem *items, const QTask *tasks, const int32_t *qinfo
     }
     hipLaunchKernelGGL((k_queue<GK>), dim3((unsigned)n_blocks), dim3(kQThreads), lds_bytes, st, items, tasks, qinfo,
                        n_sub, init, counters, n_items, ctrl, outs, stamps, run_start);
+    return hipGetLastError();
+}
+
+template <int GK>
+hipError_t go_level(const QItem *items, const int32_t *first, int n_items, int n_blocks, void *const *outs,
+                    int64_t *stamps, const int32_t *done, int n_done, hipStream_t st) {
+    // (a tile's LDS is below the 64 KB a kernel may use unasked)
+    hipLaunchKernelGGL((k_level<GK>), dim3((unsigned)n_blocks), dim3(kQThreads), queue_gemm_lds(GK), st, items, first,
+                       n_items, outs, stamps, done, n_done);
     return hipGetLastError();
 }
 
@@ -367,6 +412,27 @@ hipError_t launch_queue(const QItem *items, const QTask *tasks, const int32_t *q
         default: return hipErrorInvalidValue;
     }
 #undef HTN_GO
+}
+
+hipError_t launch_level(const QItem *items, const int32_t *first, int n_items, int n_blocks, void *const *outs,
+                        int64_t *stamps, const int32_t *done, int n_done, int gk, hipStream_t st) {
+    if (n_items < 1 || n_blocks < 1) return hipErrorInvalidValue;
+#define HTN_GO(G) go_level<G>(items, first, n_items, n_blocks, outs, stamps, done, n_done, st)
+    switch (gk) {
+        case 0: return HTN_GO(0);
+        case 1: return HTN_GO(1);
+        case 2: return HTN_GO(2);
+        case 3: return HTN_GO(3);
+        case 4: return HTN_GO(4);
+        case 5: return HTN_GO(5);
+        default: return hipErrorInvalidValue;
+    }
+#undef HTN_GO
+}
+
+hipError_t launch_level_end(int64_t *stamps, const int32_t *done, int n_done, hipStream_t st) {
+    hipLaunchKernelGGL(k_level_end, dim3(1), dim3(64), 0, st, stamps, done, n_done);
+    return hipGetLastError();
 }
 
 uint32_t queue_xcc_mask(uint32_t *d_word) {

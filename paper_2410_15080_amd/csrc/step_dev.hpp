@@ -114,24 +114,62 @@ __device__ __forceinline__ void split_finish_one(const double *__restrict__ part
     if (lane == 0) C[o] = st_cvt<TC>(COMP ? sum + cmp : sum);
 }
 
-// Element e of a scaled-input materialisation: the input entry (through the
-// source gather table when the layout changes) times each folded
-// coefficient tensor's entry, in the intermediate type.
-template <typename TIN, typename TI>
-__device__ __forceinline__ TI prep_value(const PrepDesc &q, const int2 *__restrict__ tab, int e) {
+__device__ __forceinline__ int prep_div(int e, uint32_t mul, int sh) {
+    return (int)(__umulhi((uint32_t)e << 1, mul) >> sh);
+}
+
+// Elements e0, e0 + step, ... (NB of them) of a scaled-input
+// materialisation: the input entry (through the source gather table when the
+// layout changes) times each folded coefficient tensor's entry, in the
+// intermediate type.  The NB elements are independent chains of loads side
+// by side, and quotients come from a multiplication: a division of an int
+// is some forty instructions, and with one per table look-up they, not
+// memory, set the time.
+template <int NB, typename TIN, typename TI>
+__device__ __forceinline__ void prep_values(const PrepDesc &q, const int2 *__restrict__ tab, int e0, int step,
+                                            TI (&v)[NB]) {
     const TIN *src = (const TIN *)q.src;
-    int se = e;
+    int se[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) se[u] = e0 + u * step;
     if (q.snlo > 0) {
-        const int eh = e / q.snlo;
-        se = tab[q.sthi + eh].x + tab[q.stlo + (e - eh * q.snlo)].x;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int e = se[u], eh = prep_div(e, q.smul, q.ssh);
+            se[u] = tab[q.sthi + eh].x + tab[q.stlo + (e - eh * q.snlo)].x;
+        }
     }
-    TI v = Ld<TI, TIN>::get(src + se);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) v[u] = Ld<TI, TIN>::get(src + se[u]);
     for (int k = 0; k < q.ns; ++k) {
-        const int eh = e / q.nlo[k];
-        const int el = e - eh * q.nlo[k];
-        v *= Ld<TI, TIN>::get((const TIN *)q.sp[k] + tab[q.thi[k] + eh].x + tab[q.tlo[k] + el].x);
+        TI c[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int e = e0 + u * step, eh = prep_div(e, q.mul[k], q.sh[k]);
+            c[u] = Ld<TI, TIN>::get((const TIN *)q.sp[k] + tab[q.thi[k] + eh].x +
+                                    tab[q.tlo[k] + (e - eh * q.nlo[k])].x);
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) v[u] *= c[u];
     }
-    return v;
+}
+
+// Elements first, first + step, ... below end, four at a time.
+template <typename TIN, typename TI>
+__device__ __forceinline__ void prep_range(const PrepDesc &q, const int2 *__restrict__ tab, TI *__restrict__ dst,
+                                           int64_t first, int64_t end, int step) {
+    int64_t e = first;
+    for (; e + 3 * (int64_t)step < end; e += 4 * (int64_t)step) {
+        TI v[4];
+        prep_values<4, TIN, TI>(q, tab, (int)e, step, v);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) dst[e + u * (int64_t)step] = v[u];
+    }
+    for (; e < end; e += step) {
+        TI v[1];
+        prep_values<1, TIN, TI>(q, tab, (int)e, step, v);
+        dst[e] = v[0];
+    }
 }
 
 }  // namespace kern
