@@ -605,6 +605,23 @@ static kern::StepArgs pack_args(const StepPlan::Pack &pk) {
     return a;
 }
 
+static kern::TileArgs tile_args(const StepPlan &s) {
+    static const int rows[3] = {32, 64, 16}, cols[3] = {32, 16, 64};
+    kern::TileArgs t;
+    t.M = (int32_t)(s.x_swap ? s.tN : s.tM);
+    t.N = (int32_t)(s.x_swap ? s.tM : s.tN);
+    t.K = (int32_t)s.tK;
+    t.t_cm = (int32_t)(s.x_swap ? s.t_cn : s.t_cm);
+    t.t_cn = (int32_t)(s.x_swap ? s.t_cm : s.t_cn);
+    t.ksplit = s.x_split;
+    t.kper = s.x_kper;
+    t.shape = s.x_shape;
+    t.tiles_m = (t.M + rows[t.shape] - 1) / rows[t.shape];
+    t.tiles_n = (t.N + cols[t.shape] - 1) / cols[t.shape];
+    t.total = s.tM * s.tN;
+    return t;
+}
+
 // Matrix-core step: pack both operands K-contiguous, then one GEMM launch.
 static void run_mfma_step(Net &n, const StepPlan &s, const void *A, int ta, const void *B, int tb, void *C, int tc,
                           unsigned char *ws, hipStream_t st) {
@@ -697,6 +714,12 @@ static void run_steps(Net &n, void *out, hipStream_t st, int64_t *ticks = nullpt
                 HIP_TRY(kern::launch_folds(jobs.data() + j0, (int)(j1 - j0), tin, tint, types[j0], st));
                 j0 = j1;
             }
+            continue;
+        }
+        if (s.x_tile) {
+            const kern::TileArgs t = tile_args(s);
+            HIP_TRY(kern::launch_tile(s.x_swap ? B : A, s.x_swap ? tb : ta, s.x_swap ? A : B, s.x_swap ? ta : tb, C, tc,
+                                      D.d_tab, t, t.ksplit > 1 ? ws + s.ws_kpart : nullptr, st));
             continue;
         }
         if (s.mfma) {
@@ -1218,7 +1241,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
     int gk = Q.gk;
     for (int k : P.kernel_steps) {
         const StepPlan &s = P.steps[k];
-        if (!s.mfma) continue;
+        if (!s.mfma || s.x_tile) continue;
         const int g = kern::queue_gemm_kind(tp, result_type(s));
         if (g < 0 || (gk != 0 && g != gk)) return false;
         gk = g;
@@ -1279,7 +1302,39 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
         int64_t coff = -1;
         if (!s.final_step) coff = voff[s.c] = Q.take(P.values[s.c].size * es);
         const int out_flags = s.final_step ? (kern::QF_OUT | kern::QF_LAST) : 0;
-        if (s.mfma) {
+        // the sum of the split-K partial products that item g writes
+        auto add_ksum = [&](int g, int64_t part_off, int ks, int64_t total) {
+            kern::QItem ksum = q_item(kern::QI_KSUM, bi, n);
+            ksum.tc = tc;
+            ksum.ksplit = ks;
+            ksum.total = total;
+            ksum.dep0 = g;
+            ksum.flags = out_flags;
+            ksum.n_units = (total + 255) / 256;
+            ksum.units_per_task = (int32_t)q_units_per_task(Q, ksum.n_units, 256 * (int64_t)ks);
+            return Q.add(ksum, {part_off, -1, coff, -1});
+        };
+        if (s.x_tile) {
+            kern::QItem it = q_item(kern::QI_TILE, bi, n);
+            std::array<int64_t, 4> o{-1, -1, -1, -1};
+            set_ab(it, o, s.x_swap ? B : A, s.x_swap ? A : B);
+            it.ta = (s.x_swap ? B : A).t;
+            it.tb = (s.x_swap ? A : B).t;
+            it.tc = tc;
+            it.t = tile_args(s);
+            it.n_units = ((int64_t)it.t.tiles_m * it.t.tiles_n * it.t.ksplit + 3) / 4;
+            // (a wave tile reads 4 x 16 values of either operand per K row)
+            it.units_per_task = (int32_t)q_units_per_task(Q, it.n_units, 256 * std::min<int64_t>(it.t.kper, it.t.K));
+            if (it.t.ksplit > 1) {
+                const int64_t part_off = o[2] = Q.take(it.t.ksplit * it.t.total * es);
+                const int g = Q.add(it, o);
+                last = add_ksum(g, part_off, it.t.ksplit, it.t.total);
+            } else {
+                it.flags = out_flags;
+                o[2] = coff;
+                last = Q.add(it, o);
+            }
+        } else if (s.mfma) {
             auto pack = [&](const Opd &x, const StepPlan::Pack &pk) {
                 if (pk.identity && x.t == tp) return x;
                 kern::QItem it = q_item(kern::QI_STEP, bi, n);
@@ -1323,15 +1378,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
                 o[2] = Q.take(ks * total * (tc == 0 ? 8 : 4));
                 const int64_t part_off = o[2];
                 const int g = Q.add(it, o);
-                kern::QItem ksum = q_item(kern::QI_KSUM, bi, n);
-                ksum.tc = tc;
-                ksum.ksplit = ks;
-                ksum.total = total;
-                ksum.dep0 = g;
-                ksum.flags = out_flags;
-                ksum.n_units = (total + 255) / 256;
-                ksum.units_per_task = (int32_t)q_units_per_task(Q, ksum.n_units, 256 * (int64_t)ks);
-                last = Q.add(ksum, {part_off, -1, coff, -1});
+                last = add_ksum(g, part_off, ks, total);
             } else {
                 it.flags = out_flags;
                 o[2] = coff;

@@ -72,6 +72,12 @@ struct StepPlan {
     // stride; floor(x / d) = (x * magic) >> 40.
     std::vector<int32_t> c_digits_m, c_digits_n;
     int TM = 1, TN = 1, GX = 16;  // per-thread tile and thread-grid width
+    // Per-step executor, work queue and level launches: the step runs on the
+    // matrix cores in its tiled form (x_tile), K split into x_split ranges of
+    // x_kper, wave tiles of shape x_shape (kernels.hpp, TileArgs); the partial
+    // products at ws_kpart.  x_swap: A and B change places, so that C's
+    // fastest label runs along a wave's lanes.
+    int x_tile = 0, x_split = 1, x_kper = 0, x_shape = 0, x_swap = 0;
     // Fused kernel: the waves [f_w0, f_w0 + f_nw) of the workgroup run the
     // step; steps of one phase are independent and run side by side.
     int f_w0 = 0, f_nw = 1;

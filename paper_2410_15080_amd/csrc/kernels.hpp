@@ -34,6 +34,21 @@ struct StepArgs {
 hipError_t launch_step(const void *A, int ta, const void *B, int tb, void *C, int tc, bool acc_f64, bool comp,
                        const int2 *tab, const StepArgs &s, hipStream_t st);
 
+// Tiled step on the matrix cores (tile_dev.hpp): C(m, n) = sum_k A[k][m]
+// B[k][n]; C's offset of (m, n) is tab[t_cm + m].x + tab[t_cn + n].x.  K range
+// kz (of length kper) goes to part + kz * total; the ranges are then summed in
+// order into C.  shape: wave tiles of 32 x 32 (0), 64 x 16 (1), 16 x 64 (2).
+// Type codes as above; FP64 throughout, or FP32 accumulation of FP32 or BF16
+// operands into FP32 or (unsplit) BF16 results.
+struct TileArgs {
+    int32_t M, N, K, t_cm, t_cn, ksplit, kper, shape, tiles_m, tiles_n;
+    int64_t total;  // elements of C
+};
+hipError_t launch_tile(const void *A, int ta, const void *B, int tb, void *C, int tc, const int2 *tab,
+                       const TileArgs &t, void *part, hipStream_t st);
+// C[i] = sum over kz of part[kz * total + i], in order (tout 0: FP64, 1: FP32).
+hipError_t launch_ksum(const void *part, void *C, int tout, int64_t total, int ksplit, hipStream_t st);
+
 // Scaled-input materialisation (one launch for all inputs of a net).
 constexpr int kMaxScalesDev = 16;
 struct PrepDesc {
@@ -199,11 +214,12 @@ hipError_t launch_qt_assemble(const int64_t *start, const int64_t *term_out, con
 // Persistent work queue (queue.hip).  Items are the units of a network's
 // per-step plan: an input materialisation (LOAD), a table-driven step or an
 // operand pack (STEP; with split sums its partials), the second pass of a
-// split sum (FINISH), a matrix-core product (GEMM) and the sum of its split-K
-// partial products (KSUM).  An item is cut into tasks of units_per_task
+// split sum (FINISH), a matrix-core product of packed operands (GEMM) or a
+// tiled step (TILE), and the sum of their split-K partial products (KSUM).  An item is cut into tasks of units_per_task
 // units (LOAD and KSUM: 256 elements; STEP: one 256-thread block of the
-// per-step kernel's grid; FINISH: 4 outputs; GEMM: one output tile).
-enum QItemKind { QI_LOAD = 0, QI_STEP = 1, QI_FINISH = 2, QI_GEMM = 3, QI_KSUM = 4 };
+// per-step kernel's grid; FINISH: 4 outputs; GEMM: one output tile; TILE:
+// four wave tiles).
+enum QItemKind { QI_LOAD = 0, QI_STEP = 1, QI_FINISH = 2, QI_GEMM = 3, QI_KSUM = 4, QI_TILE = 5 };
 enum QItemFlags { QF_FIRST = 1, QF_LAST = 2, QF_OUT = 4 };
 struct QItem {
     int32_t kind;
@@ -223,6 +239,7 @@ struct QItem {
     StepArgs s;             // STEP and FINISH geometry
     int32_t M, N, K, batch, kchunk, ksplit, kper, tiles_m, tiles_n;  // GEMM; KSUM: ksplit
     int64_t total;          // KSUM: elements of one partial product
+    TileArgs t;             // TILE
 };
 struct QTask {
     int32_t item, task;

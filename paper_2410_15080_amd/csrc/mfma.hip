@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "mfma_dev.hpp"
@@ -185,6 +186,19 @@ __global__ __launch_bounds__(256) void k_ksum(const TOUT *__restrict__ part, TOU
     }
 }
 
+hipError_t launch_ksum(const void *part, void *C, int tout, int64_t total, int ksplit, hipStream_t st) {
+    const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
+    if (tout == 0)
+        hipLaunchKernelGGL((k_ksum<double>), dim3(blocks), dim3(256), 0, st, (const double *)part, (double *)C, total,
+                           ksplit);
+    else if (tout == 1)
+        hipLaunchKernelGGL((k_ksum<float>), dim3(blocks), dim3(256), 0, st, (const float *)part, (float *)C, total,
+                           ksplit);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 static int compute_units() {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -210,12 +224,8 @@ static hipError_t go_gemm(const void *A, const void *B, void *C, int M, int N, i
     TOUT *dst = ksplit > 1 ? (TOUT *)part : (TOUT *)C;
     hipLaunchKernelGGL((k_gemm<T, TOUT, C64, WI>), dim3(grid), dim3(256), 0, st, (const T *)A, (const T *)B, dst, M,
                        N, K, sA, sB, sC, kchunk, ksplit, kper, batch, tiles_m, tiles_n, (int)n_tiles);
-    if (ksplit > 1) {
-        const int64_t total = (int64_t)batch * sC;
-        const int64_t blocks = std::min<int64_t>((total + 255) / 256, 65536);
-        hipLaunchKernelGGL((k_ksum<TOUT>), dim3((unsigned)blocks), dim3(256), 0, st, (const TOUT *)part, (TOUT *)C,
-                           total, ksplit);
-    }
+    if (ksplit > 1)
+        return launch_ksum(part, C, std::is_same<TOUT, double>::value ? 0 : 1, (int64_t)batch * sC, ksplit, st);
     return hipGetLastError();
 }
 

@@ -493,6 +493,45 @@ static void classify_mfma(const Net &n, StepPlan &s, const std::vector<int> &al,
     s.sum_labels = gk;
 }
 
+// Tiled steps that the executors other than the fused kernel run on the
+// matrix cores (tile_dev.hpp), from the operands as the layout pass leaves
+// them.  Even a side padded from 4 to 16 rows costs less than the
+// table-driven step's loads per product; below that, or with fewer than four
+// summed terms, the result's stores dominate either way.  (The random batch's
+// 4 x 9216 x 24 and 6 x 5184 x 4 steps are of that kind; with them on the
+// table-driven kernel its first two levels took 679 us, without 166.)  It also
+// takes FP32 and FP64 products that would be packed for the packed-operand
+// kernel: the operands are in tiled order already.  A BF16 product
+// stays with the packed BF16 instructions, sixteen times the FP32 rate.
+static void plan_tile_step(const Net &n, StepPlan &s) {
+    s.x_tile = 0;
+    const bool acc_is_compute = !s.final_step || n.compute == HTN_F64 || n.final_sum == HTN_SUM_PLAIN;
+    if (!s.tile || !n.allow_mfma || !acc_is_compute || (s.mfma && n.compute == HTN_BF16)) return;
+    constexpr int64_t lim = int64_t(1) << 24;  // 32-bit offsets within a K chunk
+    if (s.tM < 4 || s.tN < 4 || s.tK < 4 || s.tM >= lim || s.tN >= lim || s.tK >= lim) return;
+    s.x_tile = 1;
+    // C's fastest label along the lanes (the N side) where M holds it
+    s.x_swap = !s.c_labels.empty() && contains(s.t_gm, s.c_labels.back()) ? 1 : 0;
+    const int64_t M = s.x_swap ? s.tN : s.tM, N = s.x_swap ? s.tM : s.tN;
+    static const int rows[3] = {32, 64, 16}, cols[3] = {32, 16, 64};
+    int64_t best = 0, tiles = 0;
+    for (int k = 0; k < 3; ++k) {
+        const int64_t t = ((M + rows[k] - 1) / rows[k]) * ((N + cols[k] - 1) / cols[k]);
+        if (k == 0 || t < best) {
+            best = t;
+            s.x_shape = k;
+            tiles = t;
+        }
+    }
+    // K ranges (of at least 64) until there are about 1024 wave tiles, one
+    // per SIMD: a range is a serial chain of loads and products
+    int64_t ks = 1;
+    if (tiles < 1024 && s.tK >= 128 && !s.out_bf16) ks = std::min<int64_t>((1023 + tiles) / tiles, s.tK / 64);
+    const int64_t kper = ks > 1 ? ((s.tK + ks - 1) / ks + 15) / 16 * 16 : s.tK;
+    s.x_kper = (int)kper;
+    s.x_split = (int)((s.tK + kper - 1) / kper);
+}
+
 FoldLayout fold_layout(const Net &n, const Plan &P, const std::vector<int> &chain) {
     constexpr int kAx = 8, kOuter = 4, kStages = 8;
     constexpr int64_t kTileMax = 1024, kLdsMax = 81920;
@@ -1288,7 +1327,13 @@ void build_plan(Net &n) {
                 continue;
             }
             if (!s.final_step) P.ws_off[s.c] = ff.alloc(P.values[s.c].size * es, 256);
-            if (s.mfma) {
+            plan_tile_step(n, s);
+            if (s.x_tile) {
+                if (s.x_split > 1) {
+                    s.ws_kpart = ff.alloc(s.x_split * s.tM * s.tN * es, 256);
+                    ff.release(s.ws_kpart);
+                }
+            } else if (s.mfma) {
                 s.ws_pa = s.pack_a.identity ? -1 : ff.alloc(s.pack_a.n * pes, 256);
                 s.ws_pb = s.pack_b.identity ? -1 : ff.alloc(s.pack_b.n * pes, 256);
                 // too few 128x128 output tiles to fill the chip: split K
@@ -1826,7 +1871,7 @@ std::string plan_json(const Net &n) {
           << "],\"pack_id\":[" << (s.pack_a.identity ? 1 : 0) << "," << (s.pack_b.identity ? 1 : 0)
           << "],\"t_cm\":" << s.t_cm << ",\"t_cn\":" << s.t_cn << ",\"mfma\":" << s.mfma << ",\"gemm\":[" << s.gb << "," << s.gm
           << "," << s.gn << "," << s.gk << "],\"tile\":" << s.tile << ",\"tmnk\":[" << s.tM << "," << s.tN << ","
-          << s.tK << "],\"tcfg\":[" << s.TM << "," << s.TN << "," << s.GX << "]}";
+          << s.tK << "],\"xtile\":[" << s.x_tile << "," << s.x_split << "," << s.x_shape << "," << s.x_swap << "],\"tcfg\":[" << s.TM << "," << s.TN << "," << s.GX << "]}";
     }
     o << "],\"values\":[";
     for (size_t v = 0; v < P.values.size(); ++v) {

@@ -34,6 +34,7 @@
 #include "kernels.hpp"
 #include "mfma_dev.hpp"
 #include "step_dev.hpp"
+#include "tile_dev.hpp"
 
 namespace htn {
 namespace kern {
@@ -191,6 +192,11 @@ __device__ __forceinline__ void q_run(const QItem &it, void *C, int64_t u0, int6
             break;
         case QI_GEMM:
             if constexpr (GK != 0) q_gemm<GK>(it, C, u0, u1, lds);
+            break;
+        case QI_TILE:
+            for (int64_t u = u0; u < u1; ++u)
+                tile_wave_any(it.A, it.ta, it.B, it.tb, C, it.tc, it.tab, it.t,
+                              __builtin_amdgcn_readfirstlane((int)u * 4 + (int)(threadIdx.x >> 6)));
             break;
         default:
             if (it.tc == 0)
