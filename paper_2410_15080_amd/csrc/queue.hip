@@ -309,11 +309,15 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK ? 
     const int blk = blockIdx.x, lane = threadIdx.x & 63;
     if (blk == 0)
         for (int i = threadIdx.x; i < n_done; i += kQThreads) stamps[2 * done[i] + 1] = (int64_t)wall_clock64();
-    // the item this block belongs to: the last whose first block is <= blk
-    int i = -1;
-    for (int b = 0; b < n_items; b += 64) {
-        const bool le = b + lane < n_items && first[b + lane] <= blk;
-        i += __popcll(__ballot(le));
+    // the item this block belongs to, the last whose first block is <= blk: a
+    // search among 64 candidates per step (the first one always qualifies)
+    int i = 0;
+    for (int len = n_items; len > 1;) {
+        const int stride = (len + 63) >> 6;
+        const int o = lane * stride;
+        const int c = __popcll(__ballot(o < len && first[i + o] <= blk)) - 1;
+        i += c * stride;
+        len = min(stride, len - c * stride);
     }
     i = __builtin_amdgcn_readfirstlane(i);
     const QItem &it = items[i];
