@@ -493,6 +493,34 @@ static void classify_mfma(const Net &n, StepPlan &s, const std::vector<int> &al,
     s.sum_labels = gk;
 }
 
+// Matrix-core mode of a tiled step in the fused kernel: 16 x 16 blocks, one
+// wave each.  A side below 16 wastes part of its blocks, which a step of
+// 32 768 products or more makes up for (144 x 4 x 96 in FP64 on operands
+// outside LDS: 43 000 cycles as register tiles), a smaller one may not: with
+// all steps down to sides of 4 in blocks the batch of 1024 grid networks took
+// 137 us, with this bound 133, with sides of 16 only 132, where the batch of
+// 256 64-vertex rings takes 1 396, 1 406 and 1 514 us.
+static bool fused_mfma(const Net &n, const StepPlan &s, int64_t M, int64_t N, int64_t K) {
+    // (the accumulator is the compute type: no FP64 final sum over FP32 data)
+    const bool acc_is_compute = !s.final_step || n.compute == HTN_F64 || n.final_sum == HTN_SUM_PLAIN;
+    if (!n.allow_mfma || !acc_is_compute || M < 4 || N < 4 || K < 4) return false;
+    return (M >= 16 && N >= 16) || M * N * K >= 32768;
+}
+
+// A step with fewer outputs than its waves have lanes goes to the matrix cores
+// too where its blocks' serial sums (some 44 cycles a summed term with the
+// operands outside LDS) cost less than the table-driven step's, whose lanes
+// share an output's sum (some 100 to 300 cycles a term, each with two table
+// entries and two scattered operands): 384 outputs of 96 terms 31 000 cycles
+// table-driven.
+static bool few_outputs_tiled(const Net &n, const StepPlan &s, int64_t M, int64_t N, int64_t K) {
+    if (!fused_mfma(n, s, M, N, K)) return false;
+    const int64_t blocks = ((M + 15) / 16) * ((N + 15) / 16), rounds = (blocks + s.f_nw - 1) / s.f_nw;
+    int64_t R = 1;
+    while (2 * R * M * N <= 64 * s.f_nw) R *= 2;
+    return rounds * K * 44 < 2000 + 100 * ((K + R - 1) / R);
+}
+
 // Tiled steps that the executors other than the fused kernel run on the
 // matrix cores (tile_dev.hpp), from the operands as the layout pass leaves
 // them.  Even a side padded from 4 to 16 rows costs less than the
@@ -1005,7 +1033,8 @@ void build_plan(Net &n) {
         if (!ok) continue;
         if (M.size() > 8 || Nn.size() > 8) continue;  // digit descriptors hold up to 8 labels
         const int64_t mM = (int64_t)prod_dims(n, M), nN = (int64_t)prod_dims(n, Nn);
-        if (mM * nN < 64 * s.f_nw) continue;  // fewer outputs than threads: split the sums instead
+        // (fewer outputs than threads: the sums are split instead)
+        if (mM * nN < 64 * s.f_nw && !few_outputs_tiled(n, s, mM, nN, (int64_t)prod_dims(n, s.sum_labels))) continue;
         K = s.sum_labels;
         std::sort(K.begin(), K.end());
         std::sort(M.begin(), M.end());
@@ -1083,12 +1112,7 @@ void build_plan(Net &n) {
             digits(s.t_gm, cm, s.c_digits_m);
             digits(s.t_gn, cn, s.c_digits_n);
             choose_tile(s, 64 * s.f_nw);
-            // matrix-core mode (TM = 0): 16x16 blocks, one wave each, when
-            // the blocks are mostly filled and the accumulator is the
-            // compute type (not an FP64 final sum over FP32 data)
-            const bool acc_is_compute =
-                !s.final_step || n.compute == HTN_F64 || n.final_sum == HTN_SUM_PLAIN;
-            if (n.allow_mfma && acc_is_compute && s.tM >= 16 && s.tN >= 16 && s.tK >= 4) {
+            if (fused_mfma(n, s, s.tM, s.tN, s.tK)) {  // matrix-core mode: TM = 0
                 s.TM = 0;
                 s.TN = 0;
             }
