@@ -432,135 +432,157 @@ struct FMfma<float> {
 // arrive at the rate of the L1 cache (64 bytes a clock, which single blocks
 // use up) instead of one round trip per 16.  A 144 x 144 x 216 step with both
 // operands outside took 262 000 cycles with single blocks and no read ahead.
+// The products of block (bm, bn) over K summed terms from A and B on, in two
+// accumulators (to be added); mok and nok tell a lane's valid rows and columns.
+template <int BM, int BN, typename T, typename P>
+__device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const int K, const int bm, const int bn,
+                                       const int lane, typename FMfma<T>::acc (&acc0)[BM][BN],
+                                       typename FMfma<T>::acc (&acc1)[BM][BN]) {
+    typedef FMfma<T> Op;
+    const int li = lane & 15, lk = lane >> 4;
+            int am[BM], bx[BN];  // operand columns (0 outside the matrix, whose products are dropped below)
+            bool mok[BM], nok[BN];
+    #pragma unroll
+            for (int i = 0; i < BM; ++i) {
+                const int m = (bm * BM + i) * 16 + li;
+                mok[i] = m < M;
+                am[i] = mok[i] ? m : 0;
+            }
+    #pragma unroll
+            for (int j = 0; j < BN; ++j) {
+                const int n = (bn * BN + j) * 16 + li;
+                nok[j] = n < N;
+                bx[j] = nok[j] ? n : 0;
+            }
+    #pragma unroll
+            for (int i = 0; i < BM; ++i)
+    #pragma unroll
+                for (int j = 0; j < BN; ++j) acc0[i][j] = acc1[i][j] = typename Op::acc{0, 0, 0, 0};
+            auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok, typename Op::acc (&acc)[BM][BN]) {
+                T a[BM], b[BN];
+    #pragma unroll
+                for (int i = 0; i < BM; ++i) a[i] = mok[i] && ok ? av[i] : T(0);
+    #pragma unroll
+                for (int j = 0; j < BN; ++j) b[j] = nok[j] && ok ? bv[j] : T(0);
+    #pragma unroll
+                for (int i = 0; i < BM; ++i)
+    #pragma unroll
+                    for (int j = 0; j < BN; ++j) acc[i][j] = Op::mma(a[i], b[j], acc[i][j]);
+            };
+            T av[4][BM], bv[4][BN];
+            int ao = lk * M, bo = lk * N;
+            auto load = [&](int u, int so, int to) {
+    #pragma unroll
+                for (int i = 0; i < BM; ++i) av[u][i] = A[so + am[i]];
+    #pragma unroll
+                for (int j = 0; j < BN; ++j) bv[u][j] = B[to + bx[j]];
+            };
+            int k = K;
+            if (k >= 16) {
+    #pragma unroll
+                for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
+                for (;;) {
+                    T ac[4][BM], bc[4][BN];
+    #pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+    #pragma unroll
+                        for (int i = 0; i < BM; ++i) ac[u][i] = av[u][i];
+    #pragma unroll
+                        for (int j = 0; j < BN; ++j) bc[u][j] = bv[u][j];
+                    }
+                    k -= 16;
+                    ao += 16 * M;
+                    bo += 16 * N;
+                    if (k >= 16) {
+    #pragma unroll
+                        for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+    #pragma unroll
+                    for (int u = 0; u < 4; u += 2) {
+                        mma_all(ac[u], bc[u], true, acc0);
+                        mma_all(ac[u + 1], bc[u + 1], true, acc1);
+                    }
+                    if (k < 16) break;
+                }
+            }
+            // the last k < 16: a pair of slices, then up to two into acc0
+            const bool pair = k >= 8;
+            const int rest = k & 7;
+            if (pair) {
+                load(0, ao, bo);
+                load(1, ao + 4 * M, bo + 4 * N);
+                ao += 8 * M;
+                bo += 8 * N;
+            }
+            const bool ok0 = lk < rest, ok1 = lk + 4 < rest;
+            if (rest > 0) load(2, ok0 ? ao : 0, ok0 ? bo : 0);
+            if (rest > 4) load(3, ok1 ? ao + 4 * M : 0, ok1 ? bo + 4 * N : 0);
+            if (pair) {
+                mma_all(av[0], bv[0], true, acc0);
+                mma_all(av[1], bv[1], true, acc1);
+            }
+            if (rest > 0) mma_all(av[2], bv[2], ok0, acc0);
+            if (rest > 4) mma_all(av[3], bv[3], ok1, acc0);
+}
+
+// Block (bm, bn)'s results acc0 + acc1 into C.
+template <int BM, int BN, typename T, typename TOUT>
+__device__ __forceinline__ void mstore(const Dest<TOUT> &C, const StepWords &p, const int bm, const int bn,
+                                       const int lane, const typename FMfma<T>::acc (&acc0)[BM][BN],
+                                       const typename FMfma<T>::acc (&acc1)[BM][BN]) {
+    typedef FMfma<T> Op;
+    const int M = p(4), N = p(5), nm = p(11), nn_l = p(12), li = lane & 15;
+    const bool narrow = narrow_digits(M, N);
+    bool nok[BN];
+#pragma unroll
+    for (int j = 0; j < BN; ++j) nok[j] = (bn * BN + j) * 16 + li < N;
+            uint32_t xn[BN];
+            int cn[BN];
+    #pragma unroll
+            for (int j = 0; j < BN; ++j) xn[j] = (uint32_t)((bn * BN + j) * 16 + li);
+            digit_offsets<BN>(p, 4 * nm, nn_l, narrow, xn, cn);
+    #pragma unroll
+            for (int i = 0; i < BM; ++i) {
+                const int m0 = (bm * BM + i) * 16;
+                uint32_t xm[4];
+                int cm[4];
+    #pragma unroll
+                for (int r = 0; r < 4; ++r) xm[r] = (uint32_t)(m0 + Op::row(lane, r));
+                digit_offsets<4>(p, 0, nm, narrow, xm, cm);
+                if (C.in_lds) {
+    #pragma unroll
+                    for (int j = 0; j < BN; ++j)
+    #pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (nok[j] && m0 + Op::row(lane, r) < M)
+                                C.l[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
+                } else {
+    #pragma unroll
+                    for (int j = 0; j < BN; ++j)
+    #pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (nok[j] && m0 + Op::row(lane, r) < M)
+                                C.g[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
+                }
+            }
+}
+
 template <int BM, int BN, typename T, typename TOUT, typename P>
 __device__ __forceinline__ void mstep(P A, P B, const Dest<TOUT> &C, const StepWords &p, const int tid, const int nthr) {
-    typedef FMfma<T> Op;
-    const int M = p(4), N = p(5), K = p(6), nm = p(11), nn_l = p(12);
+    const int M = p(4), N = p(5), K = p(6);
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, lk = lane >> 4;
     const int nbm = (M + 16 * BM - 1) / (16 * BM), nbn = (N + 16 * BN - 1) / (16 * BN);
     const int nw = nthr >> 6;
-    const bool narrow = narrow_digits(M, N);
     int bm = 0, bn = wave;  // block bm * nbn + bn, advanced without divisions
     while (bn >= nbn) {
         bn -= nbn;
         ++bm;
     }
     while (bm < nbm) {
-        int am[BM], bx[BN];  // operand columns (0 outside the matrix, whose products are dropped below)
-        bool mok[BM], nok[BN];
-#pragma unroll
-        for (int i = 0; i < BM; ++i) {
-            const int m = (bm * BM + i) * 16 + li;
-            mok[i] = m < M;
-            am[i] = mok[i] ? m : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < BN; ++j) {
-            const int n = (bn * BN + j) * 16 + li;
-            nok[j] = n < N;
-            bx[j] = nok[j] ? n : 0;
-        }
-        typename Op::acc acc0[BM][BN], acc1[BM][BN];
-#pragma unroll
-        for (int i = 0; i < BM; ++i)
-#pragma unroll
-            for (int j = 0; j < BN; ++j) acc0[i][j] = acc1[i][j] = typename Op::acc{0, 0, 0, 0};
-        auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok, typename Op::acc (&acc)[BM][BN]) {
-            T a[BM], b[BN];
-#pragma unroll
-            for (int i = 0; i < BM; ++i) a[i] = mok[i] && ok ? av[i] : T(0);
-#pragma unroll
-            for (int j = 0; j < BN; ++j) b[j] = nok[j] && ok ? bv[j] : T(0);
-#pragma unroll
-            for (int i = 0; i < BM; ++i)
-#pragma unroll
-                for (int j = 0; j < BN; ++j) acc[i][j] = Op::mma(a[i], b[j], acc[i][j]);
-        };
-        T av[4][BM], bv[4][BN];
-        int ao = lk * M, bo = lk * N;
-        auto load = [&](int u, int so, int to) {
-#pragma unroll
-            for (int i = 0; i < BM; ++i) av[u][i] = A[so + am[i]];
-#pragma unroll
-            for (int j = 0; j < BN; ++j) bv[u][j] = B[to + bx[j]];
-        };
-        int k = K;
-        if (k >= 16) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
-            for (;;) {
-                T ac[4][BM], bc[4][BN];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                    for (int i = 0; i < BM; ++i) ac[u][i] = av[u][i];
-#pragma unroll
-                    for (int j = 0; j < BN; ++j) bc[u][j] = bv[u][j];
-                }
-                k -= 16;
-                ao += 16 * M;
-                bo += 16 * N;
-                if (k >= 16) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < 4; u += 2) {
-                    mma_all(ac[u], bc[u], true, acc0);
-                    mma_all(ac[u + 1], bc[u + 1], true, acc1);
-                }
-                if (k < 16) break;
-            }
-        }
-        // the last k < 16: a pair of slices, then up to two into acc0
-        const bool pair = k >= 8;
-        const int rest = k & 7;
-        if (pair) {
-            load(0, ao, bo);
-            load(1, ao + 4 * M, bo + 4 * N);
-            ao += 8 * M;
-            bo += 8 * N;
-        }
-        const bool ok0 = lk < rest, ok1 = lk + 4 < rest;
-        if (rest > 0) load(2, ok0 ? ao : 0, ok0 ? bo : 0);
-        if (rest > 4) load(3, ok1 ? ao + 4 * M : 0, ok1 ? bo + 4 * N : 0);
-        if (pair) {
-            mma_all(av[0], bv[0], true, acc0);
-            mma_all(av[1], bv[1], true, acc1);
-        }
-        if (rest > 0) mma_all(av[2], bv[2], ok0, acc0);
-        if (rest > 4) mma_all(av[3], bv[3], ok1, acc0);
-        uint32_t xn[BN];
-        int cn[BN];
-#pragma unroll
-        for (int j = 0; j < BN; ++j) xn[j] = (uint32_t)((bn * BN + j) * 16 + li);
-        digit_offsets<BN>(p, 4 * nm, nn_l, narrow, xn, cn);
-#pragma unroll
-        for (int i = 0; i < BM; ++i) {
-            const int m0 = (bm * BM + i) * 16;
-            uint32_t xm[4];
-            int cm[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) xm[r] = (uint32_t)(m0 + Op::row(lane, r));
-            digit_offsets<4>(p, 0, nm, narrow, xm, cm);
-            if (C.in_lds) {
-#pragma unroll
-                for (int j = 0; j < BN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (nok[j] && m0 + Op::row(lane, r) < M)
-                            C.l[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < BN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (nok[j] && m0 + Op::row(lane, r) < M)
-                            C.g[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
-            }
-        }
+        typename FMfma<T>::acc acc0[BM][BN], acc1[BM][BN];
+        mblock<BM, BN, T>(A, B, M, N, K, bm, bn, lane, acc0, acc1);
+        mstore<BM, BN, T>(C, p, bm, bn, lane, acc0, acc1);
         bn += nw;
         while (bn >= nbn) {
             bn -= nbn;
@@ -569,8 +591,53 @@ __device__ __forceinline__ void mstep(P A, P B, const Dest<TOUT> &C, const StepW
     }
 }
 
+// A step of few blocks and a long sum that has all of the workgroup's waves
+// (planned only alone in its phase): p(8) ranges of K, each block of a range a
+// wave; the first range's waves add the others' results, in order, from LDS
+// (element p(9) on, 256 values a block).  One wave per block took 24 outputs
+// of 3456 terms, operands outside LDS, 150 000 cycles, and lanes that share an
+// output's sum 162 000.
+template <typename T, typename TOUT, typename P>
+__device__ __forceinline__ void msplit(P A, P B, const Dest<TOUT> &C, const StepWords &p, T *sm, const int tid) {
+    const int M = p(4), N = p(5), K = p(6), parts = p(8);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nbm = (M + 15) >> 4, nbn = (N + 15) >> 4, nb = nbm * nbn;
+    int part = 0, blk = wave;
+    while (blk >= nb) {
+        blk -= nb;
+        ++part;
+    }
+    int bm = 0, bn = blk;
+    while (bn >= nbn) {
+        bn -= nbn;
+        ++bm;
+    }
+    const int kper = ((K + parts - 1) / parts + 3) & ~3;
+    const int k0 = part * kper, kn = part < parts ? min(K - k0, kper) : 0;
+    LdsPtr<T> red = (LdsPtr<T>)(sm + p(9));
+    typename FMfma<T>::acc acc0[1][1], acc1[1][1];
+    if (part < parts) {
+        if (kn > 0)
+            mblock<1, 1, T>(A + k0 * M, B + k0 * N, M, N, kn, bm, bn, lane, acc0, acc1);
+        else
+            acc0[0][0] = acc1[0][0] = typename FMfma<T>::acc{0, 0, 0, 0};
+        if (part > 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[((part - 1) * nb + blk) * 256 + 64 * r + lane] = acc0[0][0][r] + acc1[0][0][r];
+        }
+    }
+    __syncthreads();
+    if (part == 0) {
+        for (int q = 1; q < parts; ++q) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc1[0][0][r] += red[((q - 1) * nb + blk) * 256 + 64 * r + lane];
+        }
+        mstore<1, 1, T>(C, p, bm, bn, lane, acc0, acc1);
+    }
+}
+
 template <typename T, typename ACC, typename TOUT, typename P>
-__device__ __forceinline__ void tstep_sel(P A, P B, const Dest<TOUT> &C, const StepWords &p,
+__device__ __forceinline__ void tstep_sel(P A, P B, const Dest<TOUT> &C, const StepWords &p, T *sm,
                                           const int tid, const int nthr) {
     const int TM = p(7), TN = p(8);
     if constexpr (std::is_same<T, ACC>::value) {
@@ -580,6 +647,10 @@ __device__ __forceinline__ void tstep_sel(P A, P B, const Dest<TOUT> &C, const S
                 mstep<2, 2, T>(A, B, C, p, tid, nthr);
             else
                 mstep<1, 1, T>(A, B, C, p, tid, nthr);
+            return;
+        }
+        if (TM < 0) {
+            msplit<T>(A, B, C, p, sm, tid);
             return;
         }
     }
@@ -599,7 +670,8 @@ __device__ __forceinline__ void tstep_sel(P A, P B, const Dest<TOUT> &C, const S
 // One step on its waves (threads tid of nthr).
 //   OP_TSTEP: [a, b, c, M, N, K, TM, TN, GX, final, nm, nn, w0, nw, digits of M, digits of N]
 //             (TM = 0: matrix-core mode, planned only where the accumulator is
-//             the compute type)
+//             the compute type; TM = -1: the same with K split into TN ranges,
+//             GX the LDS element offset of their sums)
 //   OP_STEP:  [a, b, c, n_ohi, n_olo, n_shi, n_slo, t_ohi, t_olo, t_shi, t_slo, R, final, slot, w0, nw]
 // Operands in LDS take a body of their own (LDS reads, not flat ones).
 template <int BLK, typename T, int FM>
@@ -622,7 +694,7 @@ __device__ __forceinline__ void run_step(const StepWords &p, T *sm, T *scr, void
     auto go = [&](auto A, auto B) {
         if (FM == FM_INTER || !fin) {
             if (tiled)
-                tstep_sel<T, T>(A, B, C, p, tid, nthr);
+                tstep_sel<T, T>(A, B, C, p, sm, tid, nthr);
             else if (unary)
                 fstep<BLK, T, false, true>(A, B, C, tab, p, (T *)red, tid, nthr);
             else
@@ -630,7 +702,7 @@ __device__ __forceinline__ void run_step(const StepWords &p, T *sm, T *scr, void
         } else {
             const Dest<TO> O = {false, nullptr, (GlobalPtr<TO>)out};
             if (tiled)
-                tstep_sel<T, TO>(A, B, O, p, tid, nthr);
+                tstep_sel<T, TO>(A, B, O, p, sm, tid, nthr);
             else if (unary)
                 fstep<BLK, TO, CMP, true>(A, B, O, tab, p, (TO *)red, tid, nthr);
             else

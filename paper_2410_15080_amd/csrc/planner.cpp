@@ -504,21 +504,31 @@ static bool fused_mfma(const Net &n, const StepPlan &s, int64_t M, int64_t N, in
     // (the accumulator is the compute type: no FP64 final sum over FP32 data)
     const bool acc_is_compute = !s.final_step || n.compute == HTN_F64 || n.final_sum == HTN_SUM_PLAIN;
     if (!n.allow_mfma || !acc_is_compute || M < 4 || N < 4 || K < 4) return false;
-    return (M >= 16 && N >= 16) || M * N * K >= 32768;
+    return (M >= 16 && N >= 16) || M * N * K >= (M * N < 64 * s.f_nw ? 4096 : 32768);
+}
+
+// K ranges of a matrix-core step in the fused kernel: where it has all of the
+// workgroup's waves and leaves half of them or more without a block, and its
+// sum is long enough (128 terms, some 2000 to 6000 cycles) to pay for adding
+// the ranges' results.
+static int64_t fused_k_parts(const Net &n, int64_t blocks, int64_t K, int f_nw) {
+    const int W = std::max(1, n.fused_threads / 64);
+    if (f_nw != W || 2 * blocks > W || K < 128) return 1;
+    return W / blocks;
 }
 
 // A step with fewer outputs than its waves have lanes goes to the matrix cores
 // too where its blocks' serial sums (some 44 cycles a summed term with the
 // operands outside LDS) cost less than the table-driven step's, whose lanes
-// share an output's sum (some 100 to 300 cycles a term, each with two table
-// entries and two scattered operands): 384 outputs of 96 terms 31 000 cycles
-// table-driven.
+// share an output's sum (some 100 cycles a term in LDS, up to 1 200 outside,
+// each with two table entries and two scattered operands): 96 outputs of 384
+// terms 118 000 cycles table-driven.
 static bool few_outputs_tiled(const Net &n, const StepPlan &s, int64_t M, int64_t N, int64_t K) {
     if (!fused_mfma(n, s, M, N, K)) return false;
     const int64_t blocks = ((M + 15) / 16) * ((N + 15) / 16), rounds = (blocks + s.f_nw - 1) / s.f_nw;
     int64_t R = 1;
     while (2 * R * M * N <= 64 * s.f_nw) R *= 2;
-    return rounds * K * 44 < 2000 + 100 * ((K + R - 1) / R);
+    return rounds * K * 44 / fused_k_parts(n, blocks, K, s.f_nw) < 2000 + 100 * ((K + R - 1) / R);
 }
 
 // Tiled steps that the executors other than the fused kernel run on the
@@ -1586,6 +1596,7 @@ void build_plan(Net &n) {
         // keep spill scratch above the inputs area
         glb_ff.used[0] = inputs_end;
         std::vector<int> pending;
+        std::vector<int64_t> phase_scratch;  // LDS of the phase's split sums
         int phase = 0, last_step = -1;
         bool lds_only = true;
         for (auto &r : seq) {
@@ -1613,6 +1624,17 @@ void build_plan(Net &n) {
                 r.w[1] = (int32_t)loc[s.a];
                 r.w[2] = s.b >= 0 ? (int32_t)loc[s.b] : -1;
                 r.w[3] = (int32_t)cl;
+                if (r.kind == OP_TSTEP && s.TM == 0) {
+                    const int64_t blocks = ((s.tM + 15) / 16) * ((s.tN + 15) / 16);
+                    const int64_t parts = fused_k_parts(n, blocks, s.tK, s.f_nw);
+                    const int64_t l = parts > 1 ? place((parts - 1) * blocks * 256) : -1;
+                    if (l >= 0) {
+                        r.w[7] = -1;
+                        r.w[8] = (int32_t)parts;
+                        r.w[9] = (int32_t)l;
+                        phase_scratch.push_back(l);
+                    }
+                }
                 pending.push_back(s.a);
                 pending.push_back(s.b);
                 if (loc[s.a] < 0 || (s.b >= 0 && loc[s.b] < 0) || (!s.final_step && cl < 0)) lds_only = false;
@@ -1625,6 +1647,8 @@ void build_plan(Net &n) {
                 for (int id : pending)
                     if (id >= 0) unplace(loc[id]);
                 pending.clear();
+                for (int64_t l : phase_scratch) unplace(l);
+                phase_scratch.clear();
                 ++phase;
                 last_step = -1;
             }
@@ -1649,7 +1673,8 @@ void build_plan(Net &n) {
                         const StepPlan &s = P.steps[t->step];
                         // (a matrix-core step has no work for waves beyond its
                         // 16x16 blocks)
-                        const int64_t blocks = s.tile && s.TM == 0 ? ((s.tM + 15) / 16) * ((s.tN + 15) / 16) : s.f_nw;
+                        const int64_t blocks = t->kind == OP_TSTEP && t->w[7] == 0 ? ((s.tM + 15) / 16) * ((s.tN + 15) / 16)
+                                                                                   : s.f_nw;
                         for (int w = 0; w < s.f_nw && w < blocks; ++w) entry[2 + s.f_w0 + w] = (int32_t)prog.size();
                         prog.insert(prog.end(), t->w.begin(), t->w.end());
                     }

@@ -108,3 +108,19 @@ def test_index_outside_lds():
         torch.cuda.synchronize()
         vals.append(float(out.item()))
     assert abs(vals[0] - vals[1]) <= 1e-12 * abs(vals[0])
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("threads", [64, 256, 512])
+@pytest.mark.parametrize("lds", [163840, 20480])
+def test_split_products(dtype, threads, lds):
+    """Few blocks and long sums: K in ranges over the workgroup's waves (the
+    last one short or empty), whose results are added in LDS."""
+    rng = np.random.default_rng(threads + lds)
+    for m, n, k in [(4, 6, 3456), (16, 16, 2049), (15, 17, 257), (33, 16, 128), (64, 13, 131), (16, 48, 130),
+                    (5, 7, 1000), (17, 17, 129)]:
+        a = rng.uniform(-1, 1, (k, m)).astype(dtype).astype(np.float64)
+        b = rng.uniform(-1, 1, (k, n)).astype(dtype).astype(np.float64)
+        got = _run([a, b], [[0, 1], [0, 2]], [k, m, n], [1, 2], dtype, threads, lds).reshape(m, n)
+        bound = 2 * (k + 2) * U[dtype] * (np.abs(a).T @ np.abs(b))
+        assert (np.abs(got - a.T @ b) <= bound).all(), (m, n, k)
