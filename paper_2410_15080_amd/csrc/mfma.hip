@@ -38,10 +38,11 @@ namespace kern {
 // and the loads of the next overlap.
 // Each wave owns WI x 4 blocks of 16x16 (the workgroup tile is 32 WI x 128):
 // WI = 4 where the accumulators are the instruction's own; WI = 2 where FP64
-// accumulators are kept beside FP32 ones, so that two waves per SIMD still
-// fit in the register file.
-template <typename T, typename TOUT, bool COMBINE64, int WI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm(const T *__restrict__ A0, const T *__restrict__ B0,
+// accumulators are kept beside FP32 ones (or only the result is FP64).  WPC
+// workgroups per CU by registers and LDS: a tile's stores and another's
+// products then overlap.
+template <typename T, typename TOUT, bool COMBINE64, int WI, int WPC, bool STREAM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPC))) void k_gemm(const T *__restrict__ A0, const T *__restrict__ B0,
                                              TOUT *__restrict__ C0, int M, int N, int K, int64_t sA, int64_t sB,
                                              int64_t sC, int kchunk, int ksplit, int kper, int batch, int tiles_m,
                                              int tiles_n, int n_tiles) {
@@ -150,10 +151,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             lb.load(nxt.B, N, K, nxt.kend, nxt.n0, nxt.kbeg);
         }
         // D block: column lane%16; the row of register r depends on the
-        // instruction (Op::row).  Streaming (nontemporal) stores: the
-        // result is written once and not read back by this launch, and
-        // where the output dominates the traffic (BF16 inputs, FP64 output)
-        // they cut the GEMM's time by a fifth against plain stores.
+        // instruction (Op::row).  STREAM: nontemporal stores (the result is
+        // written once and not read back by this launch), for results whose
+        // rows are whole 128-byte lines: 4096 x 4096 from BF16 60.7 us with
+        // them, 63.4 without (the marginal's two launches).  The rows of a
+        // ragged result share lines, which plain stores complete in the L2
+        // before they are written out: 2999 x 1531 from FP32 29.2 us with
+        // plain stores, 37.8 with streaming ones.
 #pragma unroll
         for (int i = 0; i < WI; ++i)
 #pragma unroll
@@ -168,7 +172,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                             v = (TOUT)acc64[COMBINE64 ? i : 0][j][r];
                         else
                             v = (TOUT)acc[i][j][r];
-                        __builtin_nontemporal_store(v, cur.C + (int64_t)gm * N + gn);
+                        if constexpr (STREAM)
+                            __builtin_nontemporal_store(v, cur.C + (int64_t)gm * N + gn);
+                        else
+                            cur.C[(int64_t)gm * N + gn] = v;
                     }
                 }
         if (t_next >= n_tiles) break;
@@ -207,23 +214,52 @@ static int compute_units() {
     return n;
 }
 
-template <typename T, typename TOUT, bool C64>
-static hipError_t go_gemm(const void *A, const void *B, void *C, int M, int N, int K, int batch, int kchunk,
-                          int ksplit, void *part, hipStream_t st) {
+template <typename T, typename TOUT, bool C64, int WI, int WPC>
+static hipError_t go_tiles(const void *A, const void *B, TOUT *dst, int M, int N, int K, int batch, int kchunk,
+                           int ksplit, int kper, hipStream_t st) {
     const int64_t sA = (int64_t)M * K, sB = (int64_t)N * K, sC = (int64_t)M * N;
-    int kper = 0;
-    gemm_ksplit(K, ksplit, kper);
-    constexpr int WI = C64 ? 2 : 4;
     const int tiles_n = (N + GBN - 1) / GBN, tiles_m = (M + 32 * WI - 1) / (32 * WI);
     const int64_t n_tiles = (int64_t)tiles_n * tiles_m * batch * ksplit;
     if (n_tiles > INT32_MAX) return hipErrorInvalidValue;
-    // two resident workgroups per CU (registers and LDS allow two), each
+    // WPC resident workgroups per CU (registers and LDS allow as many), each
     // walking over its share of the tiles
     static const int cus = compute_units();
-    const int grid = (int)std::min<int64_t>(n_tiles, 2 * (int64_t)cus);
+    const bool stream = (int64_t)N * sizeof(TOUT) % 128 == 0 && (uintptr_t)dst % 128 == 0;
+    const int grid = (int)std::min<int64_t>(n_tiles, WPC * (int64_t)cus);
+    auto go = [&](auto str) {
+        hipLaunchKernelGGL((k_gemm<T, TOUT, C64, WI, WPC, decltype(str)::value>), dim3(grid), dim3(256), 0, st,
+                           (const T *)A, (const T *)B, dst, M, N, K, sA, sB, sC, kchunk, ksplit, kper, batch, tiles_m,
+                           tiles_n, (int)n_tiles);
+    };
+    if (stream)
+        go(std::true_type{});
+    else
+        go(std::false_type{});
+    return hipGetLastError();
+}
+
+template <typename T, typename TOUT, bool C64>
+static hipError_t go_gemm(const void *A, const void *B, void *C, int M, int N, int K, int batch, int kchunk,
+                          int ksplit, void *part, hipStream_t st) {
+    int kper = 0;
+    gemm_ksplit(K, ksplit, kper);
     TOUT *dst = ksplit > 1 ? (TOUT *)part : (TOUT *)C;
-    hipLaunchKernelGGL((k_gemm<T, TOUT, C64, WI>), dim3(grid), dim3(256), 0, st, (const T *)A, (const T *)B, dst, M,
-                       N, K, sA, sB, sC, kchunk, ksplit, kper, batch, tiles_m, tiles_n, (int)n_tiles);
+    hipError_t e;
+    if constexpr (C64) {
+        // a sum that is one chunk needs no FP64 accumulators: it is converted
+        // as it is (the same value).  BF16 inputs take a third workgroup per CU
+        // (4096 x 4096 x 256: 68.5 -> 61 us), FP32 ones are better off with two
+        // and their registers (2999 x 1531 x 64 as chunks: 38.5 us, 40.1 with
+        // three).
+        if (K <= kchunk)
+            e = go_tiles<T, TOUT, false, 2, 3>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+        else
+            e = go_tiles<T, TOUT, true, 2, sizeof(T) == 2 ? 3 : 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+    } else {
+        e = go_tiles<T, TOUT, false, 4, 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+    }
+    if (e != hipSuccess) return e;
+    const int64_t sC = (int64_t)M * N;
     if (ksplit > 1)
         return launch_ksum(part, C, std::is_same<TOUT, double>::value ? 0 : 1, (int64_t)batch * sC, ksplit, st);
     return hipGetLastError();

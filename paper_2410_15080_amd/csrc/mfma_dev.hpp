@@ -60,7 +60,7 @@ struct MfmaOp<bf16_t> {
     typedef f4_t acc;
     static constexpr int KI = 32;
     static constexpr int KPL = 8;
-    static constexpr int BK = 64;
+    static constexpr int BK = 32;  // (half the LDS of 64: room for a third workgroup on a CU)
     static constexpr int PAD = 8;
     __device__ __forceinline__ static int row(int lane, int r) { return 4 * (lane >> 4) + r; }
     __device__ __forceinline__ static acc mma(frag a, frag b, acc c) {

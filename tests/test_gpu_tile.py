@@ -49,3 +49,20 @@ def test_tiled_steps_are_exact(compute):
         htn.htn_batch_destroy(b)
         for i, (got, ref) in enumerate(zip(r[0], refs)):
             assert np.array_equal(got.astype(np.float64).reshape(ref.shape), ref), (mode, i, SHAPES[i // 2])
+
+
+@pytest.mark.parametrize("compute", [htn.HTN_F32, htn.HTN_BF16])
+def test_products_into_fp64_are_exact(compute):
+    """Packed products with an FP64 result: sums of one chunk (up to 64 terms)
+    and of more, rows of whole 128-byte lines and ragged ones."""
+    rng = np.random.default_rng(6)
+    for M, N, K in [(800, 672, 8), (301, 272, 63), (257, 259, 64), (272, 256, 65), (300, 129, 130)]:
+        w, ref = _net(rng, M, N, K, False)
+        n = create(w, compute=compute, final_sum=htn.HTN_SUM_FP64, storage=htn.HTN_F64, exec_mode=htn.HTN_EXEC_STEPS)
+        p = json.loads(htn.htn_plan_json(n))["steps"][-1]
+        assert p["mfma"] and not p["xtile"][0]
+        import torch
+        out = htn.new_output(n)
+        htn.htn_contract(n, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().reshape(M, N), ref), (M, N, K)
