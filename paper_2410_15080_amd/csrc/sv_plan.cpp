@@ -21,9 +21,16 @@ struct Op {
     int need = -1;  // amplitude bit that must be a register bit (-1: none)
     int p0 = 0, p1 = 0;
     double m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int bit = 0;               // PROJ: the value kept
-    std::vector<int> preds;    // ops that must come before
-    bool done = false;
+    int bit = 0;  // PROJ: the value kept
+};
+
+// An op not yet run, as masks of amplitude bits: those that it changes, those
+// that it is diagonal in (or controlled by), those that must be register bits,
+// and those of which one must be (0: none).  Its order is kept against every
+// earlier op that changes one of its bits, or that touches the one it changes.
+struct Left {
+    uint32_t chg = 0, dia = 0, req = 0, any = 0;
+    int op = 0;
 };
 
 // c = a * b, 2x2 complex row-major (re, im)
@@ -43,29 +50,26 @@ void mul2(const double *a, const double *b, double *c) {
 
 struct Scheduler {
     std::vector<Op> ops;
-    std::vector<int> left;   // ops not yet run, program order
-    std::vector<int> mark;   // trial runs: mark[i] == stamp
-    int stamp = 0;
+    std::vector<Left> left;  // program order
+    uint32_t bits = 0;       // bits that any op acts on
 
-    bool ready(int i) const {
-        for (int p : ops[i].preds)
-            if (!ops[p].done && mark[p] != stamp) return false;
-        return true;
-    }
     // Worth of the ops that can run with register (or tile) bits `set`, in
-    // program order within the window; `order`, if given, receives them.
-    // A CZ waits for one of its bits.
-    int trial(uint32_t set, std::vector<int> *order) {
-        ++stamp;
-        int n = 0, seen = 0;
-        for (int i : left) {
-            if (++seen > kWindow) break;
-            const Op &o = ops[i];
-            if (o.need >= 0 && !((set >> o.need) & 1)) continue;
-            if (o.kind == CZ && !((set >> o.p0) & 1) && !((set >> o.p1) & 1)) continue;
-            if (!ready(i)) continue;
-            mark[i] = stamp;
-            n += o.need >= 0 ? 4 : 1;
+    // program order within the window; `order`, if given, receives their
+    // places in `left`.  A CZ waits for one of its bits.  An op that cannot
+    // run holds up the later ones that do not commute with it.
+    int trial(uint32_t set, std::vector<int> *order) const {
+        const int end = std::min((int)left.size(), kWindow);
+        uint32_t held = 0, held_chg = 0;  // bits of ops held up; those that they change
+        int n = 0;
+        for (int i = 0; i < end; ++i) {
+            const Left &o = left[i];
+            if ((o.req & ~set) || (o.any && !(o.any & set)) || (o.chg & held) || (o.dia & held_chg)) {
+                held |= o.chg | o.dia;
+                held_chg |= o.chg;
+                if (held_chg == bits) break;  // nothing commutes with all that is held up
+                continue;
+            }
+            n += o.req ? 4 : 1;
             if (order) order->push_back(i);
         }
         return n;
@@ -87,9 +91,16 @@ struct Scheduler {
         }
         return set;
     }
+    // the ops at these places of `left` have run
     void finish(const std::vector<int> &run) {
-        for (int i : run) ops[i].done = true;
-        left.erase(std::remove_if(left.begin(), left.end(), [&](int i) { return ops[i].done; }), left.end());
+        size_t r = 0, w = 0;
+        for (size_t i = 0; i < left.size(); ++i) {
+            if (r < run.size() && run[r] == (int)i)
+                ++r;
+            else
+                left[w++] = left[i];
+        }
+        left.resize(w);
     }
 };
 
@@ -116,7 +127,7 @@ void emit_group(const Scheduler &S, const std::vector<int> &run, const std::vect
     };
     close();
     for (int i : run) {
-        const Op &o = S.ops[i];
+        const Op &o = S.ops[S.left[i].op];
         if (o.kind == U1) {
             const int k = reg[o.p0], l = u_next[k];
             SvRecord &x = layer(l);
@@ -221,35 +232,16 @@ SvSchedule sv_schedule(int n, const htn_sv_op *in, int n_ops, int tile, int K) {
         push(o);
     }
     for (int q = 0; q < n; ++q) flush(q);
-    // order kept: an op that changes a bit against every other op on it;
-    // diagonal ops (and controls) on a bit commute with each other
-    {
-        std::vector<int> last(nb, -1);
-        std::vector<std::vector<int>> diag(nb);
-        for (int i = 0; i < (int)S.ops.size(); ++i) {
-            Op &o = S.ops[i];
-            auto diagonal = [&](int p) {
-                if (last[p] >= 0) o.preds.push_back(last[p]);
-                diag[p].push_back(i);
-            };
-            auto changing = [&](int p) {
-                if (last[p] >= 0) o.preds.push_back(last[p]);
-                o.preds.insert(o.preds.end(), diag[p].begin(), diag[p].end());
-                diag[p].clear();
-                last[p] = i;
-            };
-            if (o.kind == U1) {
-                changing(o.p0);
-            } else {
-                diagonal(o.p0);
-                if (o.kind == CX)
-                    changing(o.p1);
-                else if (o.kind != PROJ)
-                    diagonal(o.p1);
-            }
-            S.left.push_back(i);
-        }
-        S.mark.assign(S.ops.size(), 0);
+    for (int i = 0; i < (int)S.ops.size(); ++i) {
+        const Op &o = S.ops[i];
+        Left l;
+        l.op = i;
+        if (o.need >= 0) l.req = l.chg = 1u << o.need;
+        if (o.kind != U1) l.dia |= 1u << o.p0;
+        if (o.kind == CZ || o.kind == RZZ) l.dia |= 1u << o.p1;
+        if (o.kind == CZ) l.any = l.dia;
+        S.bits |= l.chg | l.dia;
+        S.left.push_back(l);
     }
     const uint32_t all = nb >= 32 ? ~0u : (1u << nb) - 1;
     // a tile holds the three lowest bits: 128-byte runs of the state
