@@ -132,6 +132,7 @@ struct htn_batch {
         struct Level {
             int item0 = 0, n_items = 0, n_blocks = 0;
             int done0 = 0, n_done = 0;  // networks that the level before completed
+            bool products = false;      // some item is a matrix product
         };
         std::vector<Level> level;  // (then one without items: the last ones' ends)
         kern::QItem *d_items = nullptr;
@@ -1626,6 +1627,7 @@ static bool levels_upload(htn_batch *b, QBuild &Q) {
         first[i] = L.n_blocks;
         L.n_blocks += (int)tasks[k];
         ++L.n_items;
+        L.products = L.products || it.kind == kern::QI_GEMM || it.kind == kern::QI_TILE;
         items[i] = it;
     }
     open_level(ni);
@@ -1644,7 +1646,7 @@ static void run_levels(htn_batch *b, hipStream_t st) {
     for (const auto &L : lv.level) {
         if (L.n_items)
             HIP_TRY(kern::launch_level(lv.d_items + L.item0, lv.d_first + L.item0, L.n_items, L.n_blocks, b->d_outs,
-                                       b->d_stamps, lv.d_done + L.done0, L.n_done, lv.gk, st));
+                                       b->d_stamps, lv.d_done + L.done0, L.n_done, L.products ? lv.gk : -1, st));
         else if (L.n_done)
             HIP_TRY(kern::launch_level_end(b->d_stamps, lv.d_done + L.done0, L.n_done, st));
     }

@@ -280,6 +280,7 @@ hipError_t launch_queue(const QItem *items, const QTask *tasks, const int32_t *q
 // and XCD.  first[i]: the level's first block of item i (blocks in all:
 // n_blocks, one per task).  done: networks that the previous level completed
 // (their end clocks are stamped); launch_level_end stamps those of the last.
+// gk: the GEMM kind (-1: the level has neither GEMM nor TILE items).
 hipError_t launch_level(const QItem *items, const int32_t *first, int n_items, int n_blocks, void *const *outs,
                         int64_t *stamps, const int32_t *done, int n_done, int gk, hipStream_t st);
 hipError_t launch_level_end(int64_t *stamps, const int32_t *done, int n_done, hipStream_t st);

@@ -191,12 +191,14 @@ __device__ __forceinline__ void q_run(const QItem &it, void *C, int64_t u0, int6
             q_finish(it, C, u0, u1);
             break;
         case QI_GEMM:
-            if constexpr (GK != 0) q_gemm<GK>(it, C, u0, u1, lds);
+            if constexpr (GK > 0) q_gemm<GK>(it, C, u0, u1, lds);
             break;
         case QI_TILE:
-            for (int64_t u = u0; u < u1; ++u)
-                tile_wave_any(it.A, it.ta, it.B, it.tb, C, it.tc, it.tab, it.t,
-                              __builtin_amdgcn_readfirstlane((int)u * 4 + (int)(threadIdx.x >> 6)));
+            if constexpr (GK >= 0) {
+                for (int64_t u = u0; u < u1; ++u)
+                    tile_wave_any(it.A, it.ta, it.B, it.tb, C, it.tc, it.tab, it.t,
+                                  __builtin_amdgcn_readfirstlane((int)u * 4 + (int)(threadIdx.x >> 6)));
+            }
             break;
         default:
             if (it.tc == 0)
@@ -300,9 +302,12 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK ? 
 // the stream.  Launched one by one, a network's steps are a chain of small
 // grids (8 to 25 us each, most of it filling and draining the chip); all the
 // networks' steps of one level together fill it.  done: the networks that
-// the previous level completed, whose end clocks are read here.
+// the previous level completed, whose end clocks are read here.  GK = -1: a
+// level without matrix products (its inputs' materialisation above all) takes
+// a kernel without them, whose fewer registers let twice the waves or more
+// wait for memory side by side.
 template <int GK>
-__global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK ? 2 : 1))) void k_level(
+__global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(GK < 0 ? 4 : (GK ? 2 : 1)))) void k_level(
     const QItem *__restrict__ items, const int32_t *__restrict__ first, int n_items, void *const *__restrict__ outs,
     int64_t *__restrict__ stamps, const int32_t *__restrict__ done, int n_done) {
     extern __shared__ __align__(16) unsigned char q_lds[];
@@ -429,6 +434,7 @@ hipError_t launch_level(const QItem *items, const int32_t *first, int n_items, i
     if (n_items < 1 || n_blocks < 1) return hipErrorInvalidValue;
 #define HTN_GO(G) go_level<G>(items, first, n_items, n_blocks, outs, stamps, done, n_done, st)
     switch (gk) {
+        case -1: return HTN_GO(-1);
         case 0: return HTN_GO(0);
         case 1: return HTN_GO(1);
         case 2: return HTN_GO(2);
