@@ -41,12 +41,11 @@ namespace kern {
 // accumulators are kept beside FP32 ones (or only the result is FP64).  WPC
 // workgroups per CU by registers and LDS: a tile's stores and another's
 // products then overlap.
-template <typename T, typename TOUT, bool COMBINE64, int WI, int WPC, bool STREAM>
+template <typename T, typename TOUT, bool COMBINE64, int WI, typename Op, int WPC, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPC))) void k_gemm(const T *__restrict__ A0, const T *__restrict__ B0,
                                              TOUT *__restrict__ C0, int M, int N, int K, int64_t sA, int64_t sB,
                                              int64_t sC, int kchunk, int ksplit, int kper, int batch, int tiles_m,
                                              int tiles_n, int n_tiles) {
-    typedef MfmaOp<T> Op;
     constexpr int BK = Op::BK;
     constexpr int LD = BK + Op::PAD;
     constexpr int TBM = 32 * WI;
@@ -77,8 +76,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPC))) void
         return u;
     };
 
-    TileLoader<T, TBM> la;
-    TileLoader<T, GBN> lb;
+    TileLoader<T, TBM, Op> la;
+    TileLoader<T, GBN, Op> lb;
     int t = blockIdx.x;
     Tile cur = tile_of(t);
     la.load(cur.A, M, K, cur.kend, cur.m0, cur.kbeg);
@@ -206,7 +205,7 @@ hipError_t launch_ksum(const void *part, void *C, int tout, int64_t total, int k
     return hipGetLastError();
 }
 
-static int compute_units() {
+static int count_units() {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         n <= 0)
@@ -214,7 +213,12 @@ static int compute_units() {
     return n;
 }
 
-template <typename T, typename TOUT, bool C64, int WI, int WPC>
+static int compute_units() {
+    static const int n = count_units();
+    return n;
+}
+
+template <typename T, typename TOUT, bool C64, int WI, typename Op, int WPC>
 static hipError_t go_tiles(const void *A, const void *B, TOUT *dst, int M, int N, int K, int batch, int kchunk,
                            int ksplit, int kper, hipStream_t st) {
     const int64_t sA = (int64_t)M * K, sB = (int64_t)N * K, sC = (int64_t)M * N;
@@ -223,11 +227,11 @@ static hipError_t go_tiles(const void *A, const void *B, TOUT *dst, int M, int N
     if (n_tiles > INT32_MAX) return hipErrorInvalidValue;
     // WPC resident workgroups per CU (registers and LDS allow as many), each
     // walking over its share of the tiles
-    static const int cus = compute_units();
+    const int cus = compute_units();
     const bool stream = (int64_t)N * sizeof(TOUT) % 128 == 0 && (uintptr_t)dst % 128 == 0;
     const int grid = (int)std::min<int64_t>(n_tiles, WPC * (int64_t)cus);
     auto go = [&](auto str) {
-        hipLaunchKernelGGL((k_gemm<T, TOUT, C64, WI, WPC, decltype(str)::value>), dim3(grid), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_gemm<T, TOUT, C64, WI, Op, WPC, decltype(str)::value>), dim3(grid), dim3(256), 0, st,
                            (const T *)A, (const T *)B, dst, M, N, K, sA, sB, sC, kchunk, ksplit, kper, batch, tiles_m,
                            tiles_n, (int)n_tiles);
     };
@@ -247,16 +251,29 @@ static hipError_t go_gemm(const void *A, const void *B, void *C, int M, int N, i
     hipError_t e;
     if constexpr (C64) {
         // a sum that is one chunk needs no FP64 accumulators: it is converted
-        // as it is (the same value).  BF16 inputs take a third workgroup per CU
-        // (4096 x 4096 x 256: 68.5 -> 61 us), FP32 ones are better off with two
-        // and their registers (2999 x 1531 x 64 as chunks: 38.5 us, 40.1 with
-        // three).
-        if (K <= kchunk)
-            e = go_tiles<T, TOUT, false, 2, 3>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
-        else
-            e = go_tiles<T, TOUT, true, 2, sizeof(T) == 2 ? 3 : 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+        // as it is (the same value)
+        const bool one = K <= kchunk;
+        if constexpr (sizeof(T) == 2) {
+            // BF16 with more tiles than two workgroups a CU: half the K slice
+            // makes room for a third (4096 x 4096 x 256: 68.5 -> 61 us); with
+            // fewer, longer slices mean fewer round trips (1732 x 104 x 256:
+            // 32 us, 42 with half slices)
+            const int64_t tiles = (int64_t)((N + GBN - 1) / GBN) * ((M + 63) / 64) * batch * ksplit;
+            if (tiles > 2 * (int64_t)compute_units())
+                e = one ? go_tiles<T, TOUT, false, 2, MfmaOpBf16Half, 3>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st)
+                        : go_tiles<T, TOUT, true, 2, MfmaOpBf16Half, 3>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+            else
+                e = one ? go_tiles<T, TOUT, false, 2, MfmaOp<T>, 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st)
+                        : go_tiles<T, TOUT, true, 2, MfmaOp<T>, 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+        } else {
+            // (FP32 with FP64 accumulators is better off with two workgroups
+            // and their registers: 2999 x 1531 x 64 as chunks 38.5 us, 40.1
+            // with three)
+            e = one ? go_tiles<T, TOUT, false, 2, MfmaOp<T>, 3>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st)
+                    : go_tiles<T, TOUT, true, 2, MfmaOp<T>, 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+        }
     } else {
-        e = go_tiles<T, TOUT, false, 4, 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
+        e = go_tiles<T, TOUT, false, 4, MfmaOp<T>, 2>(A, B, dst, M, N, K, batch, kchunk, ksplit, kper, st);
     }
     if (e != hipSuccess) return e;
     const int64_t sC = (int64_t)M * N;

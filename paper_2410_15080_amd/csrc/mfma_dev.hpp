@@ -60,7 +60,7 @@ struct MfmaOp<bf16_t> {
     typedef f4_t acc;
     static constexpr int KI = 32;
     static constexpr int KPL = 8;
-    static constexpr int BK = 32;  // (half the LDS of 64: room for a third workgroup on a CU)
+    static constexpr int BK = 64;
     static constexpr int PAD = 8;
     __device__ __forceinline__ static int row(int lane, int r) { return 4 * (lane >> 4) + r; }
     __device__ __forceinline__ static acc mma(frag a, frag b, acc c) {
@@ -69,11 +69,16 @@ struct MfmaOp<bf16_t> {
     __device__ __forceinline__ static frag ld(const bf16_t *p) { return *(const bf8_t *)p; }
 };
 
+// BF16 with half the K slice, so half the LDS.
+struct MfmaOpBf16Half : MfmaOp<bf16_t> {
+    static constexpr int BK = 32;
+};
+
 // Load a ROWS x BK tile (rows r0.., K-columns k0..) of a [rows][K] operand
 // into registers: 16 bytes per load, zero outside the matrix.
-template <typename T, int ROWS>
+template <typename T, int ROWS, typename Op = MfmaOp<T>>
 struct TileLoader {
-    static constexpr int BK = MfmaOp<T>::BK;
+    static constexpr int BK = Op::BK;
     static constexpr int EPV = 16 / sizeof(T);               // elements per 16B vector
     static constexpr int VPR = BK / EPV;                      // vectors per row
     static constexpr int NV = ROWS * VPR / 256;               // vectors per thread
@@ -100,7 +105,7 @@ struct TileLoader {
         }
     }
     __device__ __forceinline__ void store(T *lds) const {
-        constexpr int LD = BK + MfmaOp<T>::PAD;
+        constexpr int LD = BK + Op::PAD;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int idx = threadIdx.x + i * 256;

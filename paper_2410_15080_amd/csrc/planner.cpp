@@ -535,9 +535,12 @@ static bool few_outputs_tiled(const Net &n, const StepPlan &s, int64_t M, int64_
 // matrix cores (tile_dev.hpp), from the operands as the layout pass leaves
 // them.  Even a side padded from 4 to 16 rows costs less than the
 // table-driven step's loads per product; below that, or with fewer than four
-// summed terms, the result's stores dominate either way.  (The random batch's
-// 4 x 9216 x 24 and 6 x 5184 x 4 steps are of that kind; with them on the
-// table-driven kernel its first two levels took 679 us, without 166.)  It also
+// summed terms, the result's stores dominate either way; with fewer than eight
+// and a padded side the table-driven step is faster, which spreads the stores
+// over more waves (four folds of 26 624 results over 4 terms
+// in a 1732 x 104 marginal: 33 us in all, 42 as tiles).  (With all its steps on
+// the table-driven kernel the random batch's first two levels took 679 us,
+// without 166.)  It also
 // takes FP32 and FP64 products that would be packed for the packed-operand
 // kernel: the operands are in tiled order already.  A BF16 product
 // stays with the packed BF16 instructions, sixteen times the FP32 rate.
@@ -546,6 +549,7 @@ static void plan_tile_step(const Net &n, StepPlan &s) {
     const bool acc_is_compute = !s.final_step || n.compute == HTN_F64 || n.final_sum == HTN_SUM_PLAIN;
     if (!s.tile || !n.allow_mfma || !acc_is_compute || (s.mfma && n.compute == HTN_BF16)) return;
     constexpr int64_t lim = int64_t(1) << 24;  // 32-bit offsets within a K chunk
+    if (s.tK < 8 && (s.tM < 16 || s.tN < 16)) return;
     if (s.tM < 4 || s.tN < 4 || s.tK < 4 || s.tM >= lim || s.tN >= lim || s.tK >= lim) return;
     s.x_tile = 1;
     // C's fastest label along the lanes (the N side) where M holds it
@@ -841,6 +845,21 @@ void build_plan(Net &n) {
             P.n_absorbed++;
         } else {
             classify_mfma(n, s, A.labels, B.labels, kept_set, sums, last);
+            if (last && !s.mfma) {
+                // the output may read batch..., N..., M...: the same product
+                // with its operands the other way round (a 104 x 1732 marginal
+                // in BF16 took 3 571 us in one workgroup of the fused kernel,
+                // its transpose 31 us as a matrix product).  Not where the
+                // caller asks for the fused kernel, which could not hold a
+                // large step's tables.
+                StepPlan t = s;
+                classify_mfma(n, t, B.labels, A.labels, kept_set, sums, last);
+                P.final_swappable = t.mfma != 0;
+                if (t.mfma && n.exec != HTN_EXEC_FUSED) {
+                    s = t;
+                    std::swap(s.a, s.b);
+                }
+            }
             if (s.mfma) {
                 // result laid out [batch][M][N]
             } else if (last) {

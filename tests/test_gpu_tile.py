@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 # (M, N, K): the smallest sides, one past and one short of a block and of each
 # tile shape, K around its chunks (16, 32) and split into ranges with a short
 # last one
-SHAPES = [(4, 256, 4), (256, 5, 7), (16, 64, 15), (64, 17, 16), (65, 31, 17), (33, 48, 31), (32, 97, 32), (15, 80, 33),
+SHAPES = [(4, 256, 8), (256, 5, 9), (16, 64, 15), (64, 17, 16), (65, 31, 17), (33, 48, 31), (32, 97, 32), (15, 80, 33),
           (130, 6, 63), (31, 33, 64), (96, 64, 129), (36, 24, 1000), (64, 16, 4096), (576, 36, 3456)]
 
 
@@ -66,3 +66,21 @@ def test_products_into_fp64_are_exact(compute):
         htn.htn_contract(n, out)
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy().reshape(M, N), ref), (M, N, K)
+
+
+@pytest.mark.parametrize("compute", [htn.HTN_F64, htn.HTN_F32, htn.HTN_BF16])
+def test_final_product_in_either_output_order(compute):
+    """A large final product is a matrix product whichever of its operands the
+    output's labels begin with; the fused kernel, asked for, still takes both."""
+    import torch
+    rng = np.random.default_rng(8)
+    for flip in (False, True):
+        w, ref = _net(rng, 300, 420, 48, flip)
+        n = create(w, compute=compute, final_sum=htn.HTN_SUM_FP64, storage=htn.HTN_F64)
+        assert json.loads(htn.htn_plan_json(n))["steps"][-1]["mfma"]
+        for mode in (htn.HTN_EXEC_STEPS, htn.HTN_EXEC_FUSED, htn.HTN_EXEC_AUTO):
+            htn.htn_set_option(n, htn.HTN_OPT_EXEC, mode)
+            out = htn.new_output(n)
+            htn.htn_contract(n, out)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy().reshape(ref.shape), ref), (flip, mode)
