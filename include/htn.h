@@ -76,6 +76,13 @@ typedef enum { HTN_F64 = 0, HTN_F32 = 1, HTN_BF16 = 2 } htn_dtype;
  *                        output FP64.
  *   HTN_SUM_COMPENSATED  as HTN_SUM_FP64 with Neumaier-compensated sums and
  *                        TwoSum combination of partial sums; output FP64.
+ * One exception to the last two: a last step that is a dense matrix product
+ * of 2^22 multiplications or more (both sides >= 64, K >= 8) with the
+ * output's labels in its operands' own order (batch..., the first operand's,
+ * the second's) runs on the packed matrix cores: operands in the compute
+ * type, for HTN_F32 and HTN_BF16 chunks of 64 products summed in FP32 and the
+ * chunks added in FP64, no compensation.  With the second operand's labels
+ * first, both hold as stated.
  * The final signed sum over QPD terms (weights +-1/2, gamma = 3 per CZ cut)
  * is where cancellation concentrates, so it may run in FP64 even when
  * every earlier step ran in FP32 or BF16.                                  */

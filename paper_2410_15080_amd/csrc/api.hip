@@ -1339,7 +1339,7 @@ static bool queue_net(QBuild &Q, Net &n, int bi) {
             // (a wave tile reads 4 x 16 values of either operand per K row)
             it.units_per_task = (int32_t)q_units_per_task(Q, it.n_units, 256 * std::min<int64_t>(it.t.kper, it.t.K));
             if (it.t.ksplit > 1) {
-                const int64_t part_off = o[2] = Q.take(it.t.ksplit * it.t.total * es);
+                const int64_t part_off = o[2] = Q.take(it.t.ksplit * it.t.total * (tc == 0 ? 8 : es));
                 const int g = Q.add(it, o);
                 last = add_ksum(g, part_off, it.t.ksplit, it.t.total);
             } else {

@@ -78,6 +78,10 @@ struct StepPlan {
     // products at ws_kpart.  x_swap: A and B change places, so that C's
     // fastest label runs along a wave's lanes.
     int x_tile = 0, x_split = 1, x_kper = 0, x_shape = 0, x_swap = 0;
+    // The final step is a matrix product whose operands change places because
+    // the output reads batch..., N..., M...; its operands keep the tiled layout
+    // (the fused kernel can run it as well) and are never packed to BF16.
+    bool exchanged = false;
     // Fused kernel: the waves [f_w0, f_w0 + f_nw) of the workgroup run the
     // step; steps of one phase are independent and run side by side.
     int f_w0 = 0, f_nw = 1;

@@ -38,7 +38,8 @@ hipError_t launch_step(const void *A, int ta, const void *B, int tb, void *C, in
 // B[k][n]; C's offset of (m, n) is tab[t_cm + m].x + tab[t_cn + n].x.  K range
 // kz (of length kper) goes to part + kz * total; the ranges are then summed in
 // order into C.  shape: wave tiles of 32 x 32 (0), 64 x 16 (1), 16 x 64 (2).
-// Type codes as above; FP64 throughout, or FP32 accumulation of FP32 or BF16
+// Type codes as above; FP64 throughout, FP64 products and accumulation of FP32
+// or BF16 operands into FP64 results, or FP32 accumulation of FP32 or BF16
 // operands into FP32 or (unsplit) BF16 results.
 struct TileArgs {
     int32_t M, N, K, t_cm, t_cn, ksplit, kper, shape, tiles_m, tiles_n;

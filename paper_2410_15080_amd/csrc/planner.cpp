@@ -543,11 +543,18 @@ static bool few_outputs_tiled(const Net &n, const StepPlan &s, int64_t M, int64_
 // without 166.)  It also
 // takes FP32 and FP64 products that would be packed for the packed-operand
 // kernel: the operands are in tiled order already.  A BF16 product
-// stays with the packed BF16 instructions, sixteen times the FP32 rate.
+// stays with the packed BF16 instructions, sixteen times the FP32 rate.  The
+// exchanged final product always runs here: in the output's type (FP64 products
+// and sums for HTN_SUM_FP64), on operands as they are, where the packed kernel
+// rounds an FP32 operand to BF16 and sums chunks of 64 in FP32 (700 x 900 x 64
+// from FP32: error 1.5e-7 packed, 5.6e-8 here, 19.9 us against 20.8; 4000 x
+// 4001 x 256 from BF16: 2.2e-3 and 3.9e-9, 74 us and 211, the FP64 rate; from
+// FP64 192 us either way).
 static void plan_tile_step(const Net &n, StepPlan &s) {
     s.x_tile = 0;
     const bool acc_is_compute = !s.final_step || n.compute == HTN_F64 || n.final_sum == HTN_SUM_PLAIN;
-    if (!s.tile || !n.allow_mfma || !acc_is_compute || (s.mfma && n.compute == HTN_BF16)) return;
+    if (!s.tile || !n.allow_mfma) return;
+    if (!s.exchanged && (!acc_is_compute || (s.mfma && n.compute == HTN_BF16))) return;
     constexpr int64_t lim = int64_t(1) << 24;  // 32-bit offsets within a K chunk
     if (s.tK < 8 && (s.tM < 16 || s.tN < 16)) return;
     if (s.tM < 4 || s.tN < 4 || s.tK < 4 || s.tM >= lim || s.tN >= lim || s.tK >= lim) return;
@@ -845,18 +852,17 @@ void build_plan(Net &n) {
             P.n_absorbed++;
         } else {
             classify_mfma(n, s, A.labels, B.labels, kept_set, sums, last);
-            if (last && !s.mfma) {
+            if (last && !s.mfma && n.final_sum != HTN_SUM_COMPENSATED) {
                 // the output may read batch..., N..., M...: the same product
                 // with its operands the other way round (a 104 x 1732 marginal
-                // in BF16 took 3 571 us in one workgroup of the fused kernel,
-                // its transpose 31 us as a matrix product).  Not where the
-                // caller asks for the fused kernel, which could not hold a
-                // large step's tables.
+                // in BF16 took 3 571 us in one workgroup of the fused kernel).
+                // Not with compensated sums, which no matrix instruction adds.
                 StepPlan t = s;
                 classify_mfma(n, t, B.labels, A.labels, kept_set, sums, last);
                 P.final_swappable = t.mfma != 0;
                 if (t.mfma && n.exec != HTN_EXEC_FUSED) {
                     s = t;
+                    s.exchanged = true;
                     std::swap(s.a, s.b);
                 }
             }
@@ -1032,7 +1038,7 @@ void build_plan(Net &n) {
     if (packed_layouts)
         for (int k : P.kernel_steps) {
             StepPlan &s = P.steps[k];
-            if (!s.mfma) continue;
+            if (!s.mfma || s.exchanged) continue;
             auto packed = [&](const std::vector<int> &mid) {
                 std::vector<int> o = s.g_batch;
                 o.insert(o.end(), mid.begin(), mid.end());
@@ -1045,7 +1051,7 @@ void build_plan(Net &n) {
     for (int k : P.kernel_steps) {
         StepPlan &s = P.steps[k];
         if (s.b < 0) continue;
-        if (s.mfma && packed_layouts) continue;  // operands keep the packed order
+        if (s.mfma && packed_layouts && !s.exchanged) continue;  // operands keep the packed order
         if (s.final_step && n.final_sum == HTN_SUM_COMPENSATED) continue;
         std::vector<int> al = P.values[s.a].labels, bl = P.values[s.b].labels;
         std::vector<int> K, M, Nn;
@@ -1084,6 +1090,17 @@ void build_plan(Net &n) {
         s.t_gm = M;
         s.t_gn = Nn;
         s.t_gk = K;
+    }
+    // an exchanged product without a tiled form (a batch label, an operand
+    // that a packed product wrote) stays exchanged in FP64, whose packed kernel
+    // computes in FP64; the packed FP32 and BF16 kernels do not give the final
+    // sum asked for, so the step goes back to the table-driven kernel
+    for (int k : P.kernel_steps) {
+        StepPlan &s = P.steps[k];
+        if (!s.exchanged || s.tile || n.compute == HTN_F64) continue;
+        s.exchanged = false;
+        s.mfma = 0;
+        std::swap(s.a, s.b);
     }
     for (int k : P.kernel_steps) {
         StepPlan &s = P.steps[k];
@@ -1164,7 +1181,7 @@ void build_plan(Net &n) {
             pack(s.a_labels, sta, s.g_m, s.pack_a);
             pack(s.b_labels, stb, s.g_n, s.pack_b);
             auto in_order = [&](int v, const std::vector<int> &mid) {
-                if (P.values[v].input) return false;
+                if (P.values[v].input || s.exchanged) return false;
                 const StepPlan &prod = P.steps[P.values[v].producer];
                 if (prod.mfma || prod.final_step || (prod.absorbed && n.compute == HTN_BF16)) return false;
                 std::vector<int> o = s.g_batch;
@@ -1383,7 +1400,8 @@ void build_plan(Net &n) {
             plan_tile_step(n, s);
             if (s.x_tile) {
                 if (s.x_split > 1) {
-                    s.ws_kpart = ff.alloc(s.x_split * s.tM * s.tN * es, 256);
+                    const int64_t rs = s.final_step ? dtype_size(out_dtype(n)) : es;
+                    s.ws_kpart = ff.alloc(s.x_split * s.tM * s.tN * rs, 256);
                     ff.release(s.ws_kpart);
                 }
             } else if (s.mfma) {

@@ -15,8 +15,8 @@ __global__ __launch_bounds__(kBlk) __attribute__((amdgpu_waves_per_eu(2))) void 
 
 hipError_t launch_tile(const void *A, int ta, const void *B, int tb, void *C, int tc, const int2 *tab,
                        const TileArgs &t, void *part, hipStream_t st) {
-    const bool f64 = ta == 0 || tb == 0 || tc == 0;
-    if (f64 ? (ta != 0 || tb != 0 || tc != 0) : (tc != 1 && tc != 2)) return hipErrorInvalidValue;
+    if (ta < 0 || ta > 2 || tb < 0 || tb > 2 || tc < 0 || tc > 2) return hipErrorInvalidValue;
+    if ((ta == 0) != (tb == 0) || (ta == 0 && tc != 0)) return hipErrorInvalidValue;
     if (t.M < 1 || t.N < 1 || t.K < 1 || t.ksplit < 1 || (t.ksplit > 1 && (!part || tc == 2)))
         return hipErrorInvalidValue;
     const int64_t units = (int64_t)t.tiles_m * t.tiles_n * t.ksplit;

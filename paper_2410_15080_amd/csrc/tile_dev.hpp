@@ -4,6 +4,9 @@
 // Shared by the per-step launch (tile.hip) and the batch's item kernels
 // (queue.hip), so that a step gives the same result bit for bit in all.
 //
+// With FP64 results of FP32 or BF16 operands the elements are widened as they
+// are read, and products and sums are FP64.
+//
 // A wave computes a tile of 64 16-row and 16-column blocks' worth of results
 // by itself: 32 x 32, or 64 x 16 or 16 x 64 where M or N is small.  A lane's
 // operand for a matrix instruction is one element: sixteen lanes read
@@ -135,7 +138,7 @@ __device__ __forceinline__ void tile_unit(const TA *__restrict__ A, const TB *__
             for (int j = 0; j < WN; ++j) {
                 if (n0 + 16 * j + lr >= t.N) continue;
                 const int64_t o = (int64_t)kz * t.total + cm + cn[j];
-                if constexpr (sizeof(T) == 8) {
+                if constexpr (sizeof(T) == 8) {  // FP64 results
                     ((double *)C)[o] = tot[i][j][e];
                 } else {
                     if (tc == 2)
@@ -164,6 +167,14 @@ __device__ __forceinline__ void tile_wave_any(const void *A, int ta, const void 
                                               const int2 *__restrict__ tab, const TileArgs &t, int w) {
     if (ta == 0)
         tile_wave<double, double, double>(A, B, C, tc, tab, t, w);
+    else if (tc == 0 && ta == 1 && tb == 1)
+        tile_wave<double, float, float>(A, B, C, tc, tab, t, w);
+    else if (tc == 0 && ta == 2 && tb == 2)
+        tile_wave<double, bf16_t, bf16_t>(A, B, C, tc, tab, t, w);
+    else if (tc == 0 && ta == 2)
+        tile_wave<double, bf16_t, float>(A, B, C, tc, tab, t, w);
+    else if (tc == 0)
+        tile_wave<double, float, bf16_t>(A, B, C, tc, tab, t, w);
     else if (ta == 1 && tb == 1)
         tile_wave<float, float, float>(A, B, C, tc, tab, t, w);
     else if (ta == 2 && tb == 2)
