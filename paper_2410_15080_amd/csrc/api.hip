@@ -878,20 +878,8 @@ htn_status htn_set_option(htn_net_t net, htn_option opt, int64_t value) {
     switch (opt) {
         case HTN_OPT_EXEC:
             if (value < HTN_EXEC_AUTO || value > HTN_EXEC_FUSED) return fail(HTN_E_ARG, "bad exec mode");
-        {
-            const htn_exec_mode old = net->exec;
-            net->exec = (htn_exec_mode)value;
-            // (the plan of such a final step depends on the executor)
-            if (net->plan.final_swappable && (old == HTN_EXEC_FUSED) != (net->exec == HTN_EXEC_FUSED)) {
-                try {
-                    replan(*net);
-                } catch (...) {
-                    net->exec = old;
-                    throw;
-                }
-            }
+            net->exec = (htn_exec_mode)value;  // (the plan serves every executor)
             return HTN_OK;
-        }
         case HTN_OPT_MAX_INTERMEDIATE: {
             if (value < 1 || value > 2147483647)
                 return fail(HTN_E_ARG, "cap outside [1, 2^31-1] (offsets are 32-bit)");

@@ -132,7 +132,6 @@ struct LoadPlan {
 };
 
 struct Plan {
-    bool final_swappable = false;  // the final step is a matrix product with its operands exchanged
     std::vector<StepPlan> steps;     // path steps + optional synthetic final
     std::vector<Value> values;       // indexed by SSA id
     std::vector<int> kernel_steps;   // indices into steps, execution order

@@ -859,8 +859,7 @@ void build_plan(Net &n) {
                 // Not with compensated sums, which no matrix instruction adds.
                 StepPlan t = s;
                 classify_mfma(n, t, B.labels, A.labels, kept_set, sums, last);
-                P.final_swappable = t.mfma != 0;
-                if (t.mfma && n.exec != HTN_EXEC_FUSED) {
+                if (t.mfma) {
                     s = t;
                     s.exchanged = true;
                     std::swap(s.a, s.b);

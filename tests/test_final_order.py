@@ -132,3 +132,43 @@ def test_compensated_sums_stay_compensated(compute):
     err = np.array([[abs(int(x) - int(y)) for x, y in zip(r, s)] for r, s in zip(got, ref)], dtype=np.float64)
     bound = 2 * (2.0 ** -53 * np.abs(ref.astype(np.float64)) + (2 * H) ** 2 * 2.0 ** -106 * mag.T)
     assert (err <= bound).all(), float((err / np.maximum(bound, 1e-300)).max())
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_executor_choice_leaves_the_plan(shape):
+    w = _product(np.random.default_rng(2), *shape, True)
+    net = htn.htn_create(w.tensors, w.labels, w.dims, w.out_labels, final_sum=htn.HTN_SUM_FP64)
+    plan = htn.htn_plan_json(net)
+    for mode in (htn.HTN_EXEC_FUSED, htn.HTN_EXEC_STEPS, htn.HTN_EXEC_AUTO):
+        htn.htn_set_option(net, htn.HTN_OPT_EXEC, mode)
+        assert htn.htn_plan_json(net) == plan, mode
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("compute", COMPUTE)
+def test_batch_outlives_a_change_of_executor(compute):
+    """A batch runs as it was made; the fused kernel, asked for, takes the same
+    plan (small whole numbers: every sum is exact)."""
+    import torch
+    rng = np.random.default_rng(3)
+    ws = [Network([rng.integers(-8, 9, size=(M, K)).astype(np.float64), rng.integers(-8, 9, size=(K, N)).astype(np.float64)],
+                  [[0, 2], [2, 1]], [M, N, K], [1, 0]) for M, N, K in SHAPES]
+    refs = [(w.tensors[0] @ w.tensors[1]).T for w in ws]
+    ts = [[torch.from_numpy(t).to("cuda") for t in w.tensors] for w in ws]
+    nets = [htn.htn_create(t, w.labels, w.dims, w.out_labels, compute=compute, final_sum=htn.HTN_SUM_FP64,
+                           storage=htn.HTN_F64) for t, w in zip(ts, ws)]
+    outs = [htn.new_output(n) for n in nets]
+    b = htn.htn_batch_create(nets)
+    for mode in (htn.HTN_EXEC_AUTO, htn.HTN_EXEC_FUSED, htn.HTN_EXEC_STEPS):
+        for n, o, ref in zip(nets, outs, refs):
+            htn.htn_set_option(n, htn.HTN_OPT_EXEC, mode)
+            htn.htn_contract(n, o)
+            torch.cuda.synchronize()
+            assert np.array_equal(o.cpu().numpy().reshape(ref.shape), ref), (mode, ref.shape)
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        htn.htn_batch_run(b, htn.pointer_array(outs))
+        torch.cuda.synchronize()
+        for o, ref in zip(outs, refs):
+            assert np.array_equal(o.cpu().numpy().reshape(ref.shape), ref), (mode, ref.shape)
+    htn.htn_batch_destroy(b)
