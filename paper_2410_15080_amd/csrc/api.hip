@@ -2130,6 +2130,21 @@ htn_status htn_batch_queue_info(htn_batch_t b, int32_t *n_nets, int32_t *n_tasks
     API_GUARD_END
 }
 
+htn_status htn_batch_level_info(htn_batch_t b, int32_t *n_nets, int32_t *n_levels, int32_t *max_items) {
+    API_GUARD_BEGIN
+    if (!b) return fail(HTN_E_ARG, "batch is NULL");
+    if (n_nets) *n_nets = (int32_t)std::count(b->in_levels.begin(), b->in_levels.end(), (char)1);
+    int32_t levels = 0, items = 0;
+    for (const auto &L : b->lv.level) {
+        levels += L.n_items > 0;
+        items = std::max(items, L.n_items);
+    }
+    if (n_levels) *n_levels = levels;
+    if (max_items) *max_items = items;
+    return HTN_OK;
+    API_GUARD_END
+}
+
 void htn_batch_destroy(htn_batch_t b) {
     if (!b) return;
     batch_free(b);

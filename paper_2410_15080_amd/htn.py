@@ -142,6 +142,7 @@ def load_library():
         "htn_batch_set_event_timing": (I32, [P, I32]),
         "htn_batch_launch_ms": (I32, [P, f32p, f32p, i32p]),
         "htn_batch_queue_info": (I32, [P, i32p, i32p, i32p]),
+        "htn_batch_level_info": (I32, [P, i32p, i32p, i32p]),
         "htn_qpd_sample": (I32, [I32, ctypes.POINTER(ctypes.c_double), I64, ctypes.POINTER(ctypes.c_double),
                                  i64p, ctypes.POINTER(ctypes.c_double)]),
         "htn_truncate_create": (I32, [ctypes.POINTER(P), I32, ctypes.POINTER(htn_truncation), I32]),
@@ -487,6 +488,13 @@ def htn_batch_queue_info(batch: Batch):
     the device and clears the flag."""
     a, t, e = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     _check(load_library().htn_batch_queue_info(batch.handle, ctypes.byref(a), ctypes.byref(t), ctypes.byref(e)))
+    return int(a.value), int(t.value), int(e.value)
+
+
+def htn_batch_level_info(batch: Batch):
+    """(networks in the batch's level launches, launches, most items in one)."""
+    a, t, e = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    _check(load_library().htn_batch_level_info(batch.handle, ctypes.byref(a), ctypes.byref(t), ctypes.byref(e)))
     return int(a.value), int(t.value), int(e.value)
 
 
