@@ -1556,7 +1556,8 @@ static void queue_upload(htn_batch *b, QBuild &Q, const std::vector<int> &sub_xc
 // the matrix cores' rate, about what a launch costs), without fold chains
 // (those have a kernel of their own).  Their intermediates are kept apart for
 // the batch's lifetime, up to kLevelMaxBytes in all; the nets beyond that, or
-// all of them where the device has no such memory left, keep one launch per
+// all of them where the device (or the caller's allocator) has no such memory
+// left, keep one launch per
 // step in their own workspaces.
 static constexpr double kLevelMaxMults = 1073741824.0;
 static constexpr int64_t kLevelMaxBytes = int64_t(8) << 30;
@@ -1565,19 +1566,11 @@ static bool level_net(const Net &n) {
     return n.queue_mode == 0 && n.plan.chains.empty() && n.plan.mults <= kLevelMaxMults;
 }
 
-// Orders the items by dependency level, heaviest item first, and uploads;
-// false (nothing kept) if the device has no memory for the intermediates.
-static bool levels_upload(htn_batch *b, QBuild &Q) {
+// Orders the items by dependency level, heaviest item first, and uploads.
+static void levels_build(htn_batch *b, QBuild &Q) {
     htn_batch::Levels &lv = b->lv;
     const int ni = (int)Q.items.size();
-    if (Q.ws > 0) {
-        hipError_t e = hipMalloc(&lv.d_ws, (size_t)Q.ws);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            lv.d_ws = nullptr;
-            return false;
-        }
-    }
+    if (Q.ws > 0) lv.d_ws = dalloc_bytes((size_t)Q.ws);
     unsigned char *ws = (unsigned char *)lv.d_ws;
     std::vector<int> order(ni);
     std::vector<int64_t> tasks(ni);
@@ -1638,6 +1631,18 @@ static bool levels_upload(htn_batch *b, QBuild &Q) {
     HIP_TRY(hipMemcpy(lv.d_first, first.data(), ni * 4, hipMemcpyHostToDevice));
     lv.d_done = dalloc<int32_t>(done.size());
     HIP_TRY(hipMemcpy(lv.d_done, done.data(), done.size() * 4, hipMemcpyHostToDevice));
+}
+
+// False (nothing kept) if the device, or the caller's allocator, has no
+// memory for them.
+static bool levels_upload(htn_batch *b, QBuild &Q) {
+    try {
+        levels_build(b, Q);
+    } catch (const Error &e) {
+        levels_free(b);
+        if (e.st != HTN_E_OOM) throw;
+        return false;
+    }
     return true;
 }
 

@@ -108,3 +108,41 @@ def test_mixed_batch_keeps_one_network_out():
     for got, want in zip(r[0], refs + [ref]):
         assert np.array_equal(got.reshape(want.shape), want)
     htn.htn_batch_destroy(b)
+
+
+def test_level_launches_use_the_callers_allocator():
+    """The launches' intermediates and lists come from the caller's allocator
+    and go back to it; where it has none, the networks run with a launch per
+    step as before, with the same results."""
+    import torch
+    ws = _heavy(htn.HTN_F64)
+    nets = [create(w, final_sum=htn.HTN_SUM_COMPENSATED, exec_mode=htn.HTN_EXEC_STEPS) for w in ws]
+    outs = [htn.new_output(n) for n in nets]
+    b, ref = _run_batch(nets, outs)  # (the nets' own buffers are made here)
+    assert htn.htn_batch_level_info(b)[0] == len(nets)
+    htn.htn_batch_destroy(b)
+    held, sizes, limit = {}, [], [None]
+
+    def alloc(n):
+        if limit[0] is not None and n > limit[0]:
+            return 0
+        t = torch.empty(n, dtype=torch.uint8, device="cuda")
+        held[t.data_ptr()] = t
+        sizes.append(n)
+        return t.data_ptr()
+
+    htn.htn_set_allocator(alloc, lambda p: held.pop(p, None))
+    try:
+        for cap in (None, 1 << 20, 1 << 13):
+            limit[0] = cap
+            del sizes[:]
+            b, r = _run_batch(nets, outs)
+            n = htn.htn_batch_level_info(b)[0]
+            assert n == (len(nets) if cap is None else 0), cap
+            assert cap is not None or max(sizes) > 1 << 20
+            assert all(np.array_equal(x, y) for x, y in zip(r[0], ref[0])), cap
+            htn.htn_batch_destroy(b)
+            assert not held, cap
+    finally:
+        torch.cuda.synchronize()
+        htn.htn_set_allocator(None, None)
