@@ -1856,17 +1856,19 @@ htn_status htn_batch_graph_state(htn_batch_t b, int32_t *state) {
 // d_stamps.
 static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool events) {
     const size_t n = b->nets.size();
-    // the run's start clock: written by the first materialisation launch,
-    // or by a launch of its own when there is none
-    int64_t *run_start = b->d_stamps + 2 * n;
-    // (level launches start beside it: then a launch of its own comes first)
+    // (neither the queue nor the levels while per-step phase clocks are asked for)
     const bool use_levels = !b->lv.level.empty() && !b->d_phase;
-    const bool prep_stamps = !b->groups.empty() && b->groups[0].n_fprep > 0 && !use_levels;
-    // the queue (not while per-step phase clocks are asked for); alone, it
-    // stamps the run's start itself (but for level launches beside it)
     const bool use_queue = b->q.n_tasks > 0 && !b->d_phase;
     const bool queue_alone = use_queue && b->groups.empty();
-    const bool queue_stamps = queue_alone && !use_levels;
+    auto per_step = [&](size_t k) { return !(use_queue && b->in_queue[k]) && !(use_levels && b->in_levels[k]); };
+    // the run's start clock: written by the first materialisation launch, by
+    // the queue if it is alone, or by a launch of its own: where there is
+    // neither, and where side streams have work, which starts beside them
+    int64_t *run_start = b->d_stamps + 2 * n;
+    bool side_work = use_levels;
+    for (size_t k = 0; k < b->step_nets.size(); ++k) side_work = side_work || per_step(k);
+    const bool prep_stamps = !b->groups.empty() && b->groups[0].n_fprep > 0 && !side_work;
+    const bool queue_stamps = queue_alone && !side_work;
     if (!prep_stamps && !queue_stamps) HIP_TRY(kern::launch_stamp(run_start, st));
     if (!b->sides.empty()) {
         HIP_TRY(hipEventRecord(b->ev_fork, st));
@@ -1904,7 +1906,7 @@ static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool 
         HIP_TRY(hipStreamWaitEvent(st, b->q.ev_join, 0));
     }
     for (size_t k = 0; k < b->step_nets.size(); ++k) {
-        if ((use_queue && b->in_queue[k]) || (use_levels && b->in_levels[k])) continue;
+        if (!per_step(k)) continue;
         const int i = b->step_nets[k];
         hipStream_t ss = b->sides[b->side_of[k]];
         HIP_TRY(kern::launch_stamp(b->d_stamps + 2 * (size_t)i, ss));

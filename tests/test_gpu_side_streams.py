@@ -1,0 +1,50 @@
+"""Clocks and streams of batches that mix fused networks with networks on side
+streams."""
+
+import numpy as np
+import pytest
+
+from paper_2410_15080_amd import htn
+from workloads import configs
+
+from gpu_helpers import create
+from test_gpu_level_dispatch import _products
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(b, outs, stream):
+    import torch
+    with torch.cuda.stream(stream):
+        htn.htn_batch_run(b, htn.pointer_array(outs), stream)
+    stream.synchronize()
+
+
+@pytest.mark.parametrize("fused", [0, 96])
+@pytest.mark.parametrize("how", ["eager", "graph", "phases"])
+def test_the_run_starts_before_its_networks(how, fused):
+    """Fused networks (with inputs to materialise), queued ones where there are
+    no fused ones, and one network with a launch per step: no clock of the run
+    lies before its start (but for the tick that two XCDs' clocks may differ)."""
+    import torch
+    nets = [create(configs.grid_network(s)) for s in range(fused or 2)]
+    if not fused:
+        for n in nets:
+            htn.htn_set_option(n, htn.HTN_OPT_QUEUE, 1)
+    step, _ = _products(1)
+    htn.htn_set_option(step[0], htn.HTN_OPT_QUEUE, 2)
+    nets += step
+    outs = [htn.new_output(n) for n in nets]
+    b = htn.htn_batch_create(nets)
+    assert htn.htn_batch_level_info(b)[0] == 0
+    if how == "phases":
+        htn.htn_batch_set_phase_timing(b, 4)
+    htn.htn_batch_set_graph(b, how == "graph")
+    stream = torch.cuda.Stream()
+    for rep in range(40):
+        _run(b, outs, stream)
+        t = htn.htn_batch_timestamps(b)
+        assert (t[:, 0] >= -1).all() and (t[:, 1] >= t[:, 0]).all(), (rep, t.min())
+        if how == "phases":
+            assert (htn.htn_batch_phase_times(b) >= -1).all(), rep
+    htn.htn_batch_destroy(b)
