@@ -157,11 +157,12 @@ struct htn_batch {
     int max_phases = 0;
     // Nets run step by step go on side streams, forked from and joined back
     // to the caller's stream, so they overlap each other and the fused
-    // launch; side_of[k] is the side stream of step_nets[k].
+    // launch; side_of[k] is the side stream of step_nets[k], side_of_all[k] in
+    // a run with phase clocks (no queue, no level launches).
     std::vector<hipStream_t> sides;
     std::vector<hipEvent_t> ev_join;
     hipEvent_t ev_fork = nullptr;
-    std::vector<int> side_of;
+    std::vector<int> side_of, side_of_all;
     // Optional HIP events around the prep and fused launches of eager runs
     // (htn_batch_set_event_timing): three per run.
     bool event_timing = false;
@@ -1750,16 +1751,9 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
         b->d_outs = dalloc<void *>(n);
         b->d_stamps = dalloc<int64_t>(2 * (size_t)n + 1);  // [2n]: start of the run
         if (!b->step_nets.empty()) {
-            // heaviest first, each to the least loaded side stream
             std::stable_sort(b->step_nets.begin(), b->step_nets.end(),
                              [&](int x, int y) { return nets[x]->plan.mults > nets[y]->plan.mults; });
             const int ns = std::min<int>(kSideStreams, (int)b->step_nets.size());
-            std::vector<double> load(ns, 0.0);
-            for (int i : b->step_nets) {
-                const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-                b->side_of.push_back(q);
-                load[q] += nets[i]->plan.mults;
-            }
             // the work queue takes every step-by-step net it can, each net
             // on the least loaded XCD (heaviest first)
             QBuild Q;
@@ -1803,6 +1797,24 @@ htn_status htn_batch_create(htn_batch_t *out, int32_t n, const htn_net_t *nets) 
                 ++n_level;
             }
             if (n_level < 2 || !levels_upload(b, L)) b->in_levels.assign(b->step_nets.size(), 0);
+            // launches per step: heaviest net first, each to the least loaded
+            // side stream, of which the first has the level launches; and all
+            // nets so for runs without the queue and the levels
+            auto sides = [&](bool all) {
+                std::vector<int> side(b->step_nets.size(), 0);
+                std::vector<double> load(ns, 0.0);
+                if (!all)
+                    for (size_t k = 0; k < side.size(); ++k)
+                        if (b->in_levels[k]) load[0] += nets[b->step_nets[k]]->plan.mults;
+                for (size_t k = 0; k < side.size(); ++k) {
+                    if (!all && (b->in_queue[k] || b->in_levels[k])) continue;
+                    side[k] = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+                    load[side[k]] += nets[b->step_nets[k]]->plan.mults;
+                }
+                return side;
+            };
+            b->side_of = sides(false);
+            b->side_of_all = sides(true);
             HIP_TRY(hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
             for (int q = 0; q < ns; ++q) {
                 hipStream_t sq = nullptr;
@@ -1908,7 +1920,7 @@ static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool 
     for (size_t k = 0; k < b->step_nets.size(); ++k) {
         if (!per_step(k)) continue;
         const int i = b->step_nets[k];
-        hipStream_t ss = b->sides[b->side_of[k]];
+        hipStream_t ss = b->sides[(b->d_phase ? b->side_of_all : b->side_of)[k]];
         HIP_TRY(kern::launch_stamp(b->d_stamps + 2 * (size_t)i, ss));
         run_steps(*b->nets[i], outs[i], ss, b->d_phase ? b->d_phase + (size_t)i * b->max_phases : nullptr,
                   b->max_phases);
