@@ -1562,6 +1562,8 @@ static void queue_upload(htn_batch *b, QBuild &Q, const std::vector<int> &sub_xc
 // step in their own workspaces.
 static constexpr double kLevelMaxMults = 1073741824.0;
 static constexpr int64_t kLevelMaxBytes = int64_t(8) << 30;
+// A launch has fewer than 2^32 threads.
+static constexpr int64_t kLevelMaxBlocks = ((int64_t(1) << 32) - 1) / kBlock;
 
 static bool level_net(const Net &n) {
     return n.queue_mode == 0 && n.plan.chains.empty() && n.plan.mults <= kLevelMaxMults;
@@ -1616,7 +1618,7 @@ static void levels_build(htn_batch *b, QBuild &Q) {
             seen[it.net] = 1;
         }
         if (it.flags & kern::QF_LAST) ended.push_back(it.net);
-        if (L.n_blocks + tasks[k] > (int64_t(1) << 30)) throw Error{HTN_E_UNSUPPORTED, "level: too many blocks"};
+        if (L.n_blocks + tasks[k] > kLevelMaxBlocks) throw Error{HTN_E_UNSUPPORTED, "level: too many blocks"};
         it.n_tasks = (int32_t)tasks[k];
         first[i] = L.n_blocks;
         L.n_blocks += (int)tasks[k];
@@ -1635,13 +1637,13 @@ static void levels_build(htn_batch *b, QBuild &Q) {
 }
 
 // False (nothing kept) if the device, or the caller's allocator, has no
-// memory for them.
+// memory for them, or a level has more blocks than a launch may.
 static bool levels_upload(htn_batch *b, QBuild &Q) {
     try {
         levels_build(b, Q);
     } catch (const Error &e) {
         levels_free(b);
-        if (e.st != HTN_E_OOM) throw;
+        if (e.st != HTN_E_OOM && e.st != HTN_E_UNSUPPORTED) throw;
         return false;
     }
     return true;
