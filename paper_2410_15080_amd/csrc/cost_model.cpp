@@ -46,17 +46,21 @@ void step_features(const Net &n, std::vector<float> &rows) {
         f[2] = lg((double)s.n_sum);
         f[3] = lg((double)P.values[s.a].size);
         f[4] = s.b >= 0 ? lg((double)P.values[s.b].size) : 0.0f;
-        const bool tile = fused && s.tile;
-        // matrix cores: a per-step GEMM, or a fused tiled step in MFMA mode
-        const bool mfma = (!fused && s.mfma) || (tile && s.TM == 0);
+        const bool xtile = !fused && s.x_tile;  // tiled on the matrix cores outside the fused kernel
+        const bool tile = (fused && s.tile) || xtile;
+        // matrix cores: a per-step GEMM, or a tiled step in MFMA mode
+        const bool mfma = xtile || (!fused && s.mfma) || (tile && s.TM == 0);
         if (tile) {
             f[5] = lg((double)s.tM);
             f[6] = lg((double)s.tN);
             f[7] = lg((double)s.tK);
-            f[8] = lg((double)std::max(1, s.TM * s.TN));
+            f[8] = lg((double)(xtile ? 16 : std::max(1, s.TM * s.TN)));
         }
         const int R = fused ? s.r_fused : s.r_global;
-        if (!tile && !mfma) f[9] = lg((double)R);
+        if (xtile)
+            f[9] = lg((double)s.x_split);
+        else if (!tile && !mfma)
+            f[9] = lg((double)R);
         f[10] = tile ? 1.0f : 0.0f;
         if (!tile && !mfma) {
             if (R <= 1)
