@@ -426,146 +426,175 @@ struct FMfma<float> {
     __device__ __forceinline__ static int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
-//
-// BM x BN blocks of a wave share their operands' reads, and 16 values of K
-// are read while the previous 16 are multiplied: operands outside LDS
-// arrive at the rate of the L1 cache (64 bytes a clock, which single blocks
-// use up) instead of one round trip per 16.  A 144 x 144 x 216 step with both
-// operands outside took 262 000 cycles with single blocks and no read ahead.
-// The products of block (bm, bn) over K summed terms from A and B on, in two
-// accumulators (to be added); mok and nok tell a lane's valid rows and columns.
+// Products of the BM x BN blocks from (bm, bn) on over K summed terms from A
+// and B on.  The blocks share their operands' reads, and 16 values of K are
+// read while the previous 16 are multiplied: operands outside LDS arrive at the
+// rate of the L1 cache (64 bytes a clock, which single blocks use up) instead
+// of one round trip per 16.  A 144 x 144 x 216 step with both operands outside
+// took 262 000 cycles with single blocks and no read ahead.
+// 32 terms are summed by the matrix core, in two halves, before they join the
+// result's running sum: chains of additions K long lose more than the partial
+// sums of the register tiles and of lanes that share a sum.  Relative error of
+// 1024 64-vertex rings, geometric mean, FP64 and FP32: register tiles and
+// shared sums only 1.48e-15, 8.5e-7; here with whole chains 1.72e-15, 9.3e-7,
+// joined every 64 terms 1.34e-15, 7.4e-7, every 32 1.27e-15, 7.3e-7, every 16
+// 1.22e-15, 6.5e-7.  Batches of 60 BF16 and 256 FP64 rings, 1024 grids: 442,
+// 1042, 134 us with whole chains; 454, 1055, 134 joined every 32 terms; 477,
+// 1056, 137 every 16.
 template <int BM, int BN, typename T, typename P>
 __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const int K, const int bm, const int bn,
-                                       const int lane, typename FMfma<T>::acc (&acc0)[BM][BN],
-                                       typename FMfma<T>::acc (&acc1)[BM][BN]) {
+                                       const int lane, typename FMfma<T>::acc (&acc)[BM][BN]) {
     typedef FMfma<T> Op;
+    typedef typename Op::acc Acc;
     const int li = lane & 15, lk = lane >> 4;
-            int am[BM], bx[BN];  // operand columns (0 outside the matrix, whose products are dropped below)
-            bool mok[BM], nok[BN];
-    #pragma unroll
-            for (int i = 0; i < BM; ++i) {
-                const int m = (bm * BM + i) * 16 + li;
-                mok[i] = m < M;
-                am[i] = mok[i] ? m : 0;
+    int am[BM], bx[BN];  // operand columns (0 outside the matrix: mok and nok are false there, products zero)
+    bool mok[BM], nok[BN];
+#pragma unroll
+    for (int i = 0; i < BM; ++i) {
+        const int m = (bm * BM + i) * 16 + li;
+        mok[i] = m < M;
+        am[i] = mok[i] ? m : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < BN; ++j) {
+        const int n = (bn * BN + j) * 16 + li;
+        nok[j] = n < N;
+        bx[j] = nok[j] ? n : 0;
+    }
+    Acc half0[BM][BN], half1[BM][BN];
+    auto clear = [&] {
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j) half0[i][j] = half1[i][j] = Acc{0, 0, 0, 0};
+    };
+    auto join = [&] {
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] += half0[i][j][r] + half1[i][j][r];
+    };
+    auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok, Acc (&half)[BM][BN]) {
+        T a[BM], b[BN];
+#pragma unroll
+        for (int i = 0; i < BM; ++i) a[i] = mok[i] && ok ? av[i] : T(0);
+#pragma unroll
+        for (int j = 0; j < BN; ++j) b[j] = nok[j] && ok ? bv[j] : T(0);
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j) half[i][j] = Op::mma(a[i], b[j], half[i][j]);
+    };
+    T av[4][BM], bv[4][BN];
+    int ao = lk * M, bo = lk * N;
+    auto load = [&](int u, int so, int to) {
+#pragma unroll
+        for (int i = 0; i < BM; ++i) av[u][i] = A[so + am[i]];
+#pragma unroll
+        for (int j = 0; j < BN; ++j) bv[u][j] = B[to + bx[j]];
+    };
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int j = 0; j < BN; ++j) acc[i][j] = Acc{0, 0, 0, 0};
+    clear();
+    constexpr int kJoin = 2;
+    int k = K, chunks = 0;
+    if (k >= 16) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
+        for (;;) {
+            T ac[4][BM], bc[4][BN];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                for (int i = 0; i < BM; ++i) ac[u][i] = av[u][i];
+#pragma unroll
+                for (int j = 0; j < BN; ++j) bc[u][j] = bv[u][j];
             }
-    #pragma unroll
-            for (int j = 0; j < BN; ++j) {
-                const int n = (bn * BN + j) * 16 + li;
-                nok[j] = n < N;
-                bx[j] = nok[j] ? n : 0;
-            }
-    #pragma unroll
-            for (int i = 0; i < BM; ++i)
-    #pragma unroll
-                for (int j = 0; j < BN; ++j) acc0[i][j] = acc1[i][j] = typename Op::acc{0, 0, 0, 0};
-            auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok, typename Op::acc (&acc)[BM][BN]) {
-                T a[BM], b[BN];
-    #pragma unroll
-                for (int i = 0; i < BM; ++i) a[i] = mok[i] && ok ? av[i] : T(0);
-    #pragma unroll
-                for (int j = 0; j < BN; ++j) b[j] = nok[j] && ok ? bv[j] : T(0);
-    #pragma unroll
-                for (int i = 0; i < BM; ++i)
-    #pragma unroll
-                    for (int j = 0; j < BN; ++j) acc[i][j] = Op::mma(a[i], b[j], acc[i][j]);
-            };
-            T av[4][BM], bv[4][BN];
-            int ao = lk * M, bo = lk * N;
-            auto load = [&](int u, int so, int to) {
-    #pragma unroll
-                for (int i = 0; i < BM; ++i) av[u][i] = A[so + am[i]];
-    #pragma unroll
-                for (int j = 0; j < BN; ++j) bv[u][j] = B[to + bx[j]];
-            };
-            int k = K;
+            k -= 16;
+            ao += 16 * M;
+            bo += 16 * N;
             if (k >= 16) {
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
-                for (;;) {
-                    T ac[4][BM], bc[4][BN];
-    #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-    #pragma unroll
-                        for (int i = 0; i < BM; ++i) ac[u][i] = av[u][i];
-    #pragma unroll
-                        for (int j = 0; j < BN; ++j) bc[u][j] = bv[u][j];
-                    }
-                    k -= 16;
-                    ao += 16 * M;
-                    bo += 16 * N;
-                    if (k >= 16) {
-    #pragma unroll
-                        for (int u = 0; u < 4; ++u) load(u, ao + 4 * u * M, bo + 4 * u * N);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-    #pragma unroll
-                    for (int u = 0; u < 4; u += 2) {
-                        mma_all(ac[u], bc[u], true, acc0);
-                        mma_all(ac[u + 1], bc[u + 1], true, acc1);
-                    }
-                    if (k < 16) break;
-                }
             }
-            // the last k < 16: a pair of slices, then up to two into acc0
-            const bool pair = k >= 8;
-            const int rest = k & 7;
-            if (pair) {
-                load(0, ao, bo);
-                load(1, ao + 4 * M, bo + 4 * N);
-                ao += 8 * M;
-                bo += 8 * N;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; u += 2) {
+                mma_all(ac[u], bc[u], true, half0);
+                mma_all(ac[u + 1], bc[u + 1], true, half1);
             }
-            const bool ok0 = lk < rest, ok1 = lk + 4 < rest;
-            if (rest > 0) load(2, ok0 ? ao : 0, ok0 ? bo : 0);
-            if (rest > 4) load(3, ok1 ? ao + 4 * M : 0, ok1 ? bo + 4 * N : 0);
-            if (pair) {
-                mma_all(av[0], bv[0], true, acc0);
-                mma_all(av[1], bv[1], true, acc1);
+            if (k < 16) break;
+            if (++chunks == kJoin) {
+                join();
+                clear();
+                chunks = 0;
             }
-            if (rest > 0) mma_all(av[2], bv[2], ok0, acc0);
-            if (rest > 4) mma_all(av[3], bv[3], ok1, acc0);
+        }
+    }
+    // the last k < 16: a pair of slices, then up to two into the first half
+    const bool pair = k >= 8;
+    const int rest = k & 7;
+    if (pair) {
+        load(0, ao, bo);
+        load(1, ao + 4 * M, bo + 4 * N);
+        ao += 8 * M;
+        bo += 8 * N;
+    }
+    const bool ok0 = lk < rest, ok1 = lk + 4 < rest;
+    if (rest > 0) load(2, ok0 ? ao : 0, ok0 ? bo : 0);
+    if (rest > 4) load(3, ok1 ? ao + 4 * M : 0, ok1 ? bo + 4 * N : 0);
+    if (pair) {
+        mma_all(av[0], bv[0], true, half0);
+        mma_all(av[1], bv[1], true, half1);
+    }
+    if (rest > 0) mma_all(av[2], bv[2], ok0, half0);
+    if (rest > 4) mma_all(av[3], bv[3], ok1, half0);
+    join();
 }
 
-// Block (bm, bn)'s results acc0 + acc1 into C.
+// The blocks' results into C.
 template <int BM, int BN, typename T, typename TOUT>
 __device__ __forceinline__ void mstore(const Dest<TOUT> &C, const StepWords &p, const int bm, const int bn,
-                                       const int lane, const typename FMfma<T>::acc (&acc0)[BM][BN],
-                                       const typename FMfma<T>::acc (&acc1)[BM][BN]) {
+                                       const int lane, const typename FMfma<T>::acc (&acc)[BM][BN]) {
     typedef FMfma<T> Op;
     const int M = p(4), N = p(5), nm = p(11), nn_l = p(12), li = lane & 15;
     const bool narrow = narrow_digits(M, N);
     bool nok[BN];
+    uint32_t xn[BN];
+    int cn[BN];
 #pragma unroll
-    for (int j = 0; j < BN; ++j) nok[j] = (bn * BN + j) * 16 + li < N;
-            uint32_t xn[BN];
-            int cn[BN];
-    #pragma unroll
-            for (int j = 0; j < BN; ++j) xn[j] = (uint32_t)((bn * BN + j) * 16 + li);
-            digit_offsets<BN>(p, 4 * nm, nn_l, narrow, xn, cn);
-    #pragma unroll
-            for (int i = 0; i < BM; ++i) {
-                const int m0 = (bm * BM + i) * 16;
-                uint32_t xm[4];
-                int cm[4];
-    #pragma unroll
-                for (int r = 0; r < 4; ++r) xm[r] = (uint32_t)(m0 + Op::row(lane, r));
-                digit_offsets<4>(p, 0, nm, narrow, xm, cm);
-                if (C.in_lds) {
-    #pragma unroll
-                    for (int j = 0; j < BN; ++j)
-    #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (nok[j] && m0 + Op::row(lane, r) < M)
-                                C.l[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
-                } else {
-    #pragma unroll
-                    for (int j = 0; j < BN; ++j)
-    #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (nok[j] && m0 + Op::row(lane, r) < M)
-                                C.g[cm[r] + cn[j]] = st_cvt<TOUT>(acc0[i][j][r] + acc1[i][j][r]);
-                }
-            }
+    for (int j = 0; j < BN; ++j) {
+        const int n = (bn * BN + j) * 16 + li;
+        nok[j] = n < N;
+        xn[j] = (uint32_t)n;
+    }
+    digit_offsets<BN>(p, 4 * nm, nn_l, narrow, xn, cn);
+#pragma unroll
+    for (int i = 0; i < BM; ++i) {
+        const int m0 = (bm * BM + i) * 16;
+        uint32_t xm[4];
+        int cm[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xm[r] = (uint32_t)(m0 + Op::row(lane, r));
+        digit_offsets<4>(p, 0, nm, narrow, xm, cm);
+        if (C.in_lds) {
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (nok[j] && m0 + Op::row(lane, r) < M) C.l[cm[r] + cn[j]] = st_cvt<TOUT>(acc[i][j][r]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (nok[j] && m0 + Op::row(lane, r) < M) C.g[cm[r] + cn[j]] = st_cvt<TOUT>(acc[i][j][r]);
+        }
+    }
 }
 
 template <int BM, int BN, typename T, typename TOUT, typename P>
@@ -580,9 +609,9 @@ __device__ __forceinline__ void mstep(P A, P B, const Dest<TOUT> &C, const StepW
         ++bm;
     }
     while (bm < nbm) {
-        typename FMfma<T>::acc acc0[BM][BN], acc1[BM][BN];
-        mblock<BM, BN, T>(A, B, M, N, K, bm, bn, lane, acc0, acc1);
-        mstore<BM, BN, T>(C, p, bm, bn, lane, acc0, acc1);
+        typename FMfma<T>::acc acc[BM][BN];
+        mblock<BM, BN, T>(A, B, M, N, K, bm, bn, lane, acc);
+        mstore<BM, BN, T>(C, p, bm, bn, lane, acc);
         bn += nw;
         while (bn >= nbn) {
             bn -= nbn;
@@ -615,24 +644,24 @@ __device__ __forceinline__ void msplit(P A, P B, const Dest<TOUT> &C, const Step
     const int kper = ((K + parts - 1) / parts + 3) & ~3;
     const int k0 = part * kper, kn = part < parts ? min(K - k0, kper) : 0;
     LdsPtr<T> red = (LdsPtr<T>)(sm + p(9));
-    typename FMfma<T>::acc acc0[1][1], acc1[1][1];
+    typename FMfma<T>::acc acc[1][1];
     if (part < parts) {
         if (kn > 0)
-            mblock<1, 1, T>(A + k0 * M, B + k0 * N, M, N, kn, bm, bn, lane, acc0, acc1);
+            mblock<1, 1, T>(A + k0 * M, B + k0 * N, M, N, kn, bm, bn, lane, acc);
         else
-            acc0[0][0] = acc1[0][0] = typename FMfma<T>::acc{0, 0, 0, 0};
+            acc[0][0] = typename FMfma<T>::acc{0, 0, 0, 0};
         if (part > 0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[((part - 1) * nb + blk) * 256 + 64 * r + lane] = acc0[0][0][r] + acc1[0][0][r];
+            for (int r = 0; r < 4; ++r) red[((part - 1) * nb + blk) * 256 + 64 * r + lane] = acc[0][0][r];
         }
     }
     __syncthreads();
     if (part == 0) {
         for (int q = 1; q < parts; ++q) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc1[0][0][r] += red[((q - 1) * nb + blk) * 256 + 64 * r + lane];
+            for (int r = 0; r < 4; ++r) acc[0][0][r] += red[((q - 1) * nb + blk) * 256 + 64 * r + lane];
         }
-        mstore<1, 1, T>(C, p, bm, bn, lane, acc0, acc1);
+        mstore<1, 1, T>(C, p, bm, bn, lane, acc);
     }
 }
 
