@@ -3051,11 +3051,22 @@ struct SvBuild {
         e.n_pass = (int32_t)ops.sched.passes.size();
         e.pass0 = ops.pass0;
         for (int q = 0; q < n; ++q) {
-            const double *u = &ops.sched.lead[8 * (size_t)q], *v = x.init + 4 * q;
-            double *d = e.init[n - 1 - q];
+            const long double *u = &ops.sched.lead[8 * (size_t)q];
+            const double *v = x.init + 4 * q;
+            // (what rounding the other unitaries took from the norm is made
+            // up for at the first qubit)
+            const double lost = q == 0 ? (double)ops.sched.lost : 0.0;
+            double *d = e.init[n - 1 - q], *corr = e.corr[n - 1 - q];
             for (int r = 0; r < 2; ++r) {
-                d[2 * r] = (u[4 * r] * v[0] - u[4 * r + 1] * v[1]) + (u[4 * r + 2] * v[2] - u[4 * r + 3] * v[3]);
-                d[2 * r + 1] = (u[4 * r] * v[1] + u[4 * r + 1] * v[0]) + (u[4 * r + 2] * v[3] + u[4 * r + 3] * v[2]);
+                const long double x = (u[4 * r] * v[0] - u[4 * r + 1] * v[1]) + (u[4 * r + 2] * v[2] - u[4 * r + 3] * v[3]);
+                const long double y = (u[4 * r] * v[1] + u[4 * r + 1] * v[0]) + (u[4 * r + 2] * v[3] + u[4 * r + 3] * v[2]);
+                const double hx = d[2 * r] = (double)x, hy = d[2 * r + 1] = (double)y;
+                // (x + iy) / (hx + ihy) - 1
+                const long double dx = x - hx, dy = y - hy, sq = (long double)hx * hx + (long double)hy * hy;
+                const double cx = (double)((dx * hx + dy * hy) / sq), cy = (double)((dy * hx - dx * hy) / sq);
+                const bool ok = std::abs(cx) + std::abs(cy) < 1e-15;  // (no for a zero, an infinity or a NaN)
+                corr[2 * r] = (ok ? cx : 0.0) + lost;
+                corr[2 * r + 1] = ok ? cy : 0.0;
             }
         }
         if (c == 2) {

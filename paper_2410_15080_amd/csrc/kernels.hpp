@@ -165,12 +165,13 @@ static_assert((1 << (kSvTinyQubits - kSvRegBits0)) <= kSvThreads0 && (1 << (kSvL
                   (1 << (kSvTileBits - kSvRegBits2)) <= kSvThreads2,
               "every group of a state has a thread");
 // A state to be prepared and evolved (init[p]: vector of the qubit at
-// amplitude bit p).
+// amplitude bit p, the unitaries ahead of every other op on it applied).
 struct SvState {
     int32_t n, n_pass;
     int64_t pass0;  // its passes (SvLaunch::passes)
     int64_t off;    // amplitudes into gstate (class 2)
     double init[kSvMaxQubits][4];  // (re0, im0, re1, im1)
+    double corr[kSvMaxQubits][4];  // what rounding init lost, relative to it
 };
 struct SvPass {
     int64_t rec0;  // its records (SvLaunch::recs)

@@ -22,12 +22,17 @@
 // dozen dependent records for the small ones (a record took 0.4 us whatever
 // it held until the CZ gates and unitaries of a group were packed into
 // layers).  Two 15-qubit subcircuits of 4 layers (80 instances, 37 distinct
-// states): evaluation and contraction 4 327 -> 101 us; the 44 instances of 3 to
-// 5 qubits of the 10-qubit circuit 44.2 -> 23.0 us, contraction included.  Before,
+// states): evaluation and contraction 4 317 -> 86 us; the 44 instances of 3 to
+// 5 qubits of the 10-qubit circuit 44.2 -> 19.4 us, contraction included.  Before,
 // one workgroup per instance ran every op as a pass over its state.
-// Merged unitaries and regrouped products do not cost accuracy: state error
-// against 80-bit arithmetic, mean of 400 random circuits of 1 to 16 qubits,
-// 2.85e-16 op by op and 2.78e-16 scheduled.
+//
+// Unitaries merged on the host are rounded once for the whole state: their
+// error of the norm is common to all amplitudes and does not average out of
+// an output.  The host knows it (products in 80 bits) and puts it into the
+// state's correction.  QT entries of those two workloads against 80-bit states,
+// root mean square of four sets of angles: op by op 3.3e-16 and 6.0e-16, merged
+// without the correction 5.9e-16 and 5.7e-16, with it 4.1e-16 and 5.0e-16; of
+// 12- and 11-qubit subcircuits 3.6e-16, 6.0e-16 and 3.4e-16.
 //
 // The result of a Pauli observable O = (x)_q P_q with projectors on the
 // kept qubits,
@@ -62,6 +67,7 @@ __device__ __forceinline__ int sv_slot(int i) { return i ^ ((i >> 4) & 15) ^ ((i
 struct SvTables {
     SvRecord recs[kRecChunk];
     double2 plo[64], phi[64];  // product-state factors of the low six and the higher tile bits
+    double2 clo[64], chi[64];  // and their corrections (SvState::corr), summed
     int32_t dlo[64], dhi[64];  // amplitude index bits of the low six and the higher tile bits
 };
 
@@ -231,20 +237,37 @@ __device__ __forceinline__ void tile_tables(SvTables &T, const SvState &E, const
         const int half = e >> 6, x = e & 63;
         const int j0 = 6 * half, j1 = min(tb, j0 + 6);
         int d = 0;
-        double2 f = make_double2(1.0, 0.0);
+        double2 f = make_double2(1.0, 0.0), c = make_double2(0.0, 0.0);
         for (int j = j0; j < j1; ++j) {
             const int bit = (x >> (j - j0)) & 1, p = P.lpos[j];
             d |= bit << p;
             if (prep) {
-                if (p < E.n)
+                if (p < E.n) {
                     f = cmul(f, make_double2(E.init[p][2 * bit], E.init[p][2 * bit + 1]));
-                else if (bit)
+                    c.x += E.corr[p][2 * bit];
+                    c.y += E.corr[p][2 * bit + 1];
+                } else if (bit) {
                     f = make_double2(0.0, 0.0);  // padding of a small state
+                }
             }
         }
         (half ? T.dhi : T.dlo)[x] = d;
-        if (prep) (half ? T.phi : T.plo)[x] = f;
+        if (prep) {
+            (half ? T.phi : T.plo)[x] = f;
+            (half ? T.chi : T.clo)[x] = c;
+        }
     }
+}
+
+// Amplitude i of the prepared tile (T.plo etc. filled) times ph (1 + c).  The
+// rounding of a qubit's vector is common to all amplitudes, so unlike an
+// amplitude's own rounding it does not average out of a sum over them: it is
+// carried beside the factors and added once.
+__device__ __forceinline__ double2 prepared(const SvTables &T, int i, double2 ph, double2 c) {
+    const double2 t = cmul(cmul(T.plo[i & 63], T.phi[i >> 6]), ph);
+    const double2 a = T.clo[i & 63], b = T.chi[i >> 6];
+    const double x = a.x + b.x + c.x, y = a.y + b.y + c.y;
+    return make_double2(t.x + (t.x * x - t.y * y), t.y + (t.x * y + t.y * x));
 }
 
 // c(s) conj(psi[s ^ m]) psi[s], real part
@@ -349,7 +372,8 @@ __global__ __launch_bounds__(THREADS) void k_sv_small(const SvInst *__restrict__
     load_recs(T, recs + P.rec0, 0, P.n_rec, THREADS);
     tile_tables(T, E, P, tb, true, THREADS);
     __syncthreads();
-    for (int i = threadIdx.x; i < (1 << tb); i += THREADS) sv_lds[sv_slot(i)] = cmul(T.plo[i & 63], T.phi[i >> 6]);
+    for (int i = threadIdx.x; i < (1 << tb); i += THREADS)
+        sv_lds[sv_slot(i)] = prepared(T, i, make_double2(1.0, 0.0), make_double2(0.0, 0.0));
     __syncthreads();
     run_records<K, THREADS>(sv_lds, T, recs + P.rec0, P.n_rec, tb, 0);
     auto psi = [&](int s) { return sv_lds[sv_slot(s)]; };
@@ -373,17 +397,21 @@ __global__ __launch_bounds__(THREADS) void k_sv_pass(const SvState *__restrict__
     load_recs(T, recs + P.rec0, 0, P.n_rec, THREADS);
     tile_tables(T, E, P, tb, pass == 0, THREADS);
     int hi = 0;
-    double2 ph = make_double2(1.0, 0.0);
+    double2 ph = make_double2(1.0, 0.0), pc = make_double2(0.0, 0.0);
     for (int j = 0; j < E.n - tb; ++j) {
         const int bit = (tile >> j) & 1, p = P.hpos[j];
         hi |= bit << p;
-        if (pass == 0) ph = cmul(ph, make_double2(E.init[p][2 * bit], E.init[p][2 * bit + 1]));
+        if (pass == 0) {
+            ph = cmul(ph, make_double2(E.init[p][2 * bit], E.init[p][2 * bit + 1]));
+            pc.x += E.corr[p][2 * bit];
+            pc.y += E.corr[p][2 * bit + 1];
+        }
     }
     __syncthreads();
     double2 *g = gstate + E.off;
     if (pass == 0) {
         for (int i = threadIdx.x; i < (1 << tb); i += THREADS)
-            sv_lds[sv_slot(i)] = cmul(cmul(T.plo[i & 63], T.phi[i >> 6]), ph);
+            sv_lds[sv_slot(i)] = prepared(T, i, ph, pc);
     } else {
 #pragma unroll 4
         for (int i = threadIdx.x; i < (1 << tb); i += THREADS)

@@ -34,18 +34,30 @@ struct Left {
 };
 
 // c = a * b, 2x2 complex row-major (re, im)
-void mul2(const double *a, const double *b, double *c) {
+void mul2(const double *a, const long double *b, long double *c) {
     for (int i = 0; i < 2; ++i)
         for (int j = 0; j < 2; ++j) {
-            double re = 0.0, im = 0.0;
+            long double re = 0.0L, im = 0.0L;
             for (int k = 0; k < 2; ++k) {
-                const double *x = a + 4 * i + 2 * k, *y = b + 4 * k + 2 * j;
+                const double *x = a + 4 * i + 2 * k;
+                const long double *y = b + 4 * k + 2 * j;
                 re += x[0] * y[0] - x[1] * y[1];
                 im += x[0] * y[1] + x[1] * y[0];
             }
             c[4 * i + 2 * j] = re;
             c[4 * i + 2 * j + 1] = im;
         }
+}
+
+// Re tr(M^* (M - m)) / tr(M^* M): what rounding M to m takes from the norm of a
+// state on whose qubit nothing else is known.
+long double norm_lost(const long double *M, const double *m) {
+    long double d = 0.0L, s = 0.0L;
+    for (int i = 0; i < 8; ++i) {
+        d += M[i] * (M[i] - m[i]);
+        s += M[i] * M[i];
+    }
+    return std::abs(d) < 1e-15L * s ? d / s : 0.0L;  // (no for zeros, infinities and NaN)
 }
 
 struct Scheduler {
@@ -176,23 +188,24 @@ void emit_group(const Scheduler &S, const std::vector<int> &run, const std::vect
 SvSchedule sv_schedule(int n, const htn_sv_op *in, int n_ops, int tile, int K) {
     SvSchedule out;
     const int nb = std::max(n, K);  // amplitude bits (bits n.. of a padded small state stay 0)
-    static const double one[8] = {1, 0, 0, 0, 0, 0, 1, 0};
+    static const long double one[8] = {1, 0, 0, 0, 0, 0, 1, 0};
     out.lead.resize(8 * (size_t)n);
-    for (int q = 0; q < n; ++q) std::memcpy(&out.lead[8 * (size_t)q], one, sizeof(one));
+    for (int q = 0; q < n; ++q) std::copy(one, one + 8, &out.lead[8 * (size_t)q]);
     Scheduler S;
     // consecutive single-qubit unitaries of a qubit become one matrix
-    std::vector<double> pend(8 * (size_t)n);
+    std::vector<long double> pend(8 * (size_t)n);
     std::vector<char> has(n, 0), touched(n, 0);
     auto push = [&](Op o) { S.ops.push_back(std::move(o)); };
     auto flush = [&](int q) {
         if (has[q]) {
             if (!touched[q]) {
-                std::memcpy(&out.lead[8 * (size_t)q], &pend[8 * (size_t)q], sizeof(one));
+                std::copy_n(&pend[8 * (size_t)q], 8, &out.lead[8 * (size_t)q]);
             } else {
                 Op o;
                 o.kind = U1;
                 o.need = o.p0 = n - 1 - q;
-                std::memcpy(o.m, &pend[8 * (size_t)q], sizeof(o.m));
+                std::copy_n(&pend[8 * (size_t)q], 8, o.m);
+                out.lost += norm_lost(&pend[8 * (size_t)q], o.m);
                 push(o);
             }
             has[q] = 0;
@@ -202,13 +215,13 @@ SvSchedule sv_schedule(int n, const htn_sv_op *in, int n_ops, int tile, int K) {
     for (int k = 0; k < n_ops; ++k) {
         const htn_sv_op &x = in[k];
         if (x.kind == HTN_SV_U1) {
-            double *p = &pend[8 * (size_t)x.q0];
+            long double *p = &pend[8 * (size_t)x.q0];
             if (has[x.q0]) {
-                double t[8];
+                long double t[8];
                 mul2(x.m, p, t);
-                std::memcpy(p, t, sizeof(t));
+                std::copy_n(t, 8, p);
             } else {
-                std::memcpy(p, x.m, sizeof(one));
+                std::copy_n(x.m, 8, p);
             }
             has[x.q0] = 1;
             continue;

@@ -42,7 +42,9 @@ static_assert(sizeof(SvRecord) == 224, "copied to the device as 16-byte chunks")
 struct SvSchedule {
     // per qubit, the product of the single-qubit unitaries ahead of every
     // other op on it (row-major, re/im): applied to its initial vector
-    std::vector<double> lead;
+    std::vector<long double> lead;
+    // relative loss of norm by rounding the other merged unitaries, in all
+    long double lost = 0.0L;
     struct Pass {
         std::vector<int> lpos, hpos;  // amplitude bits of the tile, and of the tile number (ascending)
         std::vector<SvRecord> recs;
