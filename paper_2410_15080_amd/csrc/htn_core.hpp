@@ -164,7 +164,6 @@ struct Plan {
     bool fused_batch_ok = false;  // batches run the net in the fused launch
     bool fused_possible = false;  // program and table slots fit the LDS budget
     bool fused_pure = false;
-    bool fused_lds_only = false;  // every operand and result of every step in LDS
     int64_t fused_lds_bytes = 0;
     int64_t fused_scratch_bytes = 0;
     std::vector<int32_t> program;

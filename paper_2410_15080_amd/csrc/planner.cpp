@@ -1634,7 +1634,6 @@ void build_plan(Net &n) {
         std::vector<int> pending;
         std::vector<int64_t> phase_scratch;  // LDS of the phase's split sums
         int phase = 0, last_step = -1;
-        bool lds_only = true;
         for (auto &r : seq) {
             if (r.kind == OP_COPY && r.value >= 0) {
                 const int64_t sz = P.values[r.value].size;
@@ -1673,7 +1672,6 @@ void build_plan(Net &n) {
                 }
                 pending.push_back(s.a);
                 pending.push_back(s.b);
-                if (loc[s.a] < 0 || (s.b >= 0 && loc[s.b] < 0) || (!s.final_step && cl < 0)) lds_only = false;
                 s.f_phase = phase;
                 s.f_spill = (loc[s.a] < 0 ? 1 : 0) | (s.b >= 0 && loc[s.b] < 0 ? 2 : 0) |
                             (!s.final_step && cl < 0 ? 4 : 0);
@@ -1744,7 +1742,6 @@ void build_plan(Net &n) {
         P.program = std::move(prog);
         P.ptr_slots = P.fused_in_ptr_slots;
         P.fused_pure = glb_ff.peak <= inputs_end;
-        P.fused_lds_only = lds_only;
         bool has_mfma = false;
         for (const auto &st : P.steps) has_mfma |= st.mfma != 0;
         // The fused kernel needs its program and table slots in LDS.  Dense
@@ -1923,6 +1920,8 @@ static std::string chains_json(const Net &n) {
 
 std::string plan_json(const Net &n) {
     const Plan &P = n.plan;
+    bool lds_only = true;  // every operand and result of every step in LDS
+    for (int k : P.kernel_steps) lds_only = lds_only && P.steps[k].f_spill == 0;
     std::ostringstream o;
     o.precision(17);
     o << "{\"n_tensors\":" << n.n_t << ",\"mults\":" << P.mults << ",\"peak\":" << P.peak
@@ -1931,7 +1930,7 @@ std::string plan_json(const Net &n) {
       << ",\"n_absorbed\":" << P.n_absorbed << ",\"fused_ok\":" << (P.fused_ok ? "true" : "false")
       << ",\"fused_batch_ok\":" << (P.fused_batch_ok ? "true" : "false")
       << ",\"fused_pure\":" << (P.fused_pure ? "true" : "false")
-      << ",\"fused_lds_only\":" << (P.fused_lds_only ? "true" : "false") << ",\"fused_lds_bytes\":" << P.fused_lds_bytes
+      << ",\"fused_lds_only\":" << (lds_only ? "true" : "false") << ",\"fused_lds_bytes\":" << P.fused_lds_bytes
       << ",\"fused_scratch_bytes\":" << P.fused_scratch_bytes << ",\"ws_bytes\":" << P.ws_bytes
       << ",\"final_value\":" << P.final_value << ",\"n_table_entries\":" << P.tables.size() / 2
       << ",\"chains\":" << chains_json(n)
