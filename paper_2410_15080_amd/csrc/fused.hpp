@@ -140,10 +140,10 @@ __device__ __forceinline__ void strided_sum(P a0, P b0, const int2 *tsh, const i
     }
 }
 
+// Table-driven step.  Threads tid = 0..nthr-1 of the step's waves run it; R ==
+// nthr (the whole workgroup per output) is planned only when the step owns the
+// workgroup (nthr == BLK), since it synchronises every wave.
 template <int BLK, typename ACC, bool COMP, bool UNARY, typename TOUT, typename P>
-// Threads tid = 0..nthr-1 of the step's waves run it; R == nthr (the whole
-// workgroup per output) is planned only when the step owns the workgroup
-// (nthr == BLK), since it synchronises every wave.
 __device__ __forceinline__ void fstep(P A, P B, const Dest<TOUT> &C, const int2 *__restrict__ tab,
                                       const StepWords &p, ACC *scratch, const int tid, const int nthr) {
     const int n_ohi = p(4), n_olo = p(5), n_shi = p(6), n_slo = p(7);

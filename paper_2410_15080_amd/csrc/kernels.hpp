@@ -151,12 +151,12 @@ constexpr int kSvMaxQubits = 24;
 constexpr int kSvLdsQubits = 12;  // states of at most this many qubits live in LDS
 // Instance classes: 0: up to kSvTinyQubits qubits, one wave each; 1: up to
 // kSvLdsQubits; 2: states in device memory, in tiles of kSvTileBits bits.
-// Register bits and threads of each.  Measured (whole calls): class 1 at
-// three register bits and 512 threads 50.3 us for 80 instances of 12 qubits
-// (four and 256: 66.8; tiles in device memory from 11 qubits on: 51.9); class
-// 2 in tiles of 10 bits 100.6 us for 37 states of 15 qubits and 42.3 for 13
-// and 14 qubits (12 bits and 512 threads: 110.3 and 47.6, too few workgroups
-// for the chip); a wave per tiny instance keeps its barriers free.
+// Register bits and threads of each.  Measured (whole calls, relative to the
+// choice): class 1 of three register bits and 512 threads, 80 instances of 12
+// qubits (46.6 us): four and 256 1.33, tiles in device memory from 11 qubits on
+// 1.03; class 2 in tiles of 10 bits, 37 states of 15 qubits (86 us) and 13 and
+// 14 qubits (39.5 us): 12 bits and 512 threads 1.10 and 1.13, too few
+// workgroups for the chip; a wave per tiny instance keeps its barriers free.
 constexpr int kSvTinyQubits = 8;
 constexpr int kSvRegBits0 = 2, kSvThreads0 = 64;
 constexpr int kSvRegBits1 = 3, kSvThreads1 = 512;

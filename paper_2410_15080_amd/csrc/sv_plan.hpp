@@ -52,8 +52,11 @@ struct SvSchedule {
     std::vector<Pass> passes;  // at least one
 };
 
-// Ops of an n-qubit instance (validated by the caller); tile: bits of a
-
+// Schedule of the n_ops ops of an n-qubit instance (validated by the caller), n
+// at least 1.  K: register bits of a group, 1 to kSvMaxRegBits; a state of
+// fewer qubits is padded to K bits, which stay 0.  tile: amplitude bits that a
+// workgroup holds, at least max(3, K), since the three lowest bits are in every
+// tile; max(n, K) or more gives one pass over the whole state.
 SvSchedule sv_schedule(int n, const htn_sv_op *ops, int n_ops, int tile, int K);
 
 }  // namespace htn

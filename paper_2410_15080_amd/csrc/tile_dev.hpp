@@ -7,8 +7,8 @@
 // With FP64 results of FP32 or BF16 operands the elements are widened as they
 // are read, and products and sums are FP64.
 //
-// A wave computes a tile of 64 16-row and 16-column blocks' worth of results
-// by itself: 32 x 32, or 64 x 16 or 16 x 64 where M or N is small.  A lane's
+// A wave computes four 16 x 16 blocks (1024 results) by itself: 32 x 32, or
+// 64 x 16 or 16 x 64 where M or N is small.  A lane's
 // operand for a matrix instruction is one element: sixteen lanes read
 // sixteen neighbours of a row of A (or B), so the fragments come straight
 // from global memory in whole segments, with no LDS (which leaves the CU to
