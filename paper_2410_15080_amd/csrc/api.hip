@@ -1866,9 +1866,9 @@ htn_status htn_batch_graph_state(htn_batch_t b, int32_t *state) {
 // materialisation and the fused launch go on the caller's stream; nets run
 // step by step (the large ones) go to the side streams, forked before that:
 // the level launches on the first, launches per step spread over all; the
-// caller's stream finally waits for every side stream.  Every net's start and completion clock lands in
-// d_stamps.
-static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool events) {
+// caller's stream finally waits for every side stream.  Every net's start and
+// completion clock lands in d_stamps.  capture: the launches go into a graph.
+static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool events, bool capture = false) {
     const size_t n = b->nets.size();
     // (neither the queue nor the levels while per-step phase clocks are asked for)
     const bool use_levels = !b->lv.level.empty() && !b->d_phase;
@@ -1888,10 +1888,14 @@ static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool 
         HIP_TRY(hipEventRecord(b->ev_fork, st));
         for (hipStream_t q : b->sides) HIP_TRY(hipStreamWaitEvent(q, b->ev_fork, 0));
     }
-    // (the level launches first: they depend on nothing of the fused nets', and
-    // behind their materialisation they would start 100 us later in the batch
-    // of 512 random networks, 629 against 595 us in all)
-    if (use_levels) run_levels(b, b->sides[0]);
+    // The level launches depend on nothing of the fused nets'.  In a graph they
+    // come first (512 random networks: behind the fused nets' materialisation
+    // they would start 100 us later, 629 us in all against 595; 1024 grids with
+    // two chains of 39 steps 645 us, 821 behind the fused launch); launched
+    // one by one they come behind the few fused launches, which would wait
+    // for the host otherwise (the same batch 780 us, 827 with the levels
+    // first, and the grids start after 86 us in place of 569).
+    if (use_levels && capture) run_levels(b, b->sides[0]);
     if (events) HIP_TRY(hipEventRecord(next_event(b), st));
     for (size_t gi = 0; gi < b->groups.size(); ++gi) {
         const auto &g = b->groups[gi];
@@ -1907,6 +1911,7 @@ static void batch_enqueue(htn_batch *b, void *const *outs, hipStream_t st, bool 
         HIP_TRY(kern::launch_fused(b->d_desc + g.desc0, b->d_outs, b->d_stamps, nullptr, b->d_phase, b->max_phases,
                                    (int)g.idx.size(), g.lds, g.compute, g.fm, g.threads, st));
     if (events) HIP_TRY(hipEventRecord(next_event(b), st));
+    if (use_levels && !capture) run_levels(b, b->sides[0]);
     // the queue goes after the fused launch: launched first, its resident
     // workgroups would hold every CU while the fused nets wait
     if (use_queue) {
@@ -1952,7 +1957,7 @@ static void capture_batch(htn_batch *b, void *const *outs, hipStream_t st) {
     if (e != hipSuccess) return give_up(std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
     std::string why;
     try {
-        batch_enqueue(b, outs, st, false);
+        batch_enqueue(b, outs, st, false, true);
         if (b->force_capture_failure) why = "capture failure forced by the caller";
     } catch (const Error &err) {
         why = err.msg;

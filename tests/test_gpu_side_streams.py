@@ -86,3 +86,21 @@ def test_heavy_network_does_not_wait_for_the_levels():
     assert np.array_equal(outs[0].cpu().numpy().reshape(refs[0].shape), refs[0])
     assert np.median(starts) < np.median(ends), (starts, ends)
     htn.htn_batch_destroy(b)
+
+
+def test_fused_networks_do_not_wait_for_the_levels_to_be_launched():
+    """Eager: the fused launch is issued ahead of the 40 level launches, each of
+    which takes the host some microseconds."""
+    import torch
+    nets = [create(configs.grid_network(s), lds=81920) for s in range(256)] + [_chain(0), _chain(1)]
+    outs = [htn.new_output(n) for n in nets]
+    b = htn.htn_batch_create(nets)
+    assert htn.htn_batch_level_info(b)[0] == 2
+    stream = torch.cuda.Stream()
+    waits = []
+    for _ in range(6):
+        _run(b, outs, stream)
+        t = htn.htn_batch_timestamps(b)
+        waits.append(np.median(t[:256, 0]) / t[256:, 1].max())
+    assert np.median(waits) < 0.5, waits
+    htn.htn_batch_destroy(b)
