@@ -327,7 +327,8 @@ htn_status htn_batch_set_event_timing(htn_batch_t batch, int32_t on);
 htn_status htn_batch_queue_info(htn_batch_t batch, int32_t *n_nets, int32_t *n_tasks, int32_t *error);
 /* htn_batch_level_info: *n_nets networks in the batch's level launches
  * (HTN_OPT_QUEUE), *n_levels launches with work, at most *max_items items
- * (kernel steps, packs, materialisations) in one.  Any pointer may be NULL. */
+ * (kernel steps, packs, materialisations) in one.  While phase timing is on
+ * these networks run with one launch per step.  Any pointer may be NULL.   */
 htn_status htn_batch_level_info(htn_batch_t batch, int32_t *n_nets, int32_t *n_levels, int32_t *max_items);
 htn_status htn_batch_launch_ms(htn_batch_t batch, float *prep_ms, float *fused_ms, int32_t *runs);
 void htn_batch_destroy(htn_batch_t batch);

@@ -87,10 +87,11 @@ static void run_sliced(htn::Net &n, void *out, hipStream_t st);
 
 // A network contracted on its own (htn_contract, fused) whose inputs total
 // at most this many elements materialises them inside its workgroup, which
-// saves a launch: 24 elements (the 10-qubit circuit with two wire cuts) take
-// 21.5 us with the evaluation against 24.0, but 3 652 elements (a 4x4 grid)
-// 40.3 against 28.7, where a launch of its own spreads them over the chip
-// (batches always use one).
+// saves a launch; a launch of its own spreads more of them over the chip
+// (batches always use one).  Rings of QTs with a coefficient vector per bond, a
+// call inside against a launch of its own: 64 elements 8.1 against 9.9 us, 144
+// 8.2 / 10.1, 216 11.2 / 10.9, 288 11.2 / 11.1, 600 12.4 / 11.2, 1 568 16.2 /
+// 12.4, 4 800 31.2 / 20.5.
 static constexpr int64_t kInKernelPrepMax = 256;
 
 static kern::FusedDesc fused_desc(const DeviceState &D, const Plan &P, bool in_kernel_prep, int32_t net) {
