@@ -1348,7 +1348,9 @@ void build_plan(Net &n) {
     // Per-step executor workspace: scaled inputs are written up front by
     // one launch; each kernel step then allocates its result and releases
     // its operands.
-    {
+    // Tiled steps split their sums (k_split) unless only that takes the
+    // workspace beyond what htn_contract_noalloc has.
+    auto plan_workspace = [&](bool k_split) {
         const int64_t es = dtype_size(inter_dtype(n.compute));
         FirstFit ff;
         P.ws_off.assign(P.values.size(), -1);
@@ -1397,6 +1399,10 @@ void build_plan(Net &n) {
             }
             if (!s.final_step) P.ws_off[s.c] = ff.alloc(P.values[s.c].size * es, 256);
             plan_tile_step(n, s);
+            if (!k_split && s.x_tile) {
+                s.x_split = 1;
+                s.x_kper = (int)s.tK;
+            }
             if (s.x_tile) {
                 if (s.x_split > 1) {
                     const int64_t rs = s.final_step ? dtype_size(out_dtype(n)) : es;
@@ -1430,6 +1436,11 @@ void build_plan(Net &n) {
                 if (id >= 0 && P.ws_off[id] >= 0) ff.release(P.ws_off[id]);
         }
         P.ws_bytes = std::max<int64_t>(ff.peak, 256);
+    };
+    plan_workspace(true);
+    if (P.ws_bytes > HTN_NOALLOC_SCRATCH_BYTES) {
+        plan_workspace(false);
+        if (P.ws_bytes > HTN_NOALLOC_SCRATCH_BYTES) plan_workspace(true);
     }
 
     // Fused executor.  Inputs are first materialised (permuted into their
