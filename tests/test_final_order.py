@@ -172,3 +172,34 @@ def test_batch_outlives_a_change_of_executor(compute):
         for o, ref in zip(outs, refs):
             assert np.array_equal(o.cpu().numpy().reshape(ref.shape), ref), (mode, ref.shape)
     htn.htn_batch_destroy(b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("compute", COMPUTE)
+def test_queue_levels_and_launches_agree(compute):
+    """The exchanged product as a queue's and a level's item and as launches,
+    K ranges included: the same bits, within the bound of FP64 sums."""
+    import torch
+    rng = np.random.default_rng(12)
+    ws = [_product(rng, *s, True, compute) for s in SHAPES]
+    ts = [[torch.from_numpy(t).to("cuda") for t in w.tensors] for w in ws]
+    runs = []
+    for queue in (0, 1, 2):
+        nets = [htn.htn_create(t, w.labels, w.dims, w.out_labels, compute=compute, final_sum=htn.HTN_SUM_FP64,
+                               storage=htn.HTN_F64) for t, w in zip(ts, ws)]
+        for n in nets:
+            htn.htn_set_option(n, htn.HTN_OPT_EXEC, htn.HTN_EXEC_STEPS)
+            htn.htn_set_option(n, htn.HTN_OPT_QUEUE, queue)
+        outs = [htn.new_output(n) for n in nets]
+        b = htn.htn_batch_create(nets)
+        assert htn.htn_batch_queue_info(b)[0] == (len(nets) if queue == 1 else 0)
+        assert htn.htn_batch_level_info(b)[0] == (len(nets) if queue == 0 else 0)
+        htn.htn_batch_run(b, htn.pointer_array(outs))
+        torch.cuda.synchronize()
+        runs.append([o.cpu().numpy() for o in outs])
+        htn.htn_batch_destroy(b)
+    for k, (w, (M, N, K)) in enumerate(zip(ws, SHAPES)):
+        assert np.array_equal(runs[0][k], runs[1][k]) and np.array_equal(runs[0][k], runs[2][k]), k
+        a, b = w.tensors
+        ref, mag = (a.astype(np.longdouble) @ b.astype(np.longdouble)).T, (np.abs(a) @ np.abs(b)).T
+        assert (np.abs(runs[0][k].reshape(ref.shape) - ref) <= (K + 2) * 2.0 ** -53 * mag).all(), k
