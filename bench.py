@@ -96,19 +96,19 @@ def parse():
 MARGINAL_TRAFFIC_FILES = ["paper_2410_15080_amd/csrc/" + f for f in (
     "mfma.hip", "mfma_dev.hpp", "kernels.hip", "kernels.hpp", "step_dev.hpp", "kern_common.hpp", "planner.cpp", "api.hip")]
 TRAFFIC = {
-    # profiles/k_fused_grid4x4_batch1024_f64.md: FETCH_SIZE 18 716.2 x 2047.2 B, WRITE_SIZE 181.1 x 1024 B
-    "k_fused_grid": {"read_bytes": 38_315_694, "write_bytes": 185_446, "sources": "b23f60e326e35d2a",
+    # profiles/k_fused_grid4x4_batch1024_f64.md: FETCH_SIZE 18 426.5 x 2047.2 B, WRITE_SIZE 178.8 x 1024 B
+    "k_fused_grid": {"read_bytes": 37_722_731, "write_bytes": 183_091, "sources": "ea4f1d1ea9cee571",
                      "profile": "profiles/k_fused_grid4x4_batch1024_f64.md"},
-    # profiles/k_truncate_grid4x4_qpd8_batch1024_f64.md: FETCH_SIZE 13 479.3 x 2047.2 B, WRITE_SIZE 15 553.6 x 1024 B
-    "k_truncate_qpd8": {"read_bytes": 27_594_743, "write_bytes": 15_926_886, "sources": "e5762072f8252300",
+    # profiles/k_truncate_grid4x4_qpd8_batch1024_f64.md: FETCH_SIZE 13 478.8 x 2047.2 B, WRITE_SIZE 15 552.8 x 1024 B
+    "k_truncate_qpd8": {"read_bytes": 27_593_799, "write_bytes": 15_926_067, "sources": "c61409decf621375",
                         "files": ["paper_2410_15080_amd/csrc/qpd.hip", "paper_2410_15080_amd/csrc/api.hip",
                                   "paper_2410_15080_amd/csrc/kernels.hpp"],
                         "profile": "profiles/k_truncate_grid4x4_qpd8_batch1024_f64.md"},
     # profiles/k_gemm_marginal4096_f64_f32_bf16.md: one contraction's kernels
     # (k_fold, k_gemm), FETCH_SIZE x 2047.2 B and WRITE_SIZE x 1024 B summed
-    "marginal_bf16": {"read_bytes": 23_626_944, "write_bytes": 138_531_328, "sources": "fc6d7fa7bfcade02",
+    "marginal_bf16": {"read_bytes": 26_680_543, "write_bytes": 141_605_274, "sources": "a8ee6343784cebe9",
                       "files": MARGINAL_TRAFFIC_FILES, "profile": "profiles/k_gemm_marginal4096_f64_f32_bf16.md"},
-    "marginal_f64": {"read_bytes": 99_749_016, "write_bytes": 151_014_810, "sources": "fc6d7fa7bfcade02",
+    "marginal_f64": {"read_bytes": 99_596_280, "write_bytes": 151_000_166, "sources": "a8ee6343784cebe9",
                      "files": MARGINAL_TRAFFIC_FILES, "profile": "profiles/k_gemm_marginal4096_f64_f32_bf16.md"},
 }
 TRAFFIC_SOURCES = ["paper_2410_15080_amd/csrc/fused.hpp", "paper_2410_15080_amd/csrc/kern_common.hpp",
