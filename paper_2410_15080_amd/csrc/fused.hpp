@@ -432,15 +432,15 @@ struct FMfma<float> {
 // rate of the L1 cache (64 bytes a clock, which single blocks use up) instead
 // of one round trip per 16.  A 144 x 144 x 216 step with both operands outside
 // took 262 000 cycles with single blocks and no read ahead.
-// 32 terms are summed by the matrix core, in two halves, before they join the
-// result's running sum: chains of additions K long lose more than the partial
-// sums of the register tiles and of lanes that share a sum.  Relative error of
-// 1024 64-vertex rings, geometric mean, FP64 and FP32: register tiles and
-// shared sums only 1.48e-15, 8.5e-7; here with whole chains 1.72e-15, 9.3e-7,
-// joined every 64 terms 1.34e-15, 7.4e-7, every 32 1.27e-15, 7.3e-7, every 16
-// 1.22e-15, 6.5e-7.  Batches of 60 BF16 and 256 FP64 rings, 1024 grids: 442,
-// 1042, 134 us with whole chains; 454, 1055, 134 joined every 32 terms; 477,
-// 1056, 137 every 16.
+// 32 terms are summed by the matrix core before they join the result's running
+// sum: chains of additions K long lose more than the partial sums of the
+// register tiles and of lanes that share a sum.  Relative error of 1024
+// 64-vertex rings, geometric mean, FP64 and FP32: register tiles and shared sums
+// only 1.48e-15, 8.5e-7; here with two chains of K / 2 terms 1.72e-15, 9.3e-7,
+// joined every 32 terms 1.41e-15, 7.9e-7, every 16 1.32e-15, 7.8e-7.  Batches of
+// 60 BF16 and 256 FP64 rings, 1024 grids: two chains 447, 1042, 134 us; joined
+// every 32 terms 452, 1050, 133; every 16 453, 1056, 133; as two half sums every
+// 32 (whose registers cost the grids 1 to 2 %) 456, 1058, 135 at 1.27e-15, 7.3e-7.
 template <int BM, int BN, typename T, typename P>
 __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const int K, const int bm, const int bn,
                                        const int lane, typename FMfma<T>::acc (&acc)[BM][BN]) {
@@ -461,12 +461,12 @@ __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const
         nok[j] = n < N;
         bx[j] = nok[j] ? n : 0;
     }
-    Acc half0[BM][BN], half1[BM][BN];
+    Acc part[BM][BN];
     auto clear = [&] {
 #pragma unroll
         for (int i = 0; i < BM; ++i)
 #pragma unroll
-            for (int j = 0; j < BN; ++j) half0[i][j] = half1[i][j] = Acc{0, 0, 0, 0};
+            for (int j = 0; j < BN; ++j) part[i][j] = Acc{0, 0, 0, 0};
     };
     auto join = [&] {
 #pragma unroll
@@ -474,9 +474,9 @@ __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const
 #pragma unroll
             for (int j = 0; j < BN; ++j)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[i][j][r] += half0[i][j][r] + half1[i][j][r];
+                for (int r = 0; r < 4; ++r) acc[i][j][r] += part[i][j][r];
     };
-    auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok, Acc (&half)[BM][BN]) {
+    auto mma_all = [&](T (&av)[BM], T (&bv)[BN], bool ok) {
         T a[BM], b[BN];
 #pragma unroll
         for (int i = 0; i < BM; ++i) a[i] = mok[i] && ok ? av[i] : T(0);
@@ -485,7 +485,7 @@ __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const
 #pragma unroll
         for (int i = 0; i < BM; ++i)
 #pragma unroll
-            for (int j = 0; j < BN; ++j) half[i][j] = Op::mma(a[i], b[j], half[i][j]);
+            for (int j = 0; j < BN; ++j) part[i][j] = Op::mma(a[i], b[j], part[i][j]);
     };
     T av[4][BM], bv[4][BN];
     int ao = lk * M, bo = lk * N;
@@ -523,10 +523,7 @@ __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < 4; u += 2) {
-                mma_all(ac[u], bc[u], true, half0);
-                mma_all(ac[u + 1], bc[u + 1], true, half1);
-            }
+            for (int u = 0; u < 4; ++u) mma_all(ac[u], bc[u], true);
             if (k < 16) break;
             if (++chunks == kJoin) {
                 join();
@@ -535,7 +532,7 @@ __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const
             }
         }
     }
-    // the last k < 16: a pair of slices, then up to two into the first half
+    // the last k < 16: a pair of slices, then up to two
     const bool pair = k >= 8;
     const int rest = k & 7;
     if (pair) {
@@ -548,11 +545,11 @@ __device__ __forceinline__ void mblock(P A, P B, const int M, const int N, const
     if (rest > 0) load(2, ok0 ? ao : 0, ok0 ? bo : 0);
     if (rest > 4) load(3, ok1 ? ao + 4 * M : 0, ok1 ? bo + 4 * N : 0);
     if (pair) {
-        mma_all(av[0], bv[0], true, half0);
-        mma_all(av[1], bv[1], true, half1);
+        mma_all(av[0], bv[0], true);
+        mma_all(av[1], bv[1], true);
     }
-    if (rest > 0) mma_all(av[2], bv[2], ok0, half0);
-    if (rest > 4) mma_all(av[3], bv[3], ok1, half0);
+    if (rest > 0) mma_all(av[2], bv[2], ok0);
+    if (rest > 4) mma_all(av[3], bv[3], ok1);
     join();
 }
 
