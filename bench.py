@@ -96,8 +96,8 @@ def parse():
 MARGINAL_TRAFFIC_FILES = ["paper_2410_15080_amd/csrc/" + f for f in (
     "mfma.hip", "mfma_dev.hpp", "kernels.hip", "kernels.hpp", "step_dev.hpp", "kern_common.hpp", "planner.cpp", "api.hip")]
 TRAFFIC = {
-    # profiles/k_fused_grid4x4_batch1024_f64.md: FETCH_SIZE 18 426.5 x 2047.2 B, WRITE_SIZE 178.8 x 1024 B
-    "k_fused_grid": {"read_bytes": 37_722_731, "write_bytes": 183_091, "sources": "ea4f1d1ea9cee571",
+    # profiles/k_fused_grid4x4_batch1024_f64.md: FETCH_SIZE 18 420.1 x 2047.2 B, WRITE_SIZE 178.7 x 1024 B
+    "k_fused_grid": {"read_bytes": 37_709_629, "write_bytes": 183_020, "sources": "19b129b925f5ba72",
                      "profile": "profiles/k_fused_grid4x4_batch1024_f64.md"},
     # profiles/k_truncate_grid4x4_qpd8_batch1024_f64.md: FETCH_SIZE 13 478.8 x 2047.2 B, WRITE_SIZE 15 552.8 x 1024 B
     "k_truncate_qpd8": {"read_bytes": 27_593_799, "write_bytes": 15_926_067, "sources": "c61409decf621375",
